@@ -1,7 +1,8 @@
 """Build step for libpdhg.so (gfx950) -- run by __graft_entry__.build().
 
-Each source is compiled to an object by its own hipcc process (in parallel),
-then the objects are linked into the shared library."""
+Each source (or each part of a source in PARTS) is compiled to an object by its
+own hipcc process, in parallel, then the objects are linked into the shared
+library."""
 import os
 import subprocess
 import sys
@@ -11,6 +12,7 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libpdhg.so")
 SOURCES = [os.path.join(CSRC, f) for f in ("kernels.hip", "fishnet.hip", "noalloc.hip", "capi.cpp")]
+PARTS = {"kernels.hip": 9}  # compiled once per PDHG_PART, in parallel
 HEADERS = [os.path.join(CSRC, f) for f in ("pdhg_internal.h", "sweep.h", "kernels.h")] + \
     [os.path.join(ROOT, "include", "pdhg.h")]
 OBJDIR = os.path.join(HERE, "_build")
@@ -31,14 +33,15 @@ def build(verbose: bool = False, incremental: bool = False) -> str:
     inc = ["-I", os.path.join(ROOT, "include")]
     objs, procs = [], []
     newest_header = max(os.path.getmtime(h) for h in HEADERS)
-    for src in SOURCES:
-        obj = os.path.join(OBJDIR, os.path.splitext(os.path.basename(src))[0] + ".o")
+    units = [(src, part) for src in SOURCES for part in range(PARTS.get(os.path.basename(src), 1))]
+    for src, part in units:
+        obj = os.path.join(OBJDIR, "%s%s.o" % (os.path.splitext(os.path.basename(src))[0], part or ""))
         objs.append(obj)
         if incremental and os.path.exists(obj) and \
                 os.path.getmtime(obj) > max(os.path.getmtime(src), newest_header):
             continue
         lang = [] if src.endswith(".hip") else ["-x", "hip"]
-        cmd = [HIPCC] + FLAGS + inc + ["-c"] + lang + [src, "-o", obj]
+        cmd = [HIPCC] + FLAGS + inc + ["-DPDHG_PART=%d" % part, "-c"] + lang + [src, "-o", obj]
         if verbose:
             print(" ".join(cmd), flush=True)
         procs.append((src, subprocess.Popen(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)))

@@ -20,7 +20,15 @@
 #include "kernels.h"
 #include "sweep.h"
 
+// The build compiles this file once per part (PDHG_PART = 0 .. 8) so that the
+// parts compile in parallel: a part instantiates its share of the launch
+// wrappers at the end of the file, and with them the kernels they launch.
+#ifndef PDHG_PART
+#define PDHG_PART 0
+#endif
+
 namespace pdhg {
+namespace {  // kernels a part does not launch are not emitted in it
 
 // ---------------------------------------------------------------------------
 // hot path: fused SpMV + update sweeps
@@ -1688,6 +1696,8 @@ __global__ void k_set_raw(Dev d, const double *c, const double *q, const double 
     }
 }
 
+}  // namespace
+
 // ---------------------------------------------------------------------------
 // launch wrappers
 // ---------------------------------------------------------------------------
@@ -1797,10 +1807,12 @@ void launch_dual_ad(const Dev &d, hipStream_t s)
     RM_SWITCH(d.K.rmax, { LAUNCH((k_dual_ad<T, RMV, 0>), g, d, 0); });
 }
 
+#if PDHG_PART == 0
 void launch_step_ad(const Dev &d, hipStream_t s)
 {
     if (d.batch > 0) hipLaunchKernelGGL(k_step_ad, dim3(d.batch), dim3(STEP_WG), 0, s, d);
 }
+#endif
 
 template <typename T>
 void launch_commit_ad(const Dev &d, hipStream_t s)
@@ -1865,6 +1877,7 @@ void launch_check(const Dev &d, int avg, hipStream_t s)
     });
 }
 
+#if PDHG_PART == 7
 void launch_check64(const Dev &d, const double *xs, const double *ys, hipStream_t s)
 {
     const unsigned g = sweep_grid(d, d.K.nblk + d.Kt.nblk);
@@ -1886,6 +1899,7 @@ void launch_control(const Dev &d, const CtlParams &P, int iters_done, hipStream_
     LAUNCH(k_reduce_l2, (unsigned)d.nl2, d, 1);
     LAUNCH(k_control, (unsigned)d.batch, d, P, iters_done);
 }
+#endif
 
 template <typename T>
 void launch_restart(const Dev &d, hipStream_t s)
@@ -1893,6 +1907,7 @@ void launch_restart(const Dev &d, hipStream_t s)
     LAUNCH(k_restart<T>, sweep_grid(d, d.K.nblk + d.Kt.nblk), d);
 }
 
+#if PDHG_PART == 0
 void launch_fill(double *p, int64_t n, double v, hipStream_t s) { LAUNCH(k_fill, nblk_elem(n), p, n, v); }
 
 void launch_rowmax(const OpDev &op, int remap, bool row_first, const double *rowfac,
@@ -1919,6 +1934,7 @@ void launch_scale_vals(const OpDev &op, double *v64, float *v32, bool row_first,
         LAUNCH(k_scale_vals<false>, nblk_elem(op.nrows), op.nrows, op.rp, op.ci, v64, v32, rowfac, colfac);
     }
 }
+#endif
 
 template <typename T>
 void launch_scale_data(const Dev &d, hipStream_t s)
@@ -1927,6 +1943,7 @@ void launch_scale_data(const Dev &d, hipStream_t s)
     LAUNCH(k_scale_dual<T>, nblk_elem(d.M), d);
 }
 
+#if PDHG_PART == 0
 void launch_spmv64(const OpDev &op, int remap, const double *v, double *out, double *partials,
                    const int32_t *list, const int32_t *cnt, hipStream_t s)
 {
@@ -1954,6 +1971,7 @@ void launch_inst_nrm2(const Dev &d, int primal, const double *v, double *out, hi
 {
     LAUNCH(k_inst_nrm2, (unsigned)d.batch, d.info, primal, v, out);
 }
+#endif
 
 template <typename T>
 void launch_init_point(const Dev &d, hipStream_t s)
@@ -1973,6 +1991,7 @@ void launch_point_to64(const Dev &d, int which, double *xo, double *yo, hipStrea
     LAUNCH(k_point_to64<T>, nblk_elem(d.N > d.M ? d.N : d.M), d, which, xo, yo);
 }
 
+#if PDHG_PART == 0
 void launch_unscale_x(const Dev &d, int64_t off, int64_t n, const double *xs, double *out, hipStream_t s)
 {
     LAUNCH(k_unscale_x, nblk_elem(n), d, off, n, xs, out);
@@ -2000,6 +2019,7 @@ void launch_scale_in(const Dev &d, int64_t xoff, int64_t n, int64_t yoff, int64_
     if (xin) LAUNCH(k_scale_in_x, nblk_elem(n), d, xoff, n, xin, xs);
     if (yin) LAUNCH(k_scale_in_y, nblk_elem(m), d, yoff, m, yin, ys);
 }
+#endif
 
 template <typename T>
 void launch_set_point(const Dev &d, int64_t xoff, int64_t n, int64_t yoff, int64_t m, int64_t m1,
@@ -2008,6 +2028,7 @@ void launch_set_point(const Dev &d, int64_t xoff, int64_t n, int64_t yoff, int64
     LAUNCH(k_set_point<T>, nblk_elem(n > m ? n : m), d, xoff, n, yoff, m, m1, xs, ys);
 }
 
+#if PDHG_PART == 0
 void launch_kkt_final(const Dev &d, int inst, double *out9, hipStream_t s)
 {
     LAUNCH(k_reduce_l2, (unsigned)d.nl2, d, 0);
@@ -2023,6 +2044,7 @@ void launch_adj_w(const Dev &d, const AdjBufs &a, const uint8_t *mask_y, hipStre
 {
     LAUNCH(k_adj_w, nblk_elem(d.M), d, a, mask_y);
 }
+#endif
 
 template <typename T>
 void launch_rev_primal(const Dev &d, const AdjBufs &a, const uint8_t *mask_x, hipStream_t s)
@@ -2036,6 +2058,7 @@ void launch_rev_dual(const Dev &d, const AdjBufs &a, hipStream_t s)
     RM_SWITCH(d.K.rmax, { LAUNCH((k_rev_dual<T, RMV>), (unsigned)d.K.nblk, d, a); });
 }
 
+#if PDHG_PART == 0
 void launch_adj_out(const Dev &d, const AdjBufs &a, double *gc, double *gq, double *gl, double *gu,
                     double *gx0, double *gy0, hipStream_t s)
 {
@@ -2047,27 +2070,51 @@ void launch_set_raw(const Dev &d, const double *c, const double *q, const double
 {
     LAUNCH(k_set_raw, nblk_elem(d.N > d.M ? d.N : d.M), d, c, q, l, u);
 }
+#endif
 
-#define INST(T)                                                                              \
-    template void launch_primal<T>(const Dev &, int, int, uint8_t *, hipStream_t);           \
-    template void launch_dual<T>(const Dev &, int, int, uint8_t *, hipStream_t);             \
-    template void launch_primal_ad<T>(const Dev &, hipStream_t);                             \
-    template void launch_dual_ad<T>(const Dev &, hipStream_t);                               \
+// part 0: the wrappers above and the element-wise kernels; parts 1-8: the
+// sweeps of one iterate type each
+#define INST_ELEM(T)                                                                        \
     template void launch_commit_ad<T>(const Dev &, hipStream_t);                             \
-    template void launch_kx_ad<T>(const Dev &, int, hipStream_t);                            \
-    template void launch_infeas<T>(const Dev &, const void *, const void *, hipStream_t);    \
     template void launch_save_prev<T>(const Dev &, hipStream_t);                             \
-    template void launch_check<T>(const Dev &, int, hipStream_t);                            \
     template void launch_restart<T>(const Dev &, hipStream_t);                               \
     template void launch_scale_data<T>(const Dev &, hipStream_t);                            \
     template void launch_init_point<T>(const Dev &, hipStream_t);                            \
     template void launch_epoch_start<T>(const Dev &, hipStream_t);                           \
     template void launch_point_to64<T>(const Dev &, int, double *, double *, hipStream_t);   \
     template void launch_set_point<T>(const Dev &, int64_t, int64_t, int64_t, int64_t, int64_t, \
-                                      const double *, const double *, hipStream_t);                 \
+                                      const double *, const double *, hipStream_t);
+#define INST_STEP(T)                                                                        \
+    template void launch_primal<T>(const Dev &, int, int, uint8_t *, hipStream_t);           \
+    template void launch_dual<T>(const Dev &, int, int, uint8_t *, hipStream_t);
+#define INST_AD(T)                                                                          \
+    template void launch_primal_ad<T>(const Dev &, hipStream_t);                             \
+    template void launch_dual_ad<T>(const Dev &, hipStream_t);                               \
+    template void launch_kx_ad<T>(const Dev &, int, hipStream_t);
+#define INST_INFEAS_REV(T)                                                                  \
+    template void launch_infeas<T>(const Dev &, const void *, const void *, hipStream_t);    \
     template void launch_rev_primal<T>(const Dev &, const AdjBufs &, const uint8_t *, hipStream_t); \
     template void launch_rev_dual<T>(const Dev &, const AdjBufs &, hipStream_t);
-INST(float)
-INST(double)
+#define INST_CHECK(T) template void launch_check<T>(const Dev &, int, hipStream_t);
+#if PDHG_PART == 0
+INST_ELEM(float)
+INST_ELEM(double)
+#elif PDHG_PART == 1
+INST_STEP(float)
+#elif PDHG_PART == 2
+INST_STEP(double)
+#elif PDHG_PART == 3
+INST_AD(float)
+#elif PDHG_PART == 4
+INST_AD(double)
+#elif PDHG_PART == 5
+INST_INFEAS_REV(float)
+#elif PDHG_PART == 6
+INST_CHECK(float)
+#elif PDHG_PART == 7
+INST_CHECK(double)
+#else
+INST_INFEAS_REV(double)
+#endif
 
 }  // namespace pdhg

@@ -179,6 +179,8 @@ static int load_lp(const pdhg_lp &in, HostLP &h, bool pattern_only)
 // layout planning
 // ---------------------------------------------------------------------------
 
+static size_t elem_size(int prec) { return prec == PDHG_PREC_F64 ? sizeof(double) : sizeof(float); }
+
 struct SegH {
     int64_t row0;  // local row within the instance's internal order
     int32_t nrows, lanes_log2, ineq;
@@ -191,11 +193,25 @@ constexpr int64_t SLICE_MIN = 16, SLICE_MIN_T = 16;
 static bool row_sliced(int64_t len, int S) { return S > 1 && len >= SLICE_MIN * S; }
 static bool row_sliced_t(int64_t len, int S) { return S > 1 && len >= SLICE_MIN_T * S; }
 
+// Layout of a small instance's operators (small.hip); 0: K^T, 1: K.
+struct SmallPlan {
+    int32_t level = -1;
+    std::vector<int4> task[2];
+    std::vector<uint16_t> row[2];
+    std::vector<int32_t> src[2];
+    int64_t bytes(const int64_t n, const int64_t m, int64_t es, int lv) const
+    {
+        return small_bytes(n, m, es, (int64_t)(task[0].size() + task[1].size()), (int64_t)src[0].size(),
+                           (int64_t)src[1].size(), lv);
+    }
+};
+
 struct InstPlan {
     int64_t n, m, m1, nnz;
     std::vector<int32_t> row_order;  // internal row -> caller row
     std::vector<int32_t> col_order;  // internal col -> caller col
     std::vector<SegH> segK, segT;
+    SmallPlan small;
 };
 
 struct Bins {
@@ -287,6 +303,83 @@ static void plan_instance(const HostLP &h, const Bins &bins, const Bins &tbins, 
         }
 }
 
+// Rows of lengths `len` and `sweep` lanes (log2) in the sweeps, for small.hip:
+// sorted by length, longest first, and taken 64 lanes at a time.  A row gets as
+// many lanes (a power of two) as keep its entries per lane within `cap`, at
+// most its lanes in the sweeps and at least a quarter of them (a lane adds up
+// to 4 of the sweep's partial sums).  cap starts at 16 and halves while each
+// task still has a wavefront of its own.
+static void small_rows_layout(const std::vector<int32_t> &len, const std::vector<int32_t> &sweep, int o, SmallPlan &sp)
+{
+    const int nr = (int)len.size();
+    std::vector<int32_t> ord(nr);
+    std::vector<int64_t> first(nr + 1, 0);
+    for (int r = 0; r < nr; ++r) {
+        ord[r] = r;
+        first[r + 1] = first[r] + len[r];
+    }
+    std::stable_sort(ord.begin(), ord.end(),
+                     [&](int a, int b) { return sweep[a] != sweep[b] ? sweep[a] > sweep[b] : len[a] > len[b]; });
+    auto lanes_log2 = [&](int r, int cap) {
+        int l = 0;
+        while (l < 6 && ((int64_t)cap << l) < len[r]) ++l;
+        return std::max(sweep[r] - 2, std::min(l, sweep[r]));
+    };
+    auto tasks = [&](int cap, auto &&f) {
+        int cnt = 0;
+        for (int k = 0; k < nr; ++cnt) {
+            const int l = lanes_log2(ord[k], cap), most = 64 >> l;
+            int g = 0;
+            while (k + g < nr && g < most && lanes_log2(ord[k + g], cap) == l && sweep[ord[k + g]] == sweep[ord[k]]) ++g;
+            f(k, g, l);
+            k += g;
+        }
+        return cnt;
+    };
+    int cap = 16;
+    while (cap > 1 && tasks(cap / 2, [](int, int, int) {}) <= SMALL_WG / 64) cap /= 2;
+    tasks(cap, [&](int k, int g, int l) {
+        const int per = (len[ord[k]] + (1 << l) - 1) >> l;  // the task's longest row comes first
+        sp.task[o].push_back(make_int4((int)sp.src[o].size(), per, l | ((sweep[ord[k]] - l) << 8), g));
+        for (int q = 0; q < 64; ++q) sp.row[o].push_back((uint16_t)(q < g ? ord[k + q] : 0));
+        for (int e = 0; e < per; ++e)
+            for (int lane = 0; lane < 64; ++lane) {
+                const int q = lane >> l, at = (e << l) + (lane & ((1 << l) - 1));
+                const int32_t r = ord[k + (q < g ? q : 0)];
+                const int32_t own = (int32_t)std::min<int64_t>(first[r], first[nr] - 1);
+                sp.src[o].push_back(q < g && at < len[r] ? (int32_t)first[r] + at : ~own);
+            }
+    });
+}
+
+// Whether small.hip may iterate the instance, and its layout there: the vectors
+// fit a CU's LDS, no row takes a whole workgroup or column slices, and an
+// iteration on one CU, whose time grows with the entries, is shorter than two
+// launches (8.5-9 us).  Measured, us per iteration (launches / one CU): FP32
+// 12.5k nonzeros 9.5 / 4.0, 22k 8.8 / 6.2, 30k 8.6 / 7.6, 50k 8.9 / 10.8; FP64
+// 2k 7.7 / 1.4, 12.5k 9.8 / 5.8, 27k 9.1 / 10.3.
+constexpr int64_t SMALL_ENTRY_BYTES = 150000;
+static void plan_small(const HostLP &h, int64_t es, InstPlan &p)
+{
+    SmallPlan &sp = p.small;
+    if ((es + 2) * h.nnz > SMALL_ENTRY_BYTES || small_bytes(h.n, h.m, es, 0, 0, 0, 0) > SMALL_LDS) return;
+    std::vector<int32_t> lenK(h.m), lenT(h.n), lgK(h.m), lgT(h.n), cnt(h.n, 0);
+    for (int op = 0; op < 2; ++op)
+        for (const SegH &sg : op == 0 ? p.segT : p.segK) {
+            const int lg = sg.lanes_log2 & 15;
+            if (sg.sliced || lg > 6) return;
+            auto &l = op == 0 ? lgT : lgK;
+            std::fill(l.begin() + sg.row0, l.begin() + sg.row0 + sg.nrows, lg);
+        }
+    for (int64_t k = 0; k < h.nnz; ++k) cnt[h.ci[k]]++;
+    for (int64_t i = 0; i < h.m; ++i) lenK[i] = (int32_t)(h.rp[p.row_order[i] + 1] - h.rp[p.row_order[i]]);
+    for (int64_t j = 0; j < h.n; ++j) lenT[j] = cnt[p.col_order[j]];
+    small_rows_layout(lenT, lgT, 0, sp);
+    small_rows_layout(lenK, lgK, 1, sp);
+    for (int lv = 0; lv <= 3; ++lv)
+        if (sp.bytes(h.n, h.m, es, lv) <= SMALL_LDS) sp.level = lv;
+}
+
 // ---------------------------------------------------------------------------
 // workspace carving
 // ---------------------------------------------------------------------------
@@ -307,7 +400,9 @@ struct Carve {
 struct Sizes {
     int64_t N = 0, M = 0, NNZ = 0;
     int64_t nsegK = 0, nsegT = 0, nblkK = 0, nblkT = 0, nl2 = 0;
+    int64_t small_tasks[2] = {0, 0}, small_slots[2] = {0, 0};
     int32_t batch = 0;
+    bool small = false;  // every instance is small: small.hip iterates them
 };
 
 struct Buffers {
@@ -327,6 +422,7 @@ struct Buffers {
     int64_t *bcumK, *bcumT;  // block cost prefix sums
     int32_t *Ksb, *Ktsb;     // column-slice starts of every row of K / K^T (col_slices(_t) > 1)
     double *Kpart, *Ktpart;  // FP64 partial products of the sliced rows
+    SmallDev small;
 };
 
 struct pdhg_handle {
@@ -356,8 +452,6 @@ struct pdhg_handle {
     int64_t rec_gen = 0;    // bumped by every recording pdhg_iterate and by pdhg_set_data
     std::vector<InstState> rec_st;  // step parameters of the recorded steps
 };
-
-static size_t elem_size(int prec) { return prec == PDHG_PREC_F64 ? sizeof(double) : sizeof(float); }
 
 static int ilog2(int v)
 {
@@ -430,6 +524,17 @@ static void carve(Carve &cv, const Sizes &sz, int prec, const pdhg_opts &o, Dev 
     b.Kpart = S > 1 ? cv.take<double>(2 * (size_t)M) : nullptr;
     b.Ktsb = St > 1 ? cv.take<int32_t>((size_t)N * (St - 1)) : nullptr;
     b.Ktpart = St > 1 ? cv.take<double>(N) : nullptr;
+    b.small = SmallDev{};
+    if (sz.small) {
+        b.small.inst = cv.take<SmallInst>(sz.batch);
+        for (int op = 0; op < 2; ++op) {
+            b.small.task[op] = cv.take<int4>(sz.small_tasks[op] + 1);
+            b.small.row[op] = cv.take<uint16_t>(64 * sz.small_tasks[op] + 1);
+            b.small.src[op] = cv.take<int32_t>(sz.small_slots[op] + 1);
+            b.small.val[op] = cv.take<char>((sz.small_slots[op] + 1) * es);
+            b.small.col[op] = cv.take<uint16_t>(sz.small_slots[op] + 1);
+        }
+    }
     d.actK = cv.take<int32_t>(sz.nblkK + 1);
     d.actT = cv.take<int32_t>(sz.nblkT + 1);
     d.act_cnt = cv.take<int32_t>(2);
@@ -620,8 +725,10 @@ static void parallel_items(int64_t n, int T, F &&f)
     });
 }
 
+// layouts: also plan the operators' second layouts (small.hip), which
+// take workspace of their own
 static int plan_all(const pdhg_lp *lp, int32_t batch, const pdhg_opts *o, std::vector<HostLP> &hosts,
-                    std::vector<InstPlan> &plans, Sizes &sz, bool pattern_only)
+                    std::vector<InstPlan> &plans, Sizes &sz, bool pattern_only, bool layouts = true)
 {
     if (!lp || batch < 1) return fail(PDHG_ERR_INVALID_ARG, "need lp != NULL and batch >= 1");
     int rc = check_opts(o);
@@ -647,6 +754,7 @@ static int plan_all(const pdhg_lp *lp, int32_t batch, const pdhg_opts *o, std::v
                 return;
             }
             plan_instance(hosts[b], bins, tbins, o->col_slices, o->col_slices_t, plans[b]);
+            if (layouts) plan_small(hosts[b], (int64_t)elem_size(o->precision), plans[b]);
         } catch (...) {
             rcs[b] = PDHG_ERR_NOMEM;
             msgs[b] = "host memory exhausted";
@@ -671,7 +779,13 @@ static int plan_all(const pdhg_lp *lp, int32_t batch, const pdhg_opts *o, std::v
         sz.nl2 += (pb + pt + L2CH - 1) / L2CH;
         sz.nsegK += plans[b].segK.size();
         sz.nsegT += plans[b].segT.size();
+        sz.small = (b == 0 || sz.small) && plans[b].small.level >= 0;
     }
+    for (int b = 0; b < batch && sz.small; ++b)
+        for (int op = 0; op < 2; ++op) {
+            sz.small_tasks[op] += (int64_t)plans[b].small.task[op].size();
+            sz.small_slots[op] += (int64_t)plans[b].small.src[op].size();
+        }
     // sweeps address the gathered vectors with 32-bit byte offsets
     if (sz.N >= (int64_t(1) << 29) || sz.M >= (int64_t(1) << 29))
         return fail(PDHG_ERR_SHAPE, "total n and m over the batch must be < 2^29");
@@ -679,7 +793,7 @@ static int plan_all(const pdhg_lp *lp, int32_t batch, const pdhg_opts *o, std::v
     return PDHG_OK;
 }
 
-static size_t workspace_bytes_impl(const pdhg_lp *lp, int32_t batch, const pdhg_opts *o)
+static size_t workspace_bytes_impl(const pdhg_lp *lp, int32_t batch, const pdhg_opts *o, bool layouts = true)
 {
     pdhg_opts def;
     if (!o) {
@@ -689,7 +803,7 @@ static size_t workspace_bytes_impl(const pdhg_lp *lp, int32_t batch, const pdhg_
     std::vector<HostLP> hosts;
     std::vector<InstPlan> plans;
     Sizes sz;
-    if (plan_all(lp, batch, o, hosts, plans, sz, false)) return 0;
+    if (plan_all(lp, batch, o, hosts, plans, sz, false, layouts)) return 0;
     Carve cv;
     Dev d{};
     Buffers b{};
@@ -1025,6 +1139,31 @@ static int upload(pdhg_handle *h, std::vector<HostLP> &hosts, hipStream_t s)
         (S > 1 && (rc = h2d(b.Ksb, Ksb.data(), Ksb.size(), s))) ||
         (St > 1 && (rc = h2d(b.Ktsb, Ktsb.data(), Ktsb.size(), s))))
         return rc;
+    // small instances: their tasks, row numbers and slots, concatenated
+    std::vector<SmallInst> sinst(sz.small ? h->batch : 0);
+    if (sz.small) {
+        int64_t t0[2] = {0, 0}, s0[2] = {0, 0}, lds = 0;
+        for (int bi = 0; bi < h->batch; ++bi) {
+            const SmallPlan &sp = h->plan[bi].small;
+            SmallInst &si = sinst[bi];
+            si.level = sp.level;
+            lds = std::max(lds, sp.bytes(h->plan[bi].n, h->plan[bi].m, (int64_t)elem_size(h->prec), sp.level));
+            for (int op = 0; op < 2; ++op) {
+                si.task0[op] = (int32_t)t0[op];
+                si.ntask[op] = (int32_t)sp.task[op].size();
+                si.slot0[op] = s0[op];
+                si.nslot[op] = (int32_t)sp.src[op].size();
+                if ((rc = h2d((int4 *)b.small.task[op] + t0[op], sp.task[op].data(), sp.task[op].size(), s)) ||
+                    (rc = h2d((uint16_t *)b.small.row[op] + 64 * t0[op], sp.row[op].data(), sp.row[op].size(), s)) ||
+                    (rc = h2d((int32_t *)b.small.src[op] + s0[op], sp.src[op].data(), sp.src[op].size(), s)))
+                    return rc;
+                t0[op] += si.ntask[op];
+                s0[op] += si.nslot[op];
+            }
+        }
+        b.small.lds = (uint32_t)lds;
+        if ((rc = h2d((SmallInst *)b.small.inst, sinst.data(), sinst.size(), s))) return rc;
+    }
     // the host images die with this scope: wait for the copies
     HIPCHK(hipStreamSynchronize(s));
     h->setup_phase[2] = std::chrono::duration<double>(std::chrono::steady_clock::now() - t_copy).count();
@@ -1050,6 +1189,10 @@ static int device_setup(pdhg_handle *h, hipStream_t s)
     launch_scale_vals(d.K, h->buf.Kv64, h->buf.Kv32, true, d.rho, d.kap, s);
     launch_scale_vals(d.Kt, h->buf.Ktv64, h->buf.Ktv32, false, d.kap, d.rho, s);
     launch_scale_data<T>(d, s);
+    if (h->sz.small) {
+        HIPCHK(small_prepare(h->buf.small.lds));
+        launch_small_fill<T>(d, h->buf.small, s);
+    }
     HIPCHK(hipGetLastError());
     // norms of the scaled cost and right-hand side (primal weight, Section 2.4.3)
     std::vector<double> cn2(B), qn2(B);
@@ -1168,7 +1311,7 @@ static int device_setup(pdhg_handle *h, hipStream_t s)
 // without a copy); otherwise they live at dev_done in device memory and the
 // solve loop copies them out (pdhg_setup_noalloc)
 static int setup_impl(const pdhg_lp *lp, int32_t batch, const pdhg_opts *o, void *ws, size_t ws_bytes,
-                      hipStream_t stream, pdhg_handle **out, int32_t *dev_done = nullptr)
+                      hipStream_t stream, pdhg_handle **out, int32_t *dev_done = nullptr, bool layouts = true)
 {
     auto t0 = std::chrono::steady_clock::now();
     if (!out) return fail(PDHG_ERR_INVALID_ARG, "out is NULL");
@@ -1182,7 +1325,7 @@ static int setup_impl(const pdhg_lp *lp, int32_t batch, const pdhg_opts *o, void
     if (((uintptr_t)ws & 255) != 0) return fail(PDHG_ERR_INVALID_ARG, "workspace must be 256-byte aligned");
     std::vector<HostLP> hosts;
     auto *h = new pdhg_handle();
-    int rc = plan_all(lp, batch, o, hosts, h->plan, h->sz, false);
+    int rc = plan_all(lp, batch, o, hosts, h->plan, h->sz, false, layouts);
     if (rc) {
         delete h;
         return rc;
@@ -1291,11 +1434,24 @@ extern "C" int pdhg_setup_noalloc(const pdhg_lp *lp, int32_t batch, const pdhg_o
         pdhg_default_opts(&def);
         o = &def;
     }
-    const size_t need = pdhg_workspace_bytes(lp, batch, o);
+    size_t need = pdhg_workspace_bytes(lp, batch, o);
     if (need == 0) return g_err_code;  // the sizing call's own error
     // the done flags follow the workspace in the same array
-    const size_t flags_off = (need + 255) & ~(size_t)255;
-    const size_t total = flags_off + sizeof(int32_t) * (size_t)batch;
+    size_t flags_off = (need + 255) & ~(size_t)255;
+    size_t total = flags_off + sizeof(int32_t) * (size_t)batch;
+    // what does not fit with the second layouts may fit without them
+    bool layouts = true;
+    if (total > (size_t)PDHG_NOALLOC_MAX_BYTES) {
+        layouts = false;
+        try {
+            need = workspace_bytes_impl(lp, batch, o, false);
+        } catch (...) {
+            return fail(PDHG_ERR_NOMEM, "sizing: host memory exhausted");
+        }
+        if (need == 0) return g_err_code;
+        flags_off = (need + 255) & ~(size_t)255;
+        total = flags_off + sizeof(int32_t) * (size_t)batch;
+    }
     if (total > (size_t)PDHG_NOALLOC_MAX_BYTES)
         return fail(PDHG_ERR_NOMEM, "pdhg_setup_noalloc: the LP needs %zu bytes, the fixed workspace holds %zu "
                     "(use pdhg_setup with a caller workspace)", total, (size_t)PDHG_NOALLOC_MAX_BYTES);
@@ -1314,7 +1470,8 @@ extern "C" int pdhg_setup_noalloc(const pdhg_lp *lp, int32_t batch, const pdhg_o
             return fail(PDHG_ERR_HIP, "locating the fixed workspace on device %d: %s", dev, hipGetErrorString(e));
         }
         pdhg_handle *h = nullptr;
-        const int rc = setup_impl(lp, batch, o, ptr, need, stream, &h, (int32_t *)((char *)ptr + flags_off));
+        const int rc = setup_impl(lp, batch, o, ptr, need, stream, &h, (int32_t *)((char *)ptr + flags_off),
+                                  layouts);
         if (rc) {
             noalloc_release(dev, owner);
             delete owner;
@@ -1382,6 +1539,20 @@ static CtlParams ctl_params(const pdhg_handle *h)
     return P;
 }
 
+// fixed-step iterations j0 .. j0 + count - 1 of a check period
+template <typename T>
+static void enqueue_steps(const pdhg_handle *h, const Dev &d, int j0, int count, int avg, hipStream_t s)
+{
+    if (h->sz.small) {
+        launch_small<T>(d, h->buf.small, j0, count, avg, s);
+        return;
+    }
+    for (int j = j0; j < j0 + count; ++j) {
+        launch_primal<T>(d, j, avg, nullptr, s);
+        launch_dual<T>(d, j, avg, nullptr, s);
+    }
+}
+
 // one chunk: check_every iterations, the check, the control decision, restart
 template <typename T>
 static void enqueue_chunk(const pdhg_handle *h, hipStream_t s)
@@ -1398,22 +1569,27 @@ static void enqueue_chunk(const pdhg_handle *h, hipStream_t s)
         }
         launch_commit_ad<T>(d, s);
     } else {
-        for (int j = 0; j < h->opts.check_every; ++j) {
-            if (detect && j == h->opts.check_every - 1) launch_save_prev<T>(d, s);
-            launch_primal<T>(d, j, avg, nullptr, s);
-            launch_dual<T>(d, j, avg, nullptr, s);
+        const int last = h->opts.check_every - 1;
+        if (detect) {
+            enqueue_steps<T>(h, d, 0, last, avg, s);
+            launch_save_prev<T>(d, s);
+            enqueue_steps<T>(h, d, last, 1, avg, s);
+        } else {
+            enqueue_steps<T>(h, d, 0, last + 1, avg, s);
         }
     }
-    launch_check<T>(d, avg, s);
+    const bool small = h->sz.small;
+    // the small instances' launches leave the average point ready
+    launch_check<T>(d, avg, s, !(small && !h->opts.adaptive_step));
     // Algorithm 6 on the difference of the last step: the iterate before it is
     // in (xavg1, y1) with fixed steps, in buffer 1 (xbar, y1) with adaptive ones
     if (detect) launch_infeas<T>(d, h->opts.adaptive_step ? d.xbar : d.xavg1, d.y1, s);
-    launch_control(d, ctl_params(h), h->opts.check_every, s);
+    launch_control<T>(d, ctl_params(h), h->opts.check_every, s, small);
     if (avg) {
-        launch_restart<T>(d, s);
+        if (!small) launch_restart<T>(d, s);  // k_control restarts the small instances
         if (h->opts.adaptive_step) launch_kx_ad<T>(d, 0, s);  // K~x of the restarted iterates
     }
-    launch_active(d, s, admission_budget(h), 0);
+    if (h->batch > 1) launch_active(d, s, admission_budget(h), 0);
 }
 
 template <typename T>
@@ -1470,8 +1646,8 @@ static int solve_impl(pdhg_handle *h, pdhg_result *res, hipStream_t s)
     launch_active(d, s);
     launch_epoch_start<T>(d, s);
     launch_check<T>(d, 0, s);
-    launch_control(d, ctl_params(h), 0, s);
-    launch_active(d, s);
+    launch_control<T>(d, ctl_params(h), 0, s);
+    if (B > 1) launch_active(d, s);
     if (h->opts.adaptive_step) launch_kx_ad<T>(d, 1, s);
     // every instance has had its starting-point check: those beyond the
     // admission budget wait from here on
@@ -1599,14 +1775,17 @@ static int iterate_impl(pdhg_handle *h, int64_t k, int32_t record, hipStream_t s
     launch_active(d, s);
     const int64_t C = std::max(1, h->opts.unroll_checkpoint);
     const size_t es = elem_size(h->prec);
-    for (int64_t t = 0; t < k; ++t) {
+    // steps up to the next checkpoint, in launches of a bounded length
+    int run = 1;
+    for (int64_t t = 0; t < k; t += run) {
         if (record && t % C == 0) {
             const int64_t slot = t / C;
             HIPCHK(hipMemcpyAsync((char *)h->buf.ckx + slot * d.N * es, d.x, d.N * es, hipMemcpyDeviceToDevice, s));
             HIPCHK(hipMemcpyAsync((char *)h->buf.cky + slot * d.M * es, d.y, d.M * es, hipMemcpyDeviceToDevice, s));
         }
-        launch_primal<T>(d, 0, 0, nullptr, s);
-        launch_dual<T>(d, 0, 0, nullptr, s);
+        run = (int)std::min<int64_t>(SMALL_STEPS, k - t);
+        if (record) run = (int)std::min<int64_t>(run, C - t % C);
+        enqueue_steps<T>(h, d, 0, run, 0, s);
     }
     HIPCHK(hipGetLastError());
     if (record) {
@@ -2134,7 +2313,7 @@ static int time_impl(pdhg_handle *h, int32_t reps, pdhg_kernel_times *out, hipSt
         for (int r = 0; r < reps; ++r) {
             switch (phase) {
                 case 2: launch_check<T>(d, avg, s); break;
-                case 3: launch_control(d, Pr, h->opts.check_every, s); break;
+                case 3: launch_control<T>(d, Pr, h->opts.check_every, s); break;
                 default: launch_restart<T>(d, s); break;
             }
         }
@@ -2321,6 +2500,11 @@ static int autotune_impl(const pdhg_lp *lp, int32_t batch, const pdhg_opts *base
                 bound.nsegT = std::max(bound.nsegT, sz.nsegT);
                 bound.nblkK = std::max(bound.nblkK, sz.nblkK);
                 bound.nblkT = std::max(bound.nblkT, sz.nblkT);
+                bound.small |= sz.small;
+                for (int op = 0; op < 2; ++op) {
+                    bound.small_tasks[op] = std::max(bound.small_tasks[op], sz.small_tasks[op]);
+                    bound.small_slots[op] = std::max(bound.small_slots[op], sz.small_slots[op]);
+                }
             }
         // second-level rows: sum over instances of ceil((K + K^T blocks) / L2CH)
         bound.nl2 = (bound.nblkK + bound.nblkT + L2CH - 1) / L2CH + batch;

@@ -11,6 +11,11 @@ void launch_primal(const Dev &d, int j, int avg, uint8_t *mask, hipStream_t s);
 template <typename T>
 void launch_dual(const Dev &d, int j, int avg, uint8_t *mask, hipStream_t s);
 template <typename T>
+void launch_small(const Dev &d, const SmallDev &sd, int j0, int count, int avg, hipStream_t s);
+template <typename T>
+void launch_small_fill(const Dev &d, const SmallDev &sd, hipStream_t s);
+hipError_t small_prepare(uint32_t lds_bytes);
+template <typename T>
 void launch_primal_ad(const Dev &d, hipStream_t s);
 template <typename T>
 void launch_dual_ad(const Dev &d, hipStream_t s);
@@ -24,9 +29,10 @@ void launch_infeas(const Dev &d, const void *xp, const void *yp, hipStream_t s);
 template <typename T>
 void launch_save_prev(const Dev &d, hipStream_t s);
 template <typename T>
-void launch_check(const Dev &d, int avg, hipStream_t s);
+void launch_check(const Dev &d, int avg, hipStream_t s, bool avg_point = true);
 void launch_check64(const Dev &d, const double *xs, const double *ys, hipStream_t s);
-void launch_control(const Dev &d, const CtlParams &P, int iters_done, hipStream_t s);
+template <typename T>
+void launch_control(const Dev &d, const CtlParams &P, int iters_done, hipStream_t s, int copy = 0);
 // active lists of the running instances; budget > 0 admits waiting instances
 // (first = 1: instances beyond the budget start waiting)
 void launch_active(const Dev &d, hipStream_t s, int64_t budget = 0, int first = 0);

@@ -833,6 +833,17 @@ __device__ __forceinline__ void part_acc(double (&v)[NPART], const double *p)
     for (int k = 0; k < NPART; ++k) v[k] = part_is_max(k) ? fmax(v[k], p[k]) : v[k] + p[k];
 }
 
+// first-level rows [r0, r0 + L2CH) of an instance into the lanes' partials
+__device__ __forceinline__ void part_rows(const Dev &d, const InstInfo &in, int r0, double (&v)[NPART])
+{
+    const int nK = in.blkK1 - in.blkK0, nT = in.blkT1 - in.blkT0;
+    const int r1 = min(r0 + L2CH, nK + nT);
+    for (int r = r0 + (int)threadIdx.x; r < r1; r += WG) {
+        const int lbc = r < nK ? in.blkK0 + r : d.K.nblk + in.blkT0 + (r - nK);
+        part_acc(v, d.partials + (size_t)lbc * NPART);
+    }
+}
+
 // Second level of the check reduction: block t reduces up to L2CH consecutive
 // first-level rows of its instance (K blocks first, then K^T blocks), in a
 // fixed order, so the totals of one instance do not depend on the batch.
@@ -843,15 +854,9 @@ __global__ __launch_bounds__(WG) void k_reduce_l2(Dev d, int skip_done)
     const int b = d.l2_inst[t];
     if (skip_done && d.st[b].done) return;
     const InstInfo in = d.info[b];
-    const int nK = in.blkK1 - in.blkK0, nT = in.blkT1 - in.blkT0;
-    const int r0 = (t - in.l2off) * L2CH;
-    const int r1 = min(r0 + L2CH, nK + nT);
     double v[NPART];
     part_init(v);
-    for (int r = r0 + (int)threadIdx.x; r < r1; r += WG) {
-        const int lbc = r < nK ? in.blkK0 + r : d.K.nblk + in.blkT0 + (r - nK);
-        part_acc(v, d.partials + (size_t)lbc * NPART);
-    }
+    part_rows(d, in, (t - in.l2off) * L2CH, v);
     block_reduce_part(v, lds);
     if (threadIdx.x == 0) {
         double *o = d.partials2 + (size_t)t * NPART;
@@ -860,13 +865,17 @@ __global__ __launch_bounds__(WG) void k_reduce_l2(Dev d, int skip_done)
     }
 }
 
-// Reduces the instance's second-level rows (fixed order) into tot[NPART].
+// Reduces the instance's second-level rows (fixed order) into tot[NPART]; with
+// one such row in every instance it was not formed, and this forms it.
 __device__ void reduce_instance(const Dev &d, const InstInfo &in, double *tot)
 {
     __shared__ double lds[NPART * 4];
     double v[NPART];
     part_init(v);
-    for (int t = threadIdx.x; t < in.l2cnt; t += WG) part_acc(v, d.partials2 + (size_t)(in.l2off + t) * NPART);
+    if (d.nl2 == d.batch)
+        part_rows(d, in, 0, v);
+    else
+        for (int t = threadIdx.x; t < in.l2cnt; t += WG) part_acc(v, d.partials2 + (size_t)(in.l2off + t) * NPART);
     block_reduce_part(v, lds);
     if (threadIdx.x == 0) {
 #pragma unroll
@@ -939,17 +948,10 @@ __device__ void trace_put(const Dev &d, int b, InstState &st, int cand, double k
     st.ntrace += 1;
 }
 
-// One workgroup per instance.  iters_done: iterations since the last check
-// (0 for the check of the starting point).
-__global__ __launch_bounds__(WG) void k_control(Dev d, CtlParams P, int iters_done)
+// The decision of one instance's check from its sums (one lane).
+__device__ void control_decide(const Dev &d, const CtlParams &P, int iters_done, int b, InstState &st,
+                               const InstInfo &in, const double *tot)
 {
-    __shared__ double tot[NPART];
-    const int b = blockIdx.x;
-    InstState &st = d.st[b];
-    if (st.done) return;
-    const InstInfo in = d.info[b];
-    reduce_instance(d, in, tot);
-    if (threadIdx.x != 0) return;
     if (P.adaptive) st.par = 0;  // k_commit_ad moved the current iterate to buffer 0
 
     st.k_total += iters_done;
@@ -1051,6 +1053,44 @@ __global__ __launch_bounds__(WG) void k_control(Dev d, CtlParams P, int iters_do
     trace_put(d, b, st, cand, kwc, mt, nc, P, ci);
 }
 
+// z <- candidate, epoch start <- z, for rows [r, r1) of a vector
+template <typename T>
+__device__ __forceinline__ void restart_rows(T *z, const T *za, T *z0, int cand_avg, int64_t r, int64_t r1)
+{
+    for (r += threadIdx.x; r < r1; r += WG) {
+        const T v = cand_avg ? za[r] : z[r];
+        z[r] = v;
+        z0[r] = v;
+    }
+}
+
+// One workgroup per instance.  iters_done: iterations since the last check
+// (0 for the check of the starting point).  A handle of one instance needs no
+// new block lists: its lists empty when it stops.  With `copy` the instance
+// restarts here (small instances, whose few rows cost less than k_restart's launch).
+template <typename T>
+__global__ __launch_bounds__(WG) void k_control(Dev d, CtlParams P, int iters_done, int copy)
+{
+    __shared__ double tot[NPART];
+    __shared__ int restart, cand_avg;
+    const int b = blockIdx.x;
+    InstState &st = d.st[b];
+    if (st.done) return;
+    const InstInfo in = d.info[b];
+    reduce_instance(d, in, tot);
+    if (threadIdx.x == 0) {
+        control_decide(d, P, iters_done, b, st, in, tot);
+        if (d.batch == 1 && st.done) d.act_cnt[0] = d.act_cnt[1] = 0;
+        restart = st.restart && !st.done;
+        cand_avg = st.cand_avg;
+    }
+    if (!copy) return;
+    __syncthreads();
+    if (!restart) return;
+    restart_rows((T *)d.x, (const T *)d.xam, (T *)d.x0, cand_avg, in.xoff, in.xoff + in.n);
+    restart_rows((T *)d.y, (const T *)d.yam, (T *)d.y0, cand_avg, in.yoff, in.yoff + in.m);
+}
+
 // The average point of the running instances, x0 + xavg rounded to T, into
 // (xam, yam): what the check evaluates and a restart copies.  Walks K^T blocks
 // then K blocks of the running instances.
@@ -1090,11 +1130,7 @@ __global__ __launch_bounds__(WG) void k_restart(Dev d)
         T *z = (T *)(onT ? d.x : d.y);
         const T *za = (const T *)(onT ? d.xam : d.yam);  // the average the check evaluated
         T *z0 = (T *)(onT ? d.x0 : d.y0);
-        for (int64_t r = r0 + threadIdx.x; r < r1; r += WG) {
-            const T v = st.cand_avg ? za[r] : z[r];
-            z[r] = v;
-            z0[r] = v;
-        }
+        restart_rows(z, za, z0, st.cand_avg, r0, r1);
     });
 }
 
@@ -1842,13 +1878,13 @@ void launch_save_prev(const Dev &d, hipStream_t s)
 }
 
 template <typename T>
-void launch_check(const Dev &d, int avg, hipStream_t s)
+void launch_check(const Dev &d, int avg, hipStream_t s, bool avg_point)
 {
     const unsigned g = sweep_grid(d, d.K.nblk + d.Kt.nblk);
     const T *x = (const T *)d.x, *xa = (const T *)d.xam, *x0 = (const T *)d.x0;
     const T *y = (const T *)d.y, *ya = (const T *)d.yam, *y0 = (const T *)d.y0;
     const int rm = d.K.rmax > d.Kt.rmax ? d.K.rmax : d.Kt.rmax;
-    if (avg) LAUNCH(k_avg_point<T>, sweep_grid(d, d.K.nblk + d.Kt.nblk), d);
+    if (avg && avg_point) LAUNCH(k_avg_point<T>, sweep_grid(d, d.K.nblk + d.Kt.nblk), d);
     if (d.K.slices > 1) {
         // K's sliced rows in S passes, as the sweeps take them
         const unsigned gk = sweep_grid(d, d.K.nblk);
@@ -1884,7 +1920,9 @@ void launch_check64(const Dev &d, const double *xs, const double *ys, hipStream_
     const int rm = d.K.rmax > d.Kt.rmax ? d.K.rmax : d.Kt.rmax;
     RM_SWITCH(rm, { LAUNCH((k_check<double, 1, RMV>), g, d, xs, xs, ys, ys, xs, ys, 0); });
 }
+#endif
 
+#if PDHG_PART == 0
 void launch_active(const Dev &d, hipStream_t s, int64_t budget, int first)
 {
     if (budget > 0) hipLaunchKernelGGL(k_act_admit, dim3(1), dim3(ACT_T), 0, s, d, budget, first);
@@ -1893,13 +1931,14 @@ void launch_active(const Dev &d, hipStream_t s, int64_t budget, int first)
     LAUNCH(k_act_fill, nblk_elem(n), d);
     hipLaunchKernelGGL(k_act_split, dim3(1), dim3(64), 0, s, d);
 }
-
-void launch_control(const Dev &d, const CtlParams &P, int iters_done, hipStream_t s)
-{
-    LAUNCH(k_reduce_l2, (unsigned)d.nl2, d, 1);
-    LAUNCH(k_control, (unsigned)d.batch, d, P, iters_done);
-}
 #endif
+
+template <typename T>
+void launch_control(const Dev &d, const CtlParams &P, int iters_done, hipStream_t s, int copy)
+{
+    if (d.nl2 > d.batch) LAUNCH(k_reduce_l2, (unsigned)d.nl2, d, 1);
+    LAUNCH(k_control<T>, (unsigned)d.batch, d, P, iters_done, copy);
+}
 
 template <typename T>
 void launch_restart(const Dev &d, hipStream_t s)
@@ -2031,7 +2070,7 @@ void launch_set_point(const Dev &d, int64_t xoff, int64_t n, int64_t yoff, int64
 #if PDHG_PART == 0
 void launch_kkt_final(const Dev &d, int inst, double *out9, hipStream_t s)
 {
-    LAUNCH(k_reduce_l2, (unsigned)d.nl2, d, 0);
+    if (d.nl2 > d.batch) LAUNCH(k_reduce_l2, (unsigned)d.nl2, d, 0);
     hipLaunchKernelGGL(k_kkt_final, dim3(1), dim3(WG), 0, s, d, inst, out9);
 }
 
@@ -2076,6 +2115,7 @@ void launch_set_raw(const Dev &d, const double *c, const double *q, const double
 // sweeps of one iterate type each
 #define INST_ELEM(T)                                                                        \
     template void launch_commit_ad<T>(const Dev &, hipStream_t);                             \
+    template void launch_control<T>(const Dev &, const CtlParams &, int, hipStream_t, int);  \
     template void launch_save_prev<T>(const Dev &, hipStream_t);                             \
     template void launch_restart<T>(const Dev &, hipStream_t);                               \
     template void launch_scale_data<T>(const Dev &, hipStream_t);                            \
@@ -2095,7 +2135,7 @@ void launch_set_raw(const Dev &d, const double *c, const double *q, const double
     template void launch_infeas<T>(const Dev &, const void *, const void *, hipStream_t);    \
     template void launch_rev_primal<T>(const Dev &, const AdjBufs &, const uint8_t *, hipStream_t); \
     template void launch_rev_dual<T>(const Dev &, const AdjBufs &, hipStream_t);
-#define INST_CHECK(T) template void launch_check<T>(const Dev &, int, hipStream_t);
+#define INST_CHECK(T) template void launch_check<T>(const Dev &, int, hipStream_t, bool);
 #if PDHG_PART == 0
 INST_ELEM(float)
 INST_ELEM(double)

@@ -206,6 +206,35 @@ struct FishDev {
 constexpr int FISH_GRID = 512;  // workgroups of the gap pass
 constexpr int FISH_CHUNK = 256; // longest row a lane group sums in one pass
 
+// Small LPs (small.hip): one workgroup iterates a whole instance out of LDS.
+// Index 0 is K^T (primal sweep), 1 is K.
+constexpr int SMALL_WG = 1024;
+constexpr int SMALL_STEPS = 256;           // iterations per launch at most
+constexpr int64_t SMALL_LDS = 160 * 1024;  // LDS of a CU
+struct SmallInst {
+    int32_t level;            // what lies in LDS (small_bytes())
+    int32_t task0[2], ntask[2];
+    int64_t slot0[2];
+    int32_t nslot[2];
+};
+struct SmallDev {
+    uint32_t lds;             // dynamic LDS of a launch
+    const SmallInst *inst;    // per instance
+    const int4 *task[2];      // {first slot of the instance's, entries per lane, lanes_log2 | sums_log2 << 8, rows}
+    const uint16_t *row[2];   // 64 row numbers per task, relative to the instance
+    const int32_t *src[2];    // slot -> entry of the instance (setup), ~entry: padding
+    void *val[2];             // slot values (iterate type)
+    uint16_t *col[2];         // slot columns, relative to the instance
+};
+// LDS of an instance: step weights, x, xbar, xavg, y, yavg, row numbers; from
+// level 1 on K^T's slots, from 2 on K's, from 3 on c, l, u, x0, q, y0
+__host__ __device__ constexpr int64_t small_bytes(int64_t n, int64_t m, int64_t es, int64_t ntask, int64_t slotT,
+                                                  int64_t slotK, int level)
+{
+    return 8 * SMALL_STEPS + es * (3 * n + 2 * m) + 128 * ntask + (level >= 1 ? (es + 2) * slotT : 0) +
+           (level >= 2 ? (es + 2) * slotK : 0) + (level >= 3 ? es * (4 * n + 2 * m) : 0);
+}
+
 // FP64 adjoint vectors of the unrolled-step backward pass.
 struct AdjBufs {
     double *ax, *av, *ac, *al, *au;  // length N

@@ -367,6 +367,45 @@ __host__ __device__ __forceinline__ int block_rows(int code)
     return (lanes_log2 >= 8 ? 1 : (WG >> lanes_log2)) << rows_log2;
 }
 
+// The fixed step's updates of one row (Algorithm 1, Appendices C and D), FP64
+// from the stored operands, rounded once to the iterate type.
+
+// x+ = clip(x - tau (c~ - g), l~, u~), xbar = 2 x+ - x; clip: 0 interior, 1 at l, 2 at u
+template <typename T>
+struct PrimalStep {
+    T x, xbar;
+    int clip;
+};
+template <typename T>
+__device__ __forceinline__ PrimalStep<T> primal_step(T x, double g, T c, T l, T u, double tau)
+{
+    const double xo = (double)x, lo = (double)l, hi = (double)u;
+    const double v = xo - tau * ((double)c - g);
+    const T xn = (T)(v < lo ? lo : (v > hi ? hi : v));
+    return {xn, (T)(2.0 * (double)xn - xo), v <= lo ? 1 : (v >= hi ? 2 : 0)};
+}
+
+// y+ = proj_Y(y + sigma (q~ - r)); pass: the projection passes the step through
+template <typename T>
+struct DualStep {
+    T y;
+    int pass;
+};
+template <typename T>
+__device__ __forceinline__ DualStep<T> dual_step(T y, double r, T q, double sigma, bool ineq)
+{
+    const double wv = (double)y + sigma * ((double)q - r);
+    return {(T)((ineq && wv < 0.0) ? 0.0 : wv), (!ineq || wv > 0.0) ? 1 : 0};
+}
+
+// running mean of the offsets from the epoch start z0
+template <typename T>
+__device__ __forceinline__ T average_step(T avg, T z, T z0, double w)
+{
+    const double a = (double)avg;
+    return (T)(a + (((double)z - (double)z0) - a) * w);
+}
+
 // Block-wide sum of NV per-thread values, fixed reduction order; result valid
 // in thread 0.  lds must hold NV * 4 doubles.
 template <int NV>

@@ -206,11 +206,22 @@ struct SmallPlan {
     }
 };
 
+// An operator's tiles (tile.hip); ntile 0: not tiled.
+struct TilePlan {
+    int32_t ntile = 0, width = 0;
+    std::vector<int32_t> lg;  // lanes per row (log2) of every segment
+};
+
 struct InstPlan {
     int64_t n, m, m1, nnz;
     std::vector<int32_t> row_order;  // internal row -> caller row
     std::vector<int32_t> col_order;  // internal col -> caller col
     std::vector<SegH> segK, segT;
+    std::vector<int32_t> len[2];  // row lengths in internal order; 0: K^T, 1: K (as below)
+    // sampled entries within 32 columns (rows) of the entry before them in their
+    // row (column), minus the others
+    int64_t local[2] = {0, 0};
+    TilePlan tile[2];
     SmallPlan small;
 };
 
@@ -284,6 +295,23 @@ static void plan_instance(const HostLP &h, const Bins &bins, const Bins &tbins, 
     // their per-slice count), each ordered by bin of their entry count, stable
     std::vector<int64_t> cnt(h.n, 0);
     for (int64_t k = 0; k < h.nnz; ++k) cnt[h.ci[k]]++;
+    // how many neighbouring entries of a row (of a column) share a line of the
+    // gathered vector, on four stretches of consecutive rows
+    constexpr int64_t STRETCH = 65536;
+    const int64_t ns = h.nnz > 4 * STRETCH ? 4 : 1;
+    std::vector<int32_t> last(h.n, INT32_MIN / 2);  // row of the column's entry before
+    for (int64_t w = 0; w < ns; ++w) {
+        int64_t left = ns > 1 ? STRETCH : h.nnz;
+        for (int64_t i = h.m * w / ns; i < h.m * (w + 1) / ns && left > 0; ++i) {
+            for (int64_t k = h.rp[i]; k < h.rp[i + 1]; ++k) {
+                const int32_t c = h.ci[k];
+                p.local[0] += (int32_t)i - last[c] < 32 ? 1 : -1;
+                last[c] = (int32_t)i;
+                if (k > h.rp[i]) p.local[1] += std::abs((int64_t)c - h.ci[k - 1]) < 32 ? 1 : -1;
+            }
+            left -= h.rp[i + 1] - h.rp[i];
+        }
+    }
     std::vector<std::vector<int32_t>> cb(2 * NBIN);
     for (int64_t j = 0; j < h.n; ++j) {
         const int sl = row_sliced_t(cnt[j], St) ? 1 : 0;
@@ -301,14 +329,65 @@ static void plan_instance(const HostLP &h, const Bins &bins, const Bins &tbins, 
             p.segT.push_back(sh);
             p.col_order.insert(p.col_order.end(), v.begin(), v.end());
         }
+    p.len[0].resize(h.n);
+    p.len[1].resize(h.m);
+    for (int64_t j = 0; j < h.n; ++j) p.len[0][j] = (int32_t)cnt[p.col_order[j]];
+    for (int64_t i = 0; i < h.m; ++i) p.len[1][i] = (int32_t)(h.rp[p.row_order[i] + 1] - h.rp[p.row_order[i]]);
 }
 
-// Rows of lengths `len` and `sweep` lanes (log2) in the sweeps, for small.hip:
+// Nonzeros of a handle whose operators are tiled at most: the tiles take about
+// 12 (FP32) or 20 bytes a nonzero beside the 32 of the row-binned operators, and
+// larger handles keep the card's memory for those.
+constexpr int64_t TILE_MAX_NNZ = (int64_t)4 << 30;
+
+// Lanes per row (log2) such that a lane has 2 to 4 fours of the row's entries in
+// a tile.  Measured, us (lg: 3 / 4 / 5): 31 fours a row and tile 34.4 / 36.1 /
+// 49.1, 39 fours 46 (tile of half the width) / 44.2 / 44.7.
+static int32_t tile_lg(double fours)
+{
+    int32_t l = 0;
+    while (l < 6 && (double)(4 << l) < fours) ++l;
+    return l;
+}
+
+static bool small_size(int64_t es, const InstPlan &p);
+
+// Whether tile.hip sweeps an operator of the instance: its gathers must lack
+// locality (most neighbouring entries of a row on different 128-byte lines of
+// the vector; over local columns the row-binned sweeps' gathers cost little, and
+// they took 11 us where tiles took 22-29 on a dispatch LP of 3.7M nonzeros), and
+// with several tiles the matrix must pay for each tile's way through LDS.
+// Measured, us (row bins / tiles), planted LPs in FP32: one tile, 0.9M nonzeros
+// 6.5 / 6.0, 1.2M 8.3 / 6.6, 5M 23 / 11; two tiles, 2.0M 12.4 / 15.1, 5.0M 26 /
+// 12.3; four, 12M 57 / 24; below 0.9M see tile_blocks().  Small LPs take it in
+// any case, since small.hip sums as it does.
+static void plan_tile(int64_t es, InstPlan &p)
+{
+    for (int op = 0; op < 2; ++op) {
+        TilePlan &t = p.tile[op];
+        const auto &segs = op == 0 ? p.segT : p.segK;
+        const int64_t cols = op == 0 ? p.m : p.n, rows = op == 0 ? p.n : p.m;
+        // a tile's first element lies anywhere in a 16-byte line, its width is a multiple of four
+        const int64_t cap = TILE_BYTES / es - 4, nt = (cols + cap - 1) / cap;
+        if (p.nnz == 0 || nt > TILE_SPLIT || (nt > 1 && p.nnz < 600000 + 2000000 * (nt - 1))) continue;
+        if (!small_size(es, p) && (p.nnz < 4 * rows * nt || p.local[op] > 0)) continue;
+        if (std::any_of(segs.begin(), segs.end(), [](const SegH &g) { return g.sliced != 0; })) continue;
+        t.ntile = (int32_t)nt;
+        t.width = (int32_t)(((cols + nt - 1) / nt + 3) / 4 * 4);
+        for (const SegH &g : segs) {
+            int64_t sum = 0;
+            for (int64_t r = g.row0; r < g.row0 + g.nrows; ++r) sum += p.len[op][r];
+            t.lg.push_back(tile_lg((double)sum / (4.0 * (double)nt * std::max(1, g.nrows))));
+        }
+    }
+}
+
+// Rows of lengths `len` and `sweep` lanes (log2) in tile.hip, for small.hip:
 // sorted by length, longest first, and taken 64 lanes at a time.  A row gets as
 // many lanes (a power of two) as keep its entries per lane within `cap`, at
-// most its lanes in the sweeps and at least a quarter of them (a lane adds up
-// to 4 of the sweep's partial sums).  cap starts at 16 and halves while each
-// task still has a wavefront of its own.
+// most its lanes in tile.hip and at least a quarter of them (a lane adds up
+// to 4 of their partial sums).  cap starts at 16 and halves while each task
+// still has a wavefront of its own.  Entries go to the lanes by fours.
 static void small_rows_layout(const std::vector<int32_t> &len, const std::vector<int32_t> &sweep, int o, SmallPlan &sp)
 {
     const int nr = (int)len.size();
@@ -339,12 +418,15 @@ static void small_rows_layout(const std::vector<int32_t> &len, const std::vector
     int cap = 16;
     while (cap > 1 && tasks(cap / 2, [](int, int, int) {}) <= SMALL_WG / 64) cap /= 2;
     tasks(cap, [&](int k, int g, int l) {
-        const int per = (len[ord[k]] + (1 << l) - 1) >> l;  // the task's longest row comes first
+        // the task's longest row comes first; its first lane has the most entries
+        const int fours = (len[ord[k]] + 3) / 4, full = (fours + (1 << l) - 1) >> l;
+        const int last = (fours - 1) % (1 << l) == 0 ? len[ord[k]] - 4 * (fours - 1) : 4;
+        const int per = fours > 0 ? 4 * (full - 1) + last : 0;
         sp.task[o].push_back(make_int4((int)sp.src[o].size(), per, l | ((sweep[ord[k]] - l) << 8), g));
         for (int q = 0; q < 64; ++q) sp.row[o].push_back((uint16_t)(q < g ? ord[k + q] : 0));
         for (int e = 0; e < per; ++e)
             for (int lane = 0; lane < 64; ++lane) {
-                const int q = lane >> l, at = (e << l) + (lane & ((1 << l) - 1));
+                const int q = lane >> l, at = 4 * (((e / 4) << l) + (lane & ((1 << l) - 1))) + e % 4;
                 const int32_t r = ord[k + (q < g ? q : 0)];
                 const int32_t own = (int32_t)std::min<int64_t>(first[r], first[nr] - 1);
                 sp.src[o].push_back(q < g && at < len[r] ? (int32_t)first[r] + at : ~own);
@@ -352,30 +434,30 @@ static void small_rows_layout(const std::vector<int32_t> &len, const std::vector
     });
 }
 
-// Whether small.hip may iterate the instance, and its layout there: the vectors
-// fit a CU's LDS, no row takes a whole workgroup or column slices, and an
-// iteration on one CU, whose time grows with the entries, is shorter than two
-// launches (8.5-9 us).  Measured, us per iteration (launches / one CU): FP32
-// 12.5k nonzeros 9.5 / 4.0, 22k 8.8 / 6.2, 30k 8.6 / 7.6, 50k 8.9 / 10.8; FP64
+// Whether small.hip iterates the instance: the vectors fit a CU's LDS, no column
+// slices apply, and an iteration on one CU, whose time grows with the entries, is
+// shorter than two launches (8.5-9 us).  Measured, us per iteration (launches /
+// one CU): FP32 12.5k nonzeros 9.5 / 4.0, 22k 8.8 / 6.2, 30k 8.6 / 7.6, 50k 8.9 / 10.8; FP64
 // 2k 7.7 / 1.4, 12.5k 9.8 / 5.8, 27k 9.1 / 10.3.
 constexpr int64_t SMALL_ENTRY_BYTES = 150000;
+static bool small_size(int64_t es, const InstPlan &p)
+{
+    return (es + 2) * p.nnz <= SMALL_ENTRY_BYTES && small_bytes(p.n, p.m, es, 0, 0, 0, 0) <= SMALL_LDS;
+}
+
 static void plan_small(const HostLP &h, int64_t es, InstPlan &p)
 {
     SmallPlan &sp = p.small;
-    if ((es + 2) * h.nnz > SMALL_ENTRY_BYTES || small_bytes(h.n, h.m, es, 0, 0, 0, 0) > SMALL_LDS) return;
-    std::vector<int32_t> lenK(h.m), lenT(h.n), lgK(h.m), lgT(h.n), cnt(h.n, 0);
+    if (!small_size(es, p)) return;
     for (int op = 0; op < 2; ++op)
-        for (const SegH &sg : op == 0 ? p.segT : p.segK) {
-            const int lg = sg.lanes_log2 & 15;
-            if (sg.sliced || lg > 6) return;
-            auto &l = op == 0 ? lgT : lgK;
-            std::fill(l.begin() + sg.row0, l.begin() + sg.row0 + sg.nrows, lg);
-        }
-    for (int64_t k = 0; k < h.nnz; ++k) cnt[h.ci[k]]++;
-    for (int64_t i = 0; i < h.m; ++i) lenK[i] = (int32_t)(h.rp[p.row_order[i] + 1] - h.rp[p.row_order[i]]);
-    for (int64_t j = 0; j < h.n; ++j) lenT[j] = cnt[p.col_order[j]];
-    small_rows_layout(lenT, lgT, 0, sp);
-    small_rows_layout(lenK, lgK, 1, sp);
+        if (h.nnz > 0 && p.tile[op].ntile != 1) return;
+    for (int op = 0; op < 2; ++op) {
+        std::vector<int32_t> lg(p.len[op].size(), 0);
+        const auto &segs = op == 0 ? p.segT : p.segK;
+        for (size_t k = 0; k < p.tile[op].lg.size(); ++k)
+            std::fill(lg.begin() + segs[k].row0, lg.begin() + segs[k].row0 + segs[k].nrows, p.tile[op].lg[k]);
+        small_rows_layout(p.len[op], lg, op, sp);
+    }
     for (int lv = 0; lv <= 3; ++lv)
         if (sp.bytes(h.n, h.m, es, lv) <= SMALL_LDS) sp.level = lv;
 }
@@ -403,6 +485,16 @@ struct Sizes {
     int64_t small_tasks[2] = {0, 0}, small_slots[2] = {0, 0};
     int32_t batch = 0;
     bool small = false;  // every instance is small: small.hip iterates them
+    // tile.hip: blocks, runs, quad ranges and quads of K^T (0) and K (1)
+    int64_t tile_blk[2] = {0, 0}, tile_run[2] = {0, 0}, tile_sp[2] = {0, 0}, tile_q[2] = {0, 0};
+    bool untiled[2] = {false, false};  // some instance's operator takes the row-binned sweeps
+};
+
+// The blocks of the tiled operators.
+struct TileBlocks {
+    std::vector<TileBlk> blk[2];
+    std::vector<int4> run[2];
+    std::vector<int2> inst[2];  // block range of every instance
 };
 
 struct Buffers {
@@ -423,6 +515,7 @@ struct Buffers {
     int32_t *Ksb, *Ktsb;     // column-slice starts of every row of K / K^T (col_slices(_t) > 1)
     double *Kpart, *Ktpart;  // FP64 partial products of the sliced rows
     SmallDev small;
+    TileOp tile[2];  // K^T, K
 };
 
 struct pdhg_handle {
@@ -525,6 +618,19 @@ static void carve(Carve &cv, const Sizes &sz, int prec, const pdhg_opts &o, Dev 
     b.Ktsb = St > 1 ? cv.take<int32_t>((size_t)N * (St - 1)) : nullptr;
     b.Ktpart = St > 1 ? cv.take<double>(N) : nullptr;
     b.small = SmallDev{};
+    b.tile[0] = b.tile[1] = TileOp{};
+    for (int op = 0; op < 2; ++op) {
+        TileOp &t = b.tile[op];
+        t.nblk = (int32_t)sz.tile_blk[op];
+        if (t.nblk == 0) continue;
+        t.blk = cv.take<TileBlk>(t.nblk);
+        t.run = cv.take<int4>(sz.tile_run[op]);
+        t.sp = cv.take<uint32_t>(sz.tile_sp[op]);
+        t.idx = cv.take<uint2>(sz.tile_q[op]);
+        t.val = cv.take<char>(sz.tile_q[op] * 4 * es);
+        t.inst = cv.take<int2>(sz.batch);
+        t.act = cv.take<int32_t>(t.nblk);
+    }
     if (sz.small) {
         b.small.inst = cv.take<SmallInst>(sz.batch);
         for (int op = 0; op < 2; ++op) {
@@ -537,7 +643,7 @@ static void carve(Carve &cv, const Sizes &sz, int prec, const pdhg_opts &o, Dev 
     }
     d.actK = cv.take<int32_t>(sz.nblkK + 1);
     d.actT = cv.take<int32_t>(sz.nblkT + 1);
-    d.act_cnt = cv.take<int32_t>(2);
+    d.act_cnt = cv.take<int32_t>(4);
     d.act_off = cv.take<int32_t>(2 * (size_t)sz.batch);
     d.act_coff = cv.take<int64_t>(2 * (size_t)sz.batch + 2);
     d.act_split = cv.take<int32_t>(18);
@@ -725,10 +831,101 @@ static void parallel_items(int64_t n, int T, F &&f)
     });
 }
 
-// layouts: also plan the operators' second layouts (small.hip), which
-// take workspace of their own
+// Blocks of the tiled operators: runs of rows of equal cost.  A lone LP's
+// operator has one block per CU.  In a batch an instance's share of them goes by
+// its cost among the instances that run together (the admission budget); more
+// blocks keep the chip busy when few instances are left, as long as a block's
+// matrix outweighs its loads of the vector twice.
+static void tile_blocks(const std::vector<InstPlan> &plans, const pdhg_opts *o, Sizes &sz, TileBlocks &tb)
+{
+    const int64_t es = (int64_t)elem_size(o->precision);
+    const int B = (int)plans.size();
+    auto row_cost = [&](int64_t len) { return (es + 2) * len + 24; };
+    double sweep = 0;
+    for (const InstPlan &p : plans) sweep += 2.0 * (es + 4) * p.nnz + 8.0 * (p.n + p.m + 2) + es * (9.0 * p.n + 6.0 * p.m);
+    const double part = B > 1 && o->batch_resident_bytes > 0 ? std::min(1.0, o->batch_resident_bytes / sweep) : 1.0;
+    std::vector<int64_t> xo(B + 1, 0), yo(B + 1, 0);
+    for (int b = 0; b < B; ++b) {
+        xo[b + 1] = xo[b] + plans[b].n;
+        yo[b + 1] = yo[b] + plans[b].m;
+    }
+    for (int op = 0; op < 2; ++op) {
+        auto cost = [&](const InstPlan &p) { return (double)((es + 2) * p.nnz + 24 * (int64_t)p.len[op].size()); };
+        double all = 0;
+        for (const InstPlan &p : plans) all += cost(p);
+        for (int b = 0; b < B; ++b) {
+            const InstPlan &p = plans[b];
+            const TilePlan &t = p.tile[op];
+            const int first = (int)tb.blk[op].size();
+            if (t.ntile == 0) {
+                sz.untiled[op] = true;
+                tb.inst[op].push_back(make_int2(first, first));
+                continue;
+            }
+            const auto &segs = op == 0 ? p.segT : p.segK;
+            const int64_t rows = (int64_t)p.len[op].size(), ncol = op == 0 ? p.m : p.n;
+            const double own = cost(p), share = TILE_BLOCKS * own / (part * all);
+            const double want = std::max(share, own / (2.0 * es * ncol));
+            const int64_t nb = std::max<int64_t>(1, std::min<int64_t>({(int64_t)std::ceil(want), TILE_BLOCKS, (rows + 3) / 4}));
+            double done = 0;
+            int64_t nz = 0;
+            TileBlk k{};
+            auto close = [&](int64_t r) {  // the block ends ahead of row r
+                if (k.nrows == 0) return;
+                tb.run[op].back().y = k.nrows;
+                k.nrun = (int32_t)tb.run[op].size() - k.run0;
+                k.lg0 = tb.run[op][k.run0].z;
+                k.end0 = tb.run[op][k.run0].y;
+                if (op == 1) k.nineq = (int32_t)std::max<int64_t>(0, std::min<int64_t>(k.nrows, p.m1 - (r - k.nrows)));
+                const int64_t seg = (int64_t)k.nrows * t.ntile;
+                sz.tile_sp[op] += seg + 1;
+                sz.tile_q[op] += (nz + 3 * std::min(seg, nz)) / 4 + 1;
+                tb.blk[op].push_back(k);
+                k.nrows = 0;
+            };
+            const int32_t most = std::min(TILE_ROWS, TILE_SEGS / t.ntile);
+            int64_t cut = 1;
+            double next = own / (double)nb;  // where the block in the making ends
+            for (size_t g = 0; g < segs.size(); ++g)
+                for (int64_t r = segs[g].row0; r < segs[g].row0 + segs[g].nrows; ++r) {
+                    if (k.nrows == most || (k.nrows > 0 && done >= next)) {
+                        while (done >= next && cut < nb) next = own * (double)++cut / (double)nb;
+                        close(r);
+                    }
+                    if (k.nrows == 0) {
+                        k = TileBlk{};
+                        k.sp0 = sz.tile_sp[op];
+                        k.q0 = sz.tile_q[op];
+                        k.coff = op == 0 ? yo[b] : xo[b];
+                        k.row0 = (int32_t)((op == 0 ? xo[b] : yo[b]) + r);
+                        k.inst = b;
+                        k.run0 = (int32_t)tb.run[op].size();
+                        k.ncol = (int32_t)ncol;
+                        k.width = t.width;
+                        k.ntile = t.ntile;
+                        tb.run[op].push_back(make_int4(0, 0, t.lg[g], 0));
+                        nz = 0;
+                    } else if (tb.run[op].back().z != t.lg[g]) {
+                        tb.run[op].back().y = k.nrows;
+                        tb.run[op].push_back(make_int4(k.nrows, 0, t.lg[g], 0));
+                    }
+                    ++k.nrows;
+                    nz += p.len[op][r];
+                    done += (double)row_cost(p.len[op][r]);
+                }
+            close(rows);
+            tb.inst[op].push_back(make_int2(first, (int)tb.blk[op].size()));
+        }
+        sz.tile_blk[op] = (int64_t)tb.blk[op].size();
+        sz.tile_run[op] = (int64_t)tb.run[op].size();
+    }
+}
+
+// layouts: also plan the operators' second layouts (small.hip, tile.hip),
+// which take workspace of their own
 static int plan_all(const pdhg_lp *lp, int32_t batch, const pdhg_opts *o, std::vector<HostLP> &hosts,
-                    std::vector<InstPlan> &plans, Sizes &sz, bool pattern_only, bool layouts = true)
+                    std::vector<InstPlan> &plans, Sizes &sz, bool pattern_only, bool layouts = true,
+                    TileBlocks *tiles = nullptr)
 {
     if (!lp || batch < 1) return fail(PDHG_ERR_INVALID_ARG, "need lp != NULL and batch >= 1");
     int rc = check_opts(o);
@@ -754,7 +951,10 @@ static int plan_all(const pdhg_lp *lp, int32_t batch, const pdhg_opts *o, std::v
                 return;
             }
             plan_instance(hosts[b], bins, tbins, o->col_slices, o->col_slices_t, plans[b]);
-            if (layouts) plan_small(hosts[b], (int64_t)elem_size(o->precision), plans[b]);
+            if (layouts) {
+                plan_tile((int64_t)elem_size(o->precision), plans[b]);
+                plan_small(hosts[b], (int64_t)elem_size(o->precision), plans[b]);
+            }
         } catch (...) {
             rcs[b] = PDHG_ERR_NOMEM;
             msgs[b] = "host memory exhausted";
@@ -786,6 +986,11 @@ static int plan_all(const pdhg_lp *lp, int32_t batch, const pdhg_opts *o, std::v
             sz.small_tasks[op] += (int64_t)plans[b].small.task[op].size();
             sz.small_slots[op] += (int64_t)plans[b].small.src[op].size();
         }
+    if (layouts && !sz.small && sz.NNZ <= TILE_MAX_NNZ) {
+        TileBlocks tb;
+        tile_blocks(plans, o, sz, tb);
+        if (tiles) *tiles = std::move(tb);
+    }
     // sweeps address the gathered vectors with 32-bit byte offsets
     if (sz.N >= (int64_t(1) << 29) || sz.M >= (int64_t(1) << 29))
         return fail(PDHG_ERR_SHAPE, "total n and m over the batch must be < 2^29");
@@ -836,7 +1041,7 @@ static int h2d(X *dst, const X *src, size_t cnt, hipStream_t s)
 }
 
 // builds the host images of both operators and all vectors, then uploads
-static int upload(pdhg_handle *h, std::vector<HostLP> &hosts, hipStream_t s)
+static int upload(pdhg_handle *h, std::vector<HostLP> &hosts, const TileBlocks &tiles, hipStream_t s)
 {
     const auto t_up = std::chrono::steady_clock::now();
     const Sizes &sz = h->sz;
@@ -1062,12 +1267,13 @@ static int upload(pdhg_handle *h, std::vector<HostLP> &hosts, hipStream_t s)
             sg.inst = bi;
             sg.ineq = sh.ineq;
             sg.sliced = sh.sliced;
+            sg.tiled = sz.tile_blk[1] > 0 && p.tile[1].ntile > 0;
             for (int t = 0; t < sg.nblk; ++t) {
                 Kbs[blkK + t] = (int32_t)Kseg.size();
                 const int G = seg_group(sg.lanes_log2);
                 const int64_t r0 = sg.row0 + (int64_t)t * G;
                 const int nr = (int)std::min<int64_t>(G, sg.row0 + sg.nrows - r0);
-                Kbd[blkK + t] = make_int4((int)r0, nr, bi, sg.lanes_log2 | (sg.ineq << 8) | (sg.sliced << 9));
+                Kbd[blkK + t] = make_int4((int)r0, nr, bi, sg.lanes_log2 | (sg.ineq << 8) | (sg.sliced << 9) | (sg.tiled << 10));
             }
             blkK += sg.nblk;
             Kseg.push_back(sg);
@@ -1084,12 +1290,13 @@ static int upload(pdhg_handle *h, std::vector<HostLP> &hosts, hipStream_t s)
             sg.lanes_log2 = sh.lanes_log2;
             sg.inst = bi;
             sg.ineq = 0;
+            sg.tiled = sz.tile_blk[0] > 0 && p.tile[0].ntile > 0;
             for (int t = 0; t < sg.nblk; ++t) {
                 Ktbs[blkT + t] = (int32_t)Ktseg.size();
                 const int G = seg_group(sg.lanes_log2);
                 const int64_t r0 = sg.row0 + (int64_t)t * G;
                 const int nr = (int)std::min<int64_t>(G, sg.row0 + sg.nrows - r0);
-                Ktbd[blkT + t] = make_int4((int)r0, nr, bi, sg.lanes_log2 | (sg.sliced << 9));
+                Ktbd[blkT + t] = make_int4((int)r0, nr, bi, sg.lanes_log2 | (sg.sliced << 9) | (sg.tiled << 10));
             }
             blkT += sg.nblk;
             Ktseg.push_back(sg);
@@ -1139,6 +1346,25 @@ static int upload(pdhg_handle *h, std::vector<HostLP> &hosts, hipStream_t s)
         (S > 1 && (rc = h2d(b.Ksb, Ksb.data(), Ksb.size(), s))) ||
         (St > 1 && (rc = h2d(b.Ktsb, Ktsb.data(), Ktsb.size(), s))))
         return rc;
+    d.tile_nblk[0] = b.tile[1].nblk;
+    d.tile_nblk[1] = b.tile[0].nblk;
+    for (int op = 0; op < 2; ++op) {
+        const TileOp &t = b.tile[op];
+        if (t.nblk == 0) continue;
+        // few fours per block do not pay for the tile: gathers from global memory and
+        // a quarter of the lanes to launch.  Measured, us (row bins / tile / direct),
+        // FP32 on 256 blocks: 90 fours a block 5.4 / 5.7 / 4.1, 250 5.1 / 6.4 / 5.5 and
+        // 5.3 / 5.8 / 4.7, 900 6.5 / 5.7 / 5.6, 1,200 8.3 / 6.2 / 8.5.
+        b.tile[op].direct = sz.tile_q[op] < 1000 * sz.tile_blk[op];
+        int32_t widest = 0;
+        for (const TileBlk &k : tiles.blk[op]) widest = std::max(widest, k.width);
+        b.tile[op].lds = TILE_LDS - TILE_BYTES;
+        if (!b.tile[op].direct) b.tile[op].lds += (widest * (int)elem_size(h->prec) + 31) / 16 * 16;
+        if ((rc = h2d((TileBlk *)t.blk, tiles.blk[op].data(), tiles.blk[op].size(), s)) ||
+            (rc = h2d((int4 *)t.run, tiles.run[op].data(), tiles.run[op].size(), s)) ||
+            (rc = h2d((int2 *)t.inst, tiles.inst[op].data(), tiles.inst[op].size(), s)))
+            return rc;
+    }
     // small instances: their tasks, row numbers and slots, concatenated
     std::vector<SmallInst> sinst(sz.small ? h->batch : 0);
     if (sz.small) {
@@ -1166,6 +1392,10 @@ static int upload(pdhg_handle *h, std::vector<HostLP> &hosts, hipStream_t s)
     }
     // the host images die with this scope: wait for the copies
     HIPCHK(hipStreamSynchronize(s));
+    for (InstPlan &p : h->plan) {
+        p.small = SmallPlan();
+        for (auto &l : p.len) std::vector<int32_t>().swap(l);
+    }
     h->setup_phase[2] = std::chrono::duration<double>(std::chrono::steady_clock::now() - t_copy).count();
     return PDHG_OK;
 }
@@ -1193,6 +1423,11 @@ static int device_setup(pdhg_handle *h, hipStream_t s)
         HIPCHK(small_prepare(h->buf.small.lds));
         launch_small_fill<T>(d, h->buf.small, s);
     }
+    for (int op = 0; op < 2; ++op)
+        if (h->buf.tile[op].nblk > 0) {
+            HIPCHK(tile_prepare<T>());
+            launch_tile_build<T>(op == 0 ? d.Kt : d.K, h->buf.tile[op], s);
+        }
     HIPCHK(hipGetLastError());
     // norms of the scaled cost and right-hand side (primal weight, Section 2.4.3)
     std::vector<double> cn2(B), qn2(B);
@@ -1324,8 +1559,9 @@ static int setup_impl(const pdhg_lp *lp, int32_t batch, const pdhg_opts *o, void
     if (!ws) return fail(PDHG_ERR_INVALID_ARG, "workspace is NULL");
     if (((uintptr_t)ws & 255) != 0) return fail(PDHG_ERR_INVALID_ARG, "workspace must be 256-byte aligned");
     std::vector<HostLP> hosts;
+    TileBlocks tiles;
     auto *h = new pdhg_handle();
-    int rc = plan_all(lp, batch, o, hosts, h->plan, h->sz, false, layouts);
+    int rc = plan_all(lp, batch, o, hosts, h->plan, h->sz, false, layouts, &tiles);
     if (rc) {
         delete h;
         return rc;
@@ -1387,7 +1623,7 @@ static int setup_impl(const pdhg_lp *lp, int32_t batch, const pdhg_opts *o, void
             return fail(PDHG_ERR_HIP, "hipHostGetDevicePointer failed");
         }
     }
-    rc = upload(h, hosts, stream);
+    rc = upload(h, hosts, tiles, stream);
     hosts.clear();
     auto t_dev = std::chrono::steady_clock::now();
     if (!rc) rc = h->prec == PDHG_PREC_F32 ? device_setup<float>(h, stream) : device_setup<double>(h, stream);
@@ -1539,6 +1775,32 @@ static CtlParams ctl_params(const pdhg_handle *h)
     return P;
 }
 
+// the sweeps of a fixed step: tile.hip for the tiled operators, the row-binned
+// sweeps for the others
+template <typename T>
+static void enqueue_primal(const pdhg_handle *h, const Dev &d, int j, int avg, uint8_t *mask, hipStream_t s)
+{
+    const TileOp &t = h->buf.tile[0];
+    if (t.nblk > 0) launch_primal_tile<T>(d, t, j, avg, mask, s);
+    if (t.nblk == 0 || h->sz.untiled[0]) launch_primal<T>(d, j, avg, mask, s, t.nblk > 0);
+}
+
+template <typename T>
+static void enqueue_dual(const pdhg_handle *h, const Dev &d, int j, int avg, uint8_t *mask, hipStream_t s)
+{
+    const TileOp &t = h->buf.tile[1];
+    if (t.nblk > 0) launch_dual_tile<T>(d, t, j, avg, mask, s);
+    if (t.nblk == 0 || h->sz.untiled[1]) launch_dual<T>(d, j, avg, mask, s, t.nblk > 0);
+}
+
+// block lists of the running instances
+static void enqueue_active(const pdhg_handle *h, const Dev &d, hipStream_t s, int64_t budget = 0, int first = 0)
+{
+    launch_active(d, s, budget, first);
+    if (h->batch > 1 && h->buf.tile[0].nblk + h->buf.tile[1].nblk > 0)
+        launch_act_tile(d, h->buf.tile[1], h->buf.tile[0], s);
+}
+
 // fixed-step iterations j0 .. j0 + count - 1 of a check period
 template <typename T>
 static void enqueue_steps(const pdhg_handle *h, const Dev &d, int j0, int count, int avg, hipStream_t s)
@@ -1548,8 +1810,8 @@ static void enqueue_steps(const pdhg_handle *h, const Dev &d, int j0, int count,
         return;
     }
     for (int j = j0; j < j0 + count; ++j) {
-        launch_primal<T>(d, j, avg, nullptr, s);
-        launch_dual<T>(d, j, avg, nullptr, s);
+        enqueue_primal<T>(h, d, j, avg, nullptr, s);
+        enqueue_dual<T>(h, d, j, avg, nullptr, s);
     }
 }
 
@@ -1589,7 +1851,7 @@ static void enqueue_chunk(const pdhg_handle *h, hipStream_t s)
         if (!small) launch_restart<T>(d, s);  // k_control restarts the small instances
         if (h->opts.adaptive_step) launch_kx_ad<T>(d, 0, s);  // K~x of the restarted iterates
     }
-    if (h->batch > 1) launch_active(d, s, admission_budget(h), 0);
+    if (h->batch > 1) enqueue_active(h, d, s, admission_budget(h), 0);
 }
 
 template <typename T>
@@ -1643,16 +1905,16 @@ static int solve_impl(pdhg_handle *h, pdhg_result *res, hipStream_t s)
     else
         HIPCHK(hipMemsetAsync(d.hdone, 0, sizeof(int32_t) * B, s));
     HIPCHK(hipMemcpyAsync(d.st, st.data(), B * sizeof(InstState), hipMemcpyHostToDevice, s));
-    launch_active(d, s);
+    enqueue_active(h, d, s);
     launch_epoch_start<T>(d, s);
     launch_check<T>(d, 0, s);
     launch_control<T>(d, ctl_params(h), 0, s);
-    if (B > 1) launch_active(d, s);
+    if (B > 1) enqueue_active(h, d, s);
     if (h->opts.adaptive_step) launch_kx_ad<T>(d, 1, s);
     // every instance has had its starting-point check: those beyond the
     // admission budget wait from here on
     const int64_t budget = admission_budget(h);
-    if (budget > 0) launch_active(d, s, budget, 1);
+    if (budget > 0) enqueue_active(h, d, s, budget, 1);
     HIPCHK(hipGetLastError());
 
     const int DEPTH = 4;
@@ -1772,7 +2034,7 @@ static int iterate_impl(pdhg_handle *h, int64_t k, int32_t record, hipStream_t s
                         h->opts.unroll_capacity);
     }
     HIPCHK(hipMemcpyAsync(d.st, st.data(), h->batch * sizeof(InstState), hipMemcpyHostToDevice, s));
-    launch_active(d, s);
+    enqueue_active(h, d, s);
     const int64_t C = std::max(1, h->opts.unroll_checkpoint);
     const size_t es = elem_size(h->prec);
     // steps up to the next checkpoint, in launches of a bounded length
@@ -1819,7 +2081,7 @@ static int backward_impl(pdhg_handle *h, const double *gx, const double *gy, dou
         gyd = d.vecM64b;
     }
     HIPCHK(hipMemcpyAsync(d.st, h->rec_st.data(), h->batch * sizeof(InstState), hipMemcpyHostToDevice, s));
-    launch_active(d, s);
+    enqueue_active(h, d, s);
     // keep the live iterate: the replay runs in the iterate buffers
     char *bx = (char *)b.ckx + nseg * N * es, *by = (char *)b.cky + nseg * M * es;
     HIPCHK(hipMemcpyAsync(bx, d.x, N * es, hipMemcpyDeviceToDevice, s));
@@ -1830,8 +2092,8 @@ static int backward_impl(pdhg_handle *h, const double *gx, const double *gy, dou
         HIPCHK(hipMemcpyAsync(d.x, (char *)b.ckx + sg * N * es, N * es, hipMemcpyDeviceToDevice, s));
         HIPCHK(hipMemcpyAsync(d.y, (char *)b.cky + sg * M * es, M * es, hipMemcpyDeviceToDevice, s));
         for (int64_t t = 0; t < len; ++t) {
-            launch_primal<T>(d, 0, 0, b.maskx + t * N, s);
-            launch_dual<T>(d, 0, 0, b.masky + t * M, s);
+            enqueue_primal<T>(h, d, 0, 0, b.maskx + t * N, s);
+            enqueue_dual<T>(h, d, 0, 0, b.masky + t * M, s);
         }
         for (int64_t t = len - 1; t >= 0; --t) {
             launch_adj_w(d, a, b.masky + t * M, s);
@@ -2232,7 +2494,7 @@ static int time_impl(pdhg_handle *h, int32_t reps, pdhg_kernel_times *out, hipSt
     std::vector<InstState> st = h->st0;
     for (auto &x : st) x.done = 0;
     HIPCHK(hipMemcpyAsync(d.st, st.data(), h->batch * sizeof(InstState), hipMemcpyHostToDevice, s));
-    launch_active(d, s);
+    enqueue_active(h, d, s);
     // an event between every two launches, created up front
     const int NE = 3 * reps + 1;
     std::vector<hipEvent_t> ev(NE, nullptr);
@@ -2285,8 +2547,8 @@ static int time_impl(pdhg_handle *h, int32_t reps, pdhg_kernel_times *out, hipSt
     // the two sweeps alternate as in the iteration (each one finds the caches
     // as the other leaves them)
     time_seq(2, [&](int k, int r) {
-        if (k == 0) launch_primal<T>(d, r, avg, nullptr, s);
-        else launch_dual<T>(d, r, avg, nullptr, s);
+        if (k == 0) enqueue_primal<T>(h, d, r, avg, nullptr, s);
+        else enqueue_dual<T>(h, d, r, avg, nullptr, s);
     }, ms);
     // once-per-chunk kernels, back to back, each on the path a check takes
     // when it restarts: the control kernel runs a whole check decision (a
@@ -2324,7 +2586,7 @@ static int time_impl(pdhg_handle *h, int32_t reps, pdhg_kernel_times *out, hipSt
             // restore the state the timed launches changed
             if (hipMemcpyAsync(d.st, st.data(), h->batch * sizeof(InstState), hipMemcpyHostToDevice, s) != hipSuccess)
                 rc = fail(PDHG_ERR_HIP, "state restore failed");
-            launch_active(d, s);
+            enqueue_active(h, d, s);
         }
     }
     // adaptive attempts: the primal sweep, the dual sweep and the step
@@ -2339,7 +2601,7 @@ static int time_impl(pdhg_handle *h, int32_t reps, pdhg_kernel_times *out, hipSt
         // the step kernel flips buffers: restore the state
         if (hipMemcpyAsync(d.st, st.data(), h->batch * sizeof(InstState), hipMemcpyHostToDevice, s) != hipSuccess)
             rc = fail(PDHG_ERR_HIP, "state restore failed");
-        launch_active(d, s);
+        enqueue_active(h, d, s);
     }
     for (auto &e : ev)
         if (e) (void)hipEventDestroy(e);
@@ -2501,6 +2763,12 @@ static int autotune_impl(const pdhg_lp *lp, int32_t batch, const pdhg_opts *base
                 bound.nblkK = std::max(bound.nblkK, sz.nblkK);
                 bound.nblkT = std::max(bound.nblkT, sz.nblkT);
                 bound.small |= sz.small;
+                for (int op = 0; op < 2; ++op) {
+                    bound.tile_blk[op] = std::max(bound.tile_blk[op], sz.tile_blk[op]);
+                    bound.tile_run[op] = std::max(bound.tile_run[op], sz.tile_run[op]);
+                    bound.tile_sp[op] = std::max(bound.tile_sp[op], sz.tile_sp[op]);
+                    bound.tile_q[op] = std::max(bound.tile_q[op], sz.tile_q[op]);
+                }
                 for (int op = 0; op < 2; ++op) {
                     bound.small_tasks[op] = std::max(bound.small_tasks[op], sz.small_tasks[op]);
                     bound.small_slots[op] = std::max(bound.small_slots[op], sz.small_slots[op]);

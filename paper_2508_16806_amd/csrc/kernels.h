@@ -7,9 +7,18 @@
 namespace pdhg {
 
 template <typename T>
-void launch_primal(const Dev &d, int j, int avg, uint8_t *mask, hipStream_t s);
+void launch_primal(const Dev &d, int j, int avg, uint8_t *mask, hipStream_t s, int untiled = 0);
 template <typename T>
-void launch_dual(const Dev &d, int j, int avg, uint8_t *mask, hipStream_t s);
+void launch_dual(const Dev &d, int j, int avg, uint8_t *mask, hipStream_t s, int untiled = 0);
+template <typename T>
+void launch_primal_tile(const Dev &d, const TileOp &op, int j, int avg, uint8_t *mask, hipStream_t s);
+template <typename T>
+void launch_dual_tile(const Dev &d, const TileOp &op, int j, int avg, uint8_t *mask, hipStream_t s);
+template <typename T>
+void launch_tile_build(const OpDev &op, const TileOp &to, hipStream_t s);
+template <typename T>
+hipError_t tile_prepare();
+void launch_act_tile(const Dev &d, const TileOp &K, const TileOp &Kt, hipStream_t s);
 template <typename T>
 void launch_small(const Dev &d, const SmallDev &sd, int j0, int count, int avg, hipStream_t s);
 template <typename T>

@@ -50,6 +50,8 @@ namespace {  // kernels a part does not launch are not emitted in it
 //   SL = 2  pass S-1: the sliced rows add their last slice to the partial,
 //           the rows of unsliced segments are swept whole, and every row is
 //           updated as with SL = 0.
+// SL + 4: the same without the rows that tile.hip sweeps (a batch of both kinds;
+// a role of its own, since the test of each block costs the sweeps 5%).
 // The partial store and the update stores are in different launches, so no
 // launch chooses between two store targets for one row.
 
@@ -74,9 +76,10 @@ __device__ __forceinline__ void slice_partial(const OpDev &op, const Seg &s, int
 
 // MASK: also record the clip region of x (0 interior, 1 at l, 2 at u) for the
 // adjoint replay (whole rows only).
-template <typename T, int AVG, int MASK, int RM, int SL>
+template <typename T, int AVG, int MASK, int RM, int SLX>
 __global__ __launch_bounds__(WG) void k_primal(Dev d, int j_in_chunk, uint8_t *__restrict__ mask, int pass)
 {
+    constexpr int SL = SLX & 3;
     __shared__ double red[8];
     const OpDev &op = d.Kt;
     T *__restrict__ x = (T *)d.x;
@@ -93,6 +96,7 @@ __global__ __launch_bounds__(WG) void k_primal(Dev d, int j_in_chunk, uint8_t *_
         const int lb = full ? it : d.actT[it];
         const Seg s = block_seg(op, lb);
         if (SL == 1 && !s.sliced) return;
+        if ((SLX & 4) && s.tiled) return;
         const InstState *st = d.st + s.inst;
         const double tau = st->tau;
         const double w = AVG ? 1.0 / (double)(st->t_inner + j_in_chunk + 1) : 0.0;
@@ -143,9 +147,10 @@ __global__ __launch_bounds__(WG) void k_primal(Dev d, int j_in_chunk, uint8_t *_
     });
 }
 
-template <typename T, int AVG, int MASK, int RM, int SL>
+template <typename T, int AVG, int MASK, int RM, int SLX>
 __global__ __launch_bounds__(WG) void k_dual(Dev d, int j_in_chunk, uint8_t *__restrict__ mask, int pass)
 {
+    constexpr int SL = SLX & 3;
     __shared__ double red[8];
     const OpDev &op = d.K;
     T *__restrict__ y = (T *)d.y;
@@ -159,6 +164,7 @@ __global__ __launch_bounds__(WG) void k_dual(Dev d, int j_in_chunk, uint8_t *__r
         const int lb = full ? it : d.actK[it];
         const Seg s = block_seg(op, lb);
         if (SL == 1 && !s.sliced) return;
+        if ((SLX & 4) && s.tiled) return;
         const InstState *st = d.st + s.inst;
         const double sigma = st->sigma;
         const double w = AVG ? 1.0 / (double)(st->t_inner + j_in_chunk + 1) : 0.0;
@@ -1080,7 +1086,7 @@ __global__ __launch_bounds__(WG) void k_control(Dev d, CtlParams P, int iters_do
     reduce_instance(d, in, tot);
     if (threadIdx.x == 0) {
         control_decide(d, P, iters_done, b, st, in, tot);
-        if (d.batch == 1 && st.done) d.act_cnt[0] = d.act_cnt[1] = 0;
+        if (d.batch == 1 && st.done) d.act_cnt[0] = d.act_cnt[1] = d.act_cnt[2] = d.act_cnt[3] = 0;
         restart = st.restart && !st.done;
         cand_avg = st.cand_avg;
     }
@@ -1231,6 +1237,8 @@ __global__ __launch_bounds__(ACT_T) void k_act_scan(Dev d)
     if (t == 0) {
         d.act_cnt[0] = (int32_t)carry[0];
         d.act_cnt[1] = (int32_t)carry[1];
+        if (B == 1)  // a batch's tile lists come from k_act_tile
+            for (int o = 0; o < 2; ++o) d.act_cnt[2 + o] = d.st[0].done == 0 ? d.tile_nblk[o] : 0;
         d.act_coff[2 * B] = carry[2];
         d.act_coff[2 * B + 1] = carry[3];
     }
@@ -1767,7 +1775,7 @@ static inline unsigned sweep_grid(const Dev &d, int64_t nitems)
     } while (0)
 
 template <typename T>
-void launch_primal(const Dev &d, int j, int avg, uint8_t *mask, hipStream_t s)
+void launch_primal(const Dev &d, int j, int avg, uint8_t *mask, hipStream_t s, int untiled)
 {
     const unsigned g = sweep_grid(d, d.Kt.nblk);
     if (d.Kt.slices > 1 && !mask) {
@@ -1775,7 +1783,11 @@ void launch_primal(const Dev &d, int j, int avg, uint8_t *mask, hipStream_t s)
         const int last = d.Kt.slices - 1;
         RM_SWITCH(d.Kt.rmax, {
             for (int pass = 0; pass < last; ++pass) LAUNCH((k_primal<T, 0, 0, RMV, 1>), g, d, j, nullptr, pass);
-            if (avg) {
+            if (untiled && avg) {
+                LAUNCH((k_primal<T, 1, 0, RMV, 6>), g, d, j, nullptr, last);
+            } else if (untiled) {
+                LAUNCH((k_primal<T, 0, 0, RMV, 6>), g, d, j, nullptr, last);
+            } else if (avg) {
                 LAUNCH((k_primal<T, 1, 0, RMV, 2>), g, d, j, nullptr, last);
             } else {
                 LAUNCH((k_primal<T, 0, 0, RMV, 2>), g, d, j, nullptr, last);
@@ -1784,7 +1796,13 @@ void launch_primal(const Dev &d, int j, int avg, uint8_t *mask, hipStream_t s)
         return;
     }
     RM_SWITCH(d.Kt.rmax, {
-        if (mask) {
+        if (untiled && mask) {
+            LAUNCH((k_primal<T, 0, 1, RMV, 4>), g, d, j, mask, 0);
+        } else if (untiled && avg) {
+            LAUNCH((k_primal<T, 1, 0, RMV, 4>), g, d, j, mask, 0);
+        } else if (untiled) {
+            LAUNCH((k_primal<T, 0, 0, RMV, 4>), g, d, j, mask, 0);
+        } else if (mask) {
             LAUNCH((k_primal<T, 0, 1, RMV, 0>), g, d, j, mask, 0);
         } else if (avg) {
             LAUNCH((k_primal<T, 1, 0, RMV, 0>), g, d, j, mask, 0);
@@ -1795,14 +1813,18 @@ void launch_primal(const Dev &d, int j, int avg, uint8_t *mask, hipStream_t s)
 }
 
 template <typename T>
-void launch_dual(const Dev &d, int j, int avg, uint8_t *mask, hipStream_t s)
+void launch_dual(const Dev &d, int j, int avg, uint8_t *mask, hipStream_t s, int untiled)
 {
     const unsigned g = sweep_grid(d, d.K.nblk);
     if (d.K.slices > 1 && !mask) {
         const int last = d.K.slices - 1;
         RM_SWITCH(d.K.rmax, {
             for (int pass = 0; pass < last; ++pass) LAUNCH((k_dual<T, 0, 0, RMV, 1>), g, d, j, nullptr, pass);
-            if (avg) {
+            if (untiled && avg) {
+                LAUNCH((k_dual<T, 1, 0, RMV, 6>), g, d, j, nullptr, last);
+            } else if (untiled) {
+                LAUNCH((k_dual<T, 0, 0, RMV, 6>), g, d, j, nullptr, last);
+            } else if (avg) {
                 LAUNCH((k_dual<T, 1, 0, RMV, 2>), g, d, j, nullptr, last);
             } else {
                 LAUNCH((k_dual<T, 0, 0, RMV, 2>), g, d, j, nullptr, last);
@@ -1811,7 +1833,13 @@ void launch_dual(const Dev &d, int j, int avg, uint8_t *mask, hipStream_t s)
         return;
     }
     RM_SWITCH(d.K.rmax, {
-        if (mask) {
+        if (untiled && mask) {
+            LAUNCH((k_dual<T, 0, 1, RMV, 4>), g, d, j, mask, 0);
+        } else if (untiled && avg) {
+            LAUNCH((k_dual<T, 1, 0, RMV, 4>), g, d, j, mask, 0);
+        } else if (untiled) {
+            LAUNCH((k_dual<T, 0, 0, RMV, 4>), g, d, j, mask, 0);
+        } else if (mask) {
             LAUNCH((k_dual<T, 0, 1, RMV, 0>), g, d, j, mask, 0);
         } else if (avg) {
             LAUNCH((k_dual<T, 1, 0, RMV, 0>), g, d, j, mask, 0);
@@ -2125,8 +2153,8 @@ void launch_set_raw(const Dev &d, const double *c, const double *q, const double
     template void launch_set_point<T>(const Dev &, int64_t, int64_t, int64_t, int64_t, int64_t, \
                                       const double *, const double *, hipStream_t);
 #define INST_STEP(T)                                                                        \
-    template void launch_primal<T>(const Dev &, int, int, uint8_t *, hipStream_t);           \
-    template void launch_dual<T>(const Dev &, int, int, uint8_t *, hipStream_t);
+    template void launch_primal<T>(const Dev &, int, int, uint8_t *, hipStream_t, int);      \
+    template void launch_dual<T>(const Dev &, int, int, uint8_t *, hipStream_t, int);
 #define INST_AD(T)                                                                          \
     template void launch_primal_ad<T>(const Dev &, hipStream_t);                             \
     template void launch_dual_ad<T>(const Dev &, hipStream_t);                               \

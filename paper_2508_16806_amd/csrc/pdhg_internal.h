@@ -50,6 +50,7 @@ struct Seg {
     int32_t inst;
     int32_t ineq;       // rows of this segment are ">=" rows (dual operator only)
     int32_t sliced;     // rows swept in column slices (opts.col_slices / col_slices_t)
+    int32_t tiled;      // rows of an operator that tile.hip sweeps
 };
 
 struct OpDev {
@@ -60,7 +61,7 @@ struct OpDev {
     const double *v64;   // scaled values, FP64 (after setup)
     const Seg *seg;
     const int32_t *blk_seg;
-    const int4 *bdesc;   // per logical block: {first row, rows, instance, lanes_log2 | ineq << 8 | sliced << 9}
+    const int4 *bdesc;   // per logical block: {first row, rows, instance, lanes_log2 | ineq << 8 | sliced << 9 | tiled << 10}
     int32_t nseg;
     int32_t nblk;
     int32_t rmax;        // largest rows per lane group in any block (1, 2, 4)
@@ -162,7 +163,8 @@ struct Dev {
     const int32_t *l2_inst;       // instance of each second-level row
     int32_t nl2;
     int32_t *actK, *actT;         // logical blocks of running instances (K, K^T sweeps)
-    int32_t *act_cnt;             // [2]: lengths of actK, actT
+    int32_t *act_cnt;             // [4]: lengths of actK, actT and of the tile lists of K, K^T
+    int32_t tile_nblk[2];         // tile blocks of K, K^T
     int32_t *act_off;             // [2 * batch]: list offsets per instance
     // XCD split of the sweeps' active lists by cost: bcum = prefix sums of the
     // blocks' cost (entries + 4 per row) in block order, act_coff the list
@@ -234,6 +236,39 @@ __host__ __device__ constexpr int64_t small_bytes(int64_t n, int64_t m, int64_t 
     return 8 * SMALL_STEPS + es * (3 * n + 2 * m) + 128 * ntask + (level >= 1 ? (es + 2) * slotT : 0) +
            (level >= 2 ? (es + 2) * slotK : 0) + (level >= 3 ? es * (4 * n + 2 * m) : 0);
 }
+
+// Sweeps that gather from LDS (tile.hip).
+constexpr int TILE_WG = 1024;
+constexpr int TILE_BYTES = 128 * 1024;         // LDS of a tile of the gathered vector
+constexpr int TILE_ROWS = 1280;                // rows of a block at most (<= 2 TILE_WG)
+constexpr int TILE_LDS = TILE_BYTES + 8 * TILE_ROWS + 4 * (TILE_ROWS + 4);  // of a block at most
+constexpr int TILE_SPLIT = 8;                  // tiles of an operator at most
+constexpr int TILE_SEGS = 10240;               // rows x tiles of a block at most
+constexpr int TILE_BLOCKS = 256;               // blocks of a lone LP's operator (one per CU)
+constexpr int TILE_GRID = 4096;                // workgroups of a launch at most
+struct TileBlk {
+    int64_t sp0;        // first quad range in sp (tile by tile, row by row; relative to q0)
+    int64_t q0;         // first quad
+    int64_t coff;       // first column of the instance
+    int32_t row0;       // first row
+    int32_t nrows, nineq;  // rows, ">=" rows among them (they come first)
+    int32_t inst;
+    int32_t run0, nrun; // runs of rows with the same lanes per row
+    int32_t lg0, end0;  // the first run's lanes (log2) and end row
+    int32_t ncol, width, ntile;
+};
+struct TileOp {
+    int32_t nblk;       // 0: no instance's operator is tiled
+    int32_t direct;     // gathers from global memory, 256 lanes a workgroup (few entries per block)
+    int32_t lds;        // dynamic LDS of a workgroup
+    const TileBlk *blk;
+    const int4 *run;    // {first row in the block, end row, lanes_log2, 0}
+    uint32_t *sp;
+    uint2 *idx;         // four 16-bit columns per quad
+    void *val;          // four values per quad, iterate type
+    const int2 *inst;   // block range per instance
+    int32_t *act;       // blocks of the running instances
+};
 
 // FP64 adjoint vectors of the unrolled-step backward pass.
 struct AdjBufs {

@@ -14,10 +14,10 @@
 // contiguous.  The layout, the columns (16 bit, relative to the instance) and
 // the updates' operands are copied to LDS once per launch as far as they fit.
 //
-// A lane keeps 1, 2 or 4 partial sums, one for each lane that the sweeps
-// (k_primal / k_dual) would give the row in its place, and adds them in the
-// sweeps' order: the results are the sweeps' bit for bit, and a handle may take
-// either path.
+// A row's sum is formed as in tile.hip (fours of entries, dealt out to the row's
+// lanes there; a lane here keeps 1, 2 or 4 of those lanes' partial sums and
+// adds them in their order): the results are the same bit for bit, and a batch
+// of small and larger LPs takes tile.hip for all of them.
 //
 // Measured, us per iteration (two launches / here): FP64 200 x 500 with 2.0k
 // nonzeros 7.7 / 1.4; FP32 1003 x 2501 with 12.5k nonzeros 9.5 / 4.0.
@@ -41,10 +41,9 @@ struct SmallSlots {
     int ntask;
 };
 
-// U (<= 4) consecutive entries of every lane, loads ahead of the products, into
-// NS partial sums in turn
-template <int U, int NS, typename T>
-__device__ __forceinline__ void small_slots(double (&acc)[NS], const T *v, const uint16_t *c, const T *vec)
+// the products of U (<= 4) consecutive entries of every lane, loads ahead
+template <int U, typename T>
+__device__ __forceinline__ double small_four(const T *v, const uint16_t *c, const T *vec)
 {
     T a[U], b[U];
     uint32_t ci[U];
@@ -55,21 +54,31 @@ __device__ __forceinline__ void small_slots(double (&acc)[NS], const T *v, const
     }
 #pragma unroll
     for (int q = 0; q < U; ++q) b[q] = vec[ci[q]];
+    double s = (double)a[0] * (double)b[0];
 #pragma unroll
-    for (int q = 0; q < U; ++q) acc[q % NS] += (double)a[q] * (double)b[q];
+    for (int q = 1; q < U; ++q) s += (double)a[q] * (double)b[q];
+    return s;
 }
 
+// a lane's k entries by fours into NS partial sums in turn, and their sum
 template <int NS, typename T>
 __device__ __forceinline__ double small_lane(int k, const T *v, const uint16_t *c, const T *vec)
 {
     double acc[NS] = {};
-    for (; k >= 4; k -= 4, v += 256, c += 256) small_slots<4, NS>(acc, v, c, vec);
-    if (k == 3)
-        small_slots<3, NS>(acc, v, c, vec);
-    else if (k == 2)
-        small_slots<2, NS>(acc, v, c, vec);
-    else if (k == 1)
-        small_slots<1, NS>(acc, v, c, vec);
+    for (; k >= 4 * NS; k -= 4 * NS, v += 256 * NS, c += 256 * NS) {
+#pragma unroll
+        for (int q = 0; q < NS; ++q) acc[q] += small_four<4>(v + 256 * q, c + 256 * q, vec);
+    }
+#pragma unroll
+    for (int q = 0; q < NS; ++q) {  // the rest: fewer than NS fours and a part of one
+        if (k >= 4) {
+            acc[q] += small_four<4>(v, c, vec);
+            k -= 4, v += 256, c += 256;
+        } else if (k > 0) {
+            acc[q] += k == 3 ? small_four<3>(v, c, vec) : k == 2 ? small_four<2>(v, c, vec) : small_four<1>(v, c, vec);
+            k = 0;
+        }
+    }
     if constexpr (NS == 4) return (acc[0] + acc[2]) + (acc[1] + acc[3]);
     if constexpr (NS == 2) return acc[0] + acc[1];
     return acc[0];

@@ -99,6 +99,7 @@ __device__ __forceinline__ Seg block_seg(const OpDev &op, int lb)
     s.lanes_log2 = v.w & 0xff;  // lanes (bits 0-3) and rows per group (bits 4-5)
     s.ineq = (v.w >> 8) & 1;
     s.sliced = (v.w >> 9) & 1;
+    s.tiled = (v.w >> 10) & 1;
     return s;
 }
 

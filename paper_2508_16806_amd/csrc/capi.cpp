@@ -1461,28 +1461,29 @@ static int device_setup(pdhg_handle *h, hipStream_t s)
         return PDHG_OK;
     };
     int left = B;
+    // b is normalised as it is gathered (its norm^2 in sc); a batch's lists are
+    // rebuilt at the polls (an instance that has stopped ignores its sweeps)
+    const double *nb = nullptr;
     for (int it = 0; it < o.power_max_iters; ++it) {
-        launch_spmv64(d.K, d.remap, bv, wv, pk, lK, cK, s);
+        launch_spmv64(d.K, d.remap, bv, nb, wv, pk, lK, cK, s);
         if (it > 0) {
-            launch_inst_sum(d, 1, pk, sc, s);
-            launch_power_test(d, sc, it, o.power_tol, 0, s);
-            launch_active(d, s);
+            launch_power_test(d, pk, it, o.power_tol, 0, s);
             if (it % POLL == 0) {
                 if (remaining(&left)) return PDHG_ERR_HIP;
                 if (left == 0) break;
+                if (B > 1) launch_active(d, s);
             }
         }
-        launch_spmv64(d.Kt, d.remap, wv, bt, pt, lT, cT, s);
-        launch_inst_sum(d, 0, pt, sc + B, s);
-        launch_normalize(bt, d.inst_of_col, d.N, sc + B, s);
+        launch_spmv64(d.Kt, d.remap, wv, nullptr, bt, pt, lT, cT, s);
+        launch_inst_sum(d, 0, pt, sc, s);
+        nb = sc;
         std::swap(bv, bt);
     }
     if (remaining(&left)) return PDHG_ERR_HIP;
     if (left > 0) {
         // the pass limit: every instance still iterating takes ||K b|| of its last b
-        launch_spmv64(d.K, d.remap, bv, wv, pk, lK, cK, s);
-        launch_inst_sum(d, 1, pk, sc, s);
-        launch_power_test(d, sc, o.power_max_iters, o.power_tol, 1, s);
+        launch_spmv64(d.K, d.remap, bv, nb, wv, pk, lK, cK, s);
+        launch_power_test(d, pk, o.power_max_iters, o.power_tol, 1, s);
         if (remaining(&left)) return PDHG_ERR_HIP;
     }
     for (int b = 0; b < B; ++b) {

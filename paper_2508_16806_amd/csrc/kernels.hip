@@ -1338,19 +1338,26 @@ __global__ void k_ruiz_update(double *fac, const double *mx, int64_t n)
     if (i < n && mx[i] > 0.0) fac[i] = fac[i] / sqrt(mx[i]);
 }
 
-// scaled values (rho_i * K_ij) * kap_j in FP64 (and FP32 when v32 != null)
+// scaled values (rho_i * K_ij) * kap_j in FP64 (and FP32 when v32 != null), the
+// lanes of a block over the entries of its rows, which are contiguous (one lane
+// per row took 6.7 ms on 15M nonzeros with rows of 4,700 entries)
 template <bool ROW_FIRST>
-__global__ void k_scale_vals(int64_t nrows, const int64_t *rp, const int32_t *ci, double *v64,
-                             float *v32, const double *rowfac, const double *colfac)
+__global__ __launch_bounds__(WG) void k_scale_vals(OpDev op, double *v64, float *v32, const double *rowfac,
+                                                   const double *colfac)
 {
-    const int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (r >= nrows) return;
-    const double rf = rowfac[r];
-    for (int64_t p = rp[r]; p < rp[r + 1]; ++p) {
-        const double cf = colfac[ci[p]];
-        const double v = ROW_FIRST ? (rf * v64[p]) * cf : (cf * v64[p]) * rf;
-        v64[p] = v;
-        if (v32) v32[p] = (float)v;
+    const Seg s = block_seg(op, (int)blockIdx.x);
+    const int lanes_log2 = s.lanes_log2 & 15;
+    const int L = lanes_log2 >= 8 ? WG : 1 << lanes_log2, lane = threadIdx.x & (L - 1);
+    for (int r = threadIdx.x / L; r < s.nrows; r += WG / L) {
+        const int64_t row = s.row0 + r;
+        const double rf = rowfac[row];
+        const int64_t e = op.rp[row + 1];
+        for (int64_t p = op.rp[row] + lane; p < e; p += L) {
+            const double cf = colfac[op.ci[p]];
+            const double v = ROW_FIRST ? (rf * v64[p]) * cf : (cf * v64[p]) * rf;
+            v64[p] = v;
+            if (v32) v32[p] = (float)v;
+        }
     }
 }
 
@@ -1380,10 +1387,10 @@ __global__ void k_scale_dual(Dev d)
     ((T *)d.q)[i] = (T)q;
 }
 
-// out = K v (FP64), per-workgroup partial of sum(out^2) in partials[lb]
 // out = op v (FP64) over the blocks of `list` (list[0 .. *cnt); every block
-// when list is NULL), with each block's sum of squares in partials[block]
-__global__ __launch_bounds__(WG) void k_spmv64(OpDev op, int remap, const double *v, double *out,
+// when list is NULL), with each block's sum of squares in partials[block]; with
+// nrm2, v / sqrt(nrm2[instance]) in place of v (zero norms leave it)
+__global__ __launch_bounds__(WG) void k_spmv64(OpDev op, int remap, const double *v, const double *nrm2, double *out,
                                                double *partials, const int32_t *list, const int32_t *cntp)
 {
     __shared__ double red[8];
@@ -1393,11 +1400,14 @@ __global__ __launch_bounds__(WG) void k_spmv64(OpDev op, int remap, const double
         const Seg s = block_seg(op, lb);
         const int bi = lb - s.blk0;
         double sq[1] = {0.0};
+        const double n2 = nrm2 ? nrm2[s.inst] : 0.0;
+        const double norm = n2 > 0.0 ? sqrt(n2) : 1.0;
         dispatch_lanes<4>(s.lanes_log2, [&](auto tag, auto rtag) {
             constexpr int L = decltype(tag)::value, R = decltype(rtag)::value;
             sweep_rows<L, 1, double, double, R>(op, s, bi, v, nullptr, nullptr, red, [&](int64_t r, const double *acc) {
-                out[r] = acc[0];
-                sq[0] += acc[0] * acc[0];
+                const double o = acc[0] / norm;
+                out[r] = o;
+                sq[0] += o * o;
             });
         });
         block_sum<1>(sq, red);
@@ -1406,64 +1416,77 @@ __global__ __launch_bounds__(WG) void k_spmv64(OpDev op, int remap, const double
     });
 }
 
-// per-instance sum of partials[blk0 .. blk1) (ranges from InstInfo), fixed order
-__global__ __launch_bounds__(WG) void k_inst_sum(const InstInfo *info, int onK, const double *partials,
-                                                 double *out)
+// Sum of f(0) .. f(n - 1) by a workgroup of SUM_WG lanes with SUM_U loads in
+// flight each (the kernels below are bound by the latency of their loads), in a
+// fixed order; valid in thread 0.
+constexpr int SUM_WG = 1024;
+constexpr int SUM_U = 8;
+template <typename F>
+__device__ __forceinline__ double wg_sum(int64_t n, F &&f)
 {
-    __shared__ double lds[4];
-    const InstInfo in = info[blockIdx.x];
+    __shared__ double lds[SUM_WG / 64];
+    double v = 0.0;
+    for (int64_t t0 = threadIdx.x; t0 < n; t0 += (int64_t)SUM_U * SUM_WG) {
+        double a[SUM_U];
+#pragma unroll
+        for (int k = 0; k < SUM_U; ++k) {
+            const int64_t t = t0 + (int64_t)k * SUM_WG;
+            a[k] = t < n ? f(t) : 0.0;
+        }
+#pragma unroll
+        for (int k = 0; k < SUM_U; ++k) v += a[k];
+    }
+    v = group_reduce<64, false>(v);
+    if ((threadIdx.x & 63) == 0) lds[threadIdx.x >> 6] = v;
+    __syncthreads();
+    v = 0.0;
+    if (threadIdx.x == 0)
+        for (int w = 0; w < SUM_WG / 64; ++w) v += lds[w];
+    return v;
+}
+
+// per-instance sum of partials[blk0 .. blk1) (ranges from InstInfo)
+__global__ __launch_bounds__(SUM_WG) void k_inst_sum(Dev d, int onK, const double *partials, double *out)
+{
+    const InstInfo in = d.info[blockIdx.x];
     const int b0 = onK ? in.blkK0 : in.blkT0, b1 = onK ? in.blkK1 : in.blkT1;
-    double v[1] = {0.0};
-    for (int t = b0 + threadIdx.x; t < b1; t += WG) v[0] += partials[t];
-    block_sum<1>(v, lds);
-    if (threadIdx.x == 0) out[blockIdx.x] = v[0];
+    const double v = wg_sum(b1 - b0, [&](int64_t t) { return partials[b0 + t]; });
+    if (threadIdx.x == 0) out[blockIdx.x] = v;
 }
 
 // The stopping test of the power iteration (Algorithm 2) for every instance
-// still iterating (one lane each): est = ||K b|| from w2 = ||K b||^2; stop
-// when two successive estimates differ by at most tol * est.  The state keeps
-// est in knorm, the previous estimate in kkt_prev (negative before the first)
-// and the pass in power_iters; a stopped instance is marked done, so the next
-// active-list rebuild drops it from the sweeps.  final_pass: the pass limit
-// was reached, every instance still iterating takes this estimate.
-__global__ void k_power_test(Dev d, const double *w2, int it, double tol, int final_pass)
+// still iterating (one workgroup each): est = ||K b|| from the blocks' sums of
+// squares; stop when two successive estimates differ by at most tol * est.  The
+// state keeps est in knorm, the previous estimate in kkt_prev (negative before
+// the first) and the pass in power_iters; a stopped instance is marked done, so
+// the next active-list rebuild drops it from the sweeps (a lone instance's lists
+// empty here).  final_pass: the pass limit was reached, every instance still
+// iterating takes this estimate.
+__global__ __launch_bounds__(SUM_WG) void k_power_test(Dev d, const double *partials, int it, double tol, int final_pass)
 {
-    const int b = blockIdx.x * blockDim.x + threadIdx.x;
-    if (b >= d.batch) return;
-    InstState &st = d.st[b];
+    InstState &st = d.st[blockIdx.x];
     if (st.done) return;
-    const double est = sqrt(w2[b]);
+    const InstInfo in = d.info[blockIdx.x];
+    const double w2 = wg_sum(in.blkK1 - in.blkK0, [&](int64_t t) { return partials[in.blkK0 + t]; });
+    if (threadIdx.x != 0) return;
+    const double est = sqrt(w2);
     st.knorm = est;
     st.power_iters = it;
     if (final_pass) return;
-    if (st.kkt_prev >= 0.0 && fabs(est - st.kkt_prev) <= tol * est) st.done = 1;
+    if (st.kkt_prev >= 0.0 && fabs(est - st.kkt_prev) <= tol * est) {
+        st.done = 1;
+        if (d.batch == 1) d.act_cnt[0] = d.act_cnt[1] = 0;
+    }
     st.kkt_prev = est;
 }
 
-// v_i /= sqrt(nrm2[inst(i)])  (skips zero norms)
-__global__ void k_normalize(double *v, const int32_t *inst_of, int64_t n, const double *nrm2)
+// per-instance sum of squares of a vector
+__global__ __launch_bounds__(SUM_WG) void k_inst_nrm2(const InstInfo *info, int primal, const double *v, double *out)
 {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    const double s = nrm2[inst_of[i]];
-    if (s > 0.0) v[i] = v[i] / sqrt(s);
-}
-
-// per-instance sum of squares of a vector over [off, off + len)
-__global__ __launch_bounds__(WG) void k_inst_nrm2(const InstInfo *info, int primal, const double *v,
-                                                  double *out)
-{
-    __shared__ double lds[4];
     const InstInfo in = info[blockIdx.x];
-    const int64_t off = primal ? in.xoff : in.yoff;
-    const int64_t len = primal ? in.n : in.m;
-    double s[1] = {0.0};
-    for (int64_t t = threadIdx.x; t < len; t += WG) {
-        const double a = v[off + t];
-        s[0] += a * a;
-    }
-    block_sum<1>(s, lds);
-    if (threadIdx.x == 0) out[blockIdx.x] = s[0];
+    const double *p = v + (primal ? in.xoff : in.yoff);
+    const double s = wg_sum(primal ? in.n : in.m, [&](int64_t t) { return p[t] * p[t]; });
+    if (threadIdx.x == 0) out[blockIdx.x] = s;
 }
 
 // x = proj_X(0), y = 0 (and the epoch start / averages)
@@ -1996,9 +2019,9 @@ void launch_scale_vals(const OpDev &op, double *v64, float *v32, bool row_first,
                        const double *rowfac, const double *colfac, hipStream_t s)
 {
     if (row_first) {
-        LAUNCH(k_scale_vals<true>, nblk_elem(op.nrows), op.nrows, op.rp, op.ci, v64, v32, rowfac, colfac);
+        LAUNCH(k_scale_vals<true>, (unsigned)op.nblk, op, v64, v32, rowfac, colfac);
     } else {
-        LAUNCH(k_scale_vals<false>, nblk_elem(op.nrows), op.nrows, op.rp, op.ci, v64, v32, rowfac, colfac);
+        LAUNCH(k_scale_vals<false>, (unsigned)op.nblk, op, v64, v32, rowfac, colfac);
     }
 }
 #endif
@@ -2011,32 +2034,29 @@ void launch_scale_data(const Dev &d, hipStream_t s)
 }
 
 #if PDHG_PART == 0
-void launch_spmv64(const OpDev &op, int remap, const double *v, double *out, double *partials,
+void launch_spmv64(const OpDev &op, int remap, const double *v, const double *nrm2, double *out, double *partials,
                    const int32_t *list, const int32_t *cnt, hipStream_t s)
 {
     const unsigned g = (unsigned)(op.nblk < 65536 ? op.nblk : 65536);
     if (g == 0) return;
-    LAUNCH(k_spmv64, g, op, remap, v, out, partials, list, cnt);
+    LAUNCH(k_spmv64, g, op, remap, v, nrm2, out, partials, list, cnt);
 }
+
+#define LAUNCH_SUM(kern, ...) hipLaunchKernelGGL(kern, dim3((unsigned)d.batch), dim3(SUM_WG), 0, s, __VA_ARGS__)
 
 void launch_inst_sum(const Dev &d, int onK, const double *partials, double *out, hipStream_t s)
 {
-    LAUNCH(k_inst_sum, (unsigned)d.batch, d.info, onK, partials, out);
+    LAUNCH_SUM(k_inst_sum, d, onK, partials, out);
 }
 
-void launch_power_test(const Dev &d, const double *w2, int it, double tol, int final_pass, hipStream_t s)
+void launch_power_test(const Dev &d, const double *partials, int it, double tol, int final_pass, hipStream_t s)
 {
-    LAUNCH(k_power_test, (unsigned)((d.batch + WG - 1) / WG), d, w2, it, tol, final_pass);
-}
-
-void launch_normalize(double *v, const int32_t *inst_of, int64_t n, const double *nrm2, hipStream_t s)
-{
-    LAUNCH(k_normalize, nblk_elem(n), v, inst_of, n, nrm2);
+    LAUNCH_SUM(k_power_test, d, partials, it, tol, final_pass);
 }
 
 void launch_inst_nrm2(const Dev &d, int primal, const double *v, double *out, hipStream_t s)
 {
-    LAUNCH(k_inst_nrm2, (unsigned)d.batch, d.info, primal, v, out);
+    LAUNCH_SUM(k_inst_nrm2, d.info, primal, v, out);
 }
 #endif
 

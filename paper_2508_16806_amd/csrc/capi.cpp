@@ -231,10 +231,19 @@ struct Bins {
 };
 
 // lim: row-length limits; rows: rows per lane group (1, 2, 4; only for bins
-// of at most 16 lanes)
+// of at most 16 lanes).  The default gives a lane 5..8 entries of a row, two
+// quads: a lane's second quad costs one load's issue, twice the lanes cost a
+// row another shuffle stage and its share of the per-row work twice the waves.
+// Primal / dual / check us with the limits 4 * 2^k, 8 * 2^k and 16 * 2^k:
+//   dispatch LP, 15.2M nonzeros (124 a row): 38.5 / 26 / 218, 30 / 26 / 151,
+//     30 / 26 / 118;  its quarter: 11.1 / 10.9 / 58, 10.3 / 10.6 / 48,
+//     11.4 / 11 / 47
+//   Zipf rows, 54M nonzeros: 395 / 573 / 3640, 363 / 573 / 2880,
+//     396 / 575 / 2970;  its tenth: 24.6 / 31.9 / 158, 21.8 / 31.7 / 107,
+//     26 / 31.7 / 116
 static Bins make_bins(const int32_t *lim, const int32_t *rows)
 {
-    static const int32_t def_len[NBIN] = {4, 8, 16, 32, 64, 128, 512, INT32_MAX};
+    static const int32_t def_len[NBIN] = {8, 16, 32, 64, 128, 256, 512, INT32_MAX};
     static const int32_t lanes[NBIN] = {0, 1, 2, 3, 4, 5, 6, 8};
     Bins b;
     for (int k = 0; k < NBIN; ++k) {

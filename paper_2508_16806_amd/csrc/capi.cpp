@@ -2230,7 +2230,8 @@ extern "C" int pdhg_set_state(pdhg_handle *h, int32_t inst, const double *x, con
 
 // Once per handle: the rows of each operator by decreasing length (stable)
 // for the gap pass, and the sweep tasks: whole rows, or FISH_CHUNK-entry
-// chunks of longer rows (with one partial slot each), longest first.
+// chunks of longer rows (with one partial slot each), longest first; those of
+// more than FISH_LONG entries, the first nlong, take a workgroup each.
 static int fish_build_tables(pdhg_handle *h, hipStream_t s)
 {
     const Dev &d = h->d;
@@ -2261,6 +2262,8 @@ static int fish_build_tables(pdhg_handle *h, hipStream_t s)
         }
         std::stable_sort(tasks.begin(), tasks.end(), [](const int4 &a, const int4 &b) { return a.z - a.y > b.z - b.y; });
         std::stable_sort(splits.begin(), splits.end(), [](const int4 &a, const int4 &b) { return a.z > b.z; });
+        const auto shrt = std::find_if(tasks.begin(), tasks.end(), [](const int4 &a) { return a.z - a.y <= FISH_LONG; });
+        (op == 0 ? f.nlongK : f.nlongT) = shrt - tasks.begin();
         int32_t *rows = (int32_t *)(op == 0 ? f.rowK : f.rowT);
         int4 *tk = (int4 *)(op == 0 ? f.taskK : f.taskT);
         int4 *sp = (int4 *)(op == 0 ? f.splitK : f.splitT);

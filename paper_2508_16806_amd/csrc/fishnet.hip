@@ -6,10 +6,15 @@
 // j is the number of live points (a power of two <= 64).  Every lane of the
 // group loads the same matrix entry (one transaction for the group) and
 // gathers point q's entry of the column, so a gather moves j contiguous
-// values: the multi-point sweep reads the matrix once for all points.  Rows
-// longer than FISH_CHUNK entries are cut into chunks (their partial sums are
-// added by a combine pass in chunk order), and the tasks run longest first,
-// so no lane group walks a long dependent chain.
+// values: the multi-point sweep reads the matrix once for all points.  A sweep
+// of few points is bound by its chains of dependent loads, not by traffic (at
+// 1.5M entries the two sweeps of an iteration took 23 + 41 us with one lane per
+// point and row), so 2^ls lanes share a point's row, each reading quads of
+// entries two at a time, and rows of more than FISH_LONG entries take a whole
+// workgroup: 25 + 24 us at 32 points, 11 + 16 us at 4.  Rows longer than
+// FISH_CHUNK entries are cut into chunks (their partial sums are added by a
+// combine pass in chunk order), and the tasks run longest first.  The sums'
+// order depends on the row's length, the number of rows and of live points only.
 //
 // One round: k primal/dual steps on the live points, the duality gap of each
 // point (grid-stride partials, reduced in a fixed order), a one-workgroup
@@ -26,34 +31,63 @@
 
 namespace pdhg {
 
-// sum over entries [b, e) of a row for the lane's point:
-// acc = sum_p v_p * G[c_p * PS + q], in entry order (4 loads in flight)
+// Four consecutive entries, loaded at any alignment of one entry.
+typedef int32_t Cols4 __attribute__((ext_vector_type(4), aligned(4)));
+template <typename V>
+struct Vals4;
+template <>
+struct Vals4<float> {
+    typedef float type __attribute__((ext_vector_type(4), aligned(4)));
+};
+template <>
+struct Vals4<double> {
+    typedef double type __attribute__((ext_vector_type(4), aligned(8)));
+};
+
+// This lane's share of a row's sum over entries [b, e) for its point: quads
+// s, s + S, ... of the row (the last one may hold fewer than four entries), two
+// of them in flight.  G points at the lane's point in entry 0.
 template <typename MV, typename GV>
 __device__ __forceinline__ double fish_dot(const OpDev &op, const MV *__restrict__ va, int64_t b, int64_t e,
-                                           const GV *__restrict__ G, int PS, int q)
+                                           const GV *__restrict__ G, int PS, int s, int S)
 {
+    using V4 = typename Vals4<MV>::type;
     const int32_t *__restrict__ ci = op.ci;
+    const int st = 4 * S;
     double acc = 0.0;
-    int64_t p = b;
-    for (; p + 4 <= e; p += 4) {
-        const int32_t c0 = ci[p], c1 = ci[p + 1], c2 = ci[p + 2], c3 = ci[p + 3];
-        const double v0 = (double)va[p], v1 = (double)va[p + 1], v2 = (double)va[p + 2], v3 = (double)va[p + 3];
-        const double g0 = (double)G[(int64_t)c0 * PS + q], g1 = (double)G[(int64_t)c1 * PS + q];
-        const double g2 = (double)G[(int64_t)c2 * PS + q], g3 = (double)G[(int64_t)c3 * PS + q];
-        acc += v0 * g0;
-        acc += v1 * g1;
-        acc += v2 * g2;
-        acc += v3 * g3;
+    int64_t p = b + 4 * s;
+    for (; p + st + 4 <= e; p += 2 * st) {
+        const Cols4 c0 = *(const Cols4 *)(ci + p), c1 = *(const Cols4 *)(ci + p + st);
+        const V4 v0 = *(const V4 *)(va + p), v1 = *(const V4 *)(va + p + st);
+        GV g[8];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) g[k] = G[(int64_t)c0[k] * PS];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) g[4 + k] = G[(int64_t)c1[k] * PS];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) acc += (double)v0[k] * (double)g[k];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) acc += (double)v1[k] * (double)g[4 + k];
     }
-    for (; p < e; ++p) acc += (double)va[p] * (double)G[(int64_t)ci[p] * PS + q];
+    if (p + 4 <= e) {
+        const Cols4 c0 = *(const Cols4 *)(ci + p);
+        const V4 v0 = *(const V4 *)(va + p);
+        GV g[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) g[k] = G[(int64_t)c0[k] * PS];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) acc += (double)v0[k] * (double)g[k];
+        p += st;
+    }
+    for (; p < e; ++p) acc += (double)va[p] * (double)G[(int64_t)ci[p] * PS];
     return acc;
 }
 
-template <typename MV, typename GV>
-__device__ __forceinline__ double fish_row_dot(const OpDev &op, const MV *__restrict__ va, int64_t row,
-                                               const GV *__restrict__ G, int PS, int q)
+// Sum over the lanes of one point in a wavefront: bits [lj, top) of the lane.
+__device__ __forceinline__ double fish_sum(double v, int lj, int top)
 {
-    return fish_dot(op, va, op.rp[row], op.rp[row + 1], G, PS, q);
+    for (int off = 1 << lj; off < (1 << top); off <<= 1) v += __shfl_xor(v, off);
+    return v;
 }
 
 // x+ = clip(x - tau (c~ - g), l~, u~), xbar = 2 x+ - x
@@ -86,17 +120,44 @@ __device__ __forceinline__ void fish_dual_epi(const Dev &d, const FishDev &f, in
     Y[at] = (T)((row < m1 && w < 0.0) ? 0.0 : w);
 }
 
-// One lane group (j lanes, one per live point) per task, tasks longest first.
+// The task of this lane and its sum: a task of the first nlong takes a whole
+// workgroup (WG / j lanes per point), every other one a group of 2^(lj + ls)
+// lanes of a wavefront.  True in the lanes that hold the sum of a task.
+template <typename T>
+__device__ __forceinline__ bool fish_task(const OpDev &op, const int4 *task, int64_t ntask, int64_t nlong,
+                                          const T *__restrict__ G, int PS, int lj, int ls, double *lds, int4 &t,
+                                          double &acc)
+{
+    const int tid = threadIdx.x, q = tid & ((1 << lj) - 1), s = tid >> lj;
+    if (blockIdx.x < nlong) {
+        t = task[blockIdx.x];
+        acc = fish_sum(fish_dot(op, op_vals<T>(op), t.y, t.z, G + q, PS, s, WG >> lj), lj, 6);
+        const int wave = tid >> 6, lane = tid & 63;
+        if (lane >> lj == 0) lds[wave * 64 + lane] = acc;
+        __syncthreads();
+        if (s) return false;
+        acc = (lds[q] + lds[64 + q]) + (lds[128 + q] + lds[192 + q]);
+        return true;
+    }
+    const int lg = lj + ls;
+    const int64_t g = nlong + (blockIdx.x - nlong) * (WG >> lg) + (tid >> lg);
+    if (g >= ntask) return false;
+    t = task[g];
+    const int sl = s & ((1 << ls) - 1);
+    acc = fish_sum(fish_dot(op, op_vals<T>(op), t.y, t.z, G + q, PS, sl, 1 << ls), lj, lg);
+    return sl == 0;
+}
+
 // A task that covers its whole row applies the update; a chunk of a split
 // row stores its partial sum for the combine pass.
 template <typename T>
-__global__ __launch_bounds__(WG) void k_fish_primal(Dev d, FishDev f, int lj, double tau)
+__global__ __launch_bounds__(WG) void k_fish_primal(Dev d, FishDev f, int lj, int ls, double tau)
 {
-    const int tid = threadIdx.x, q = tid & ((1 << lj) - 1);
-    const int64_t g = (int64_t)blockIdx.x * (WG >> lj) + (tid >> lj);
-    if (g >= f.ntaskT) return;
-    const int4 t = f.taskT[g];
-    const double acc = fish_dot(d.Kt, op_vals<T>(d.Kt), t.y, t.z, (const T *)f.Y, f.PS, q);
+    __shared__ double lds[256];
+    const int q = threadIdx.x & ((1 << lj) - 1);
+    int4 t;
+    double acc;
+    if (!fish_task(d.Kt, f.taskT, f.ntaskT, f.nlongT, (const T *)f.Y, f.PS, lj, ls, lds, t, acc)) return;
     if (t.w < 0)
         fish_primal_epi<T>(d, f, t.x, q, acc, tau);
     else
@@ -104,13 +165,14 @@ __global__ __launch_bounds__(WG) void k_fish_primal(Dev d, FishDev f, int lj, do
 }
 
 template <typename T, int INIT>
-__global__ __launch_bounds__(WG) void k_fish_dual(Dev d, FishDev f, int lj, double sigma, int64_t m1)
+__global__ __launch_bounds__(WG) void k_fish_dual(Dev d, FishDev f, int lj, int ls, double sigma, int64_t m1)
 {
-    const int tid = threadIdx.x, q = tid & ((1 << lj) - 1);
-    const int64_t g = (int64_t)blockIdx.x * (WG >> lj) + (tid >> lj);
-    if (g >= f.ntaskK) return;
-    const int4 t = f.taskK[g];
-    const double acc = fish_dot(d.K, op_vals<T>(d.K), t.y, t.z, (const T *)(INIT ? f.X : f.XB), f.PS, q);
+    __shared__ double lds[256];
+    const int q = threadIdx.x & ((1 << lj) - 1);
+    int4 t;
+    double acc;
+    if (!fish_task(d.K, f.taskK, f.ntaskK, f.nlongK, (const T *)(INIT ? f.X : f.XB), f.PS, lj, ls, lds, t, acc))
+        return;
     if (t.w < 0)
         fish_dual_epi<T, INIT>(d, f, t.x, q, acc, sigma, m1);
     else
@@ -147,11 +209,12 @@ __global__ __launch_bounds__(WG) void k_fish_combine_dual(Dev d, FishDev f, int 
 // lambda = proj_Lambda(c~ - K~^T y); K rows add q~ y.  Row groups are
 // visited grid-stride, so each workgroup's sum has a fixed order.
 template <typename T>
-__global__ __launch_bounds__(WG) void k_fish_gap(Dev d, FishDev f, int lj, int64_t gT, int64_t gK)
+__global__ __launch_bounds__(WG) void k_fish_gap(Dev d, FishDev f, int lj, int ls, int64_t gT, int64_t gK)
 {
     __shared__ double lds[4 * 64];
-    const int j = 1 << lj;
-    const int tid = threadIdx.x, q = tid & (j - 1), rl = tid >> lj, rpw = WG >> lj;
+    const int j = 1 << lj, S = 1 << ls;
+    const int tid = threadIdx.x, q = tid & (j - 1), sl = (tid >> lj) & (S - 1), rl = tid >> (lj + ls);
+    const int rpw = WG >> (lj + ls);
     const int PS = f.PS;
     const T *X = (const T *)f.X;
     const T *Y = (const T *)f.Y;
@@ -161,21 +224,20 @@ __global__ __launch_bounds__(WG) void k_fish_gap(Dev d, FishDev f, int lj, int64
             const int64_t g = it * rpw + rl;
             if (g < d.Kt.nrows) {
                 const int64_t row = f.rowT[g];
-                const double a = fish_row_dot(d.Kt, d.Kt.v64, row, Y, PS, q);
+                const double a =
+                    fish_sum(fish_dot(d.Kt, d.Kt.v64, d.Kt.rp[row], d.Kt.rp[row + 1], Y + q, PS, sl, S), lj, lj + ls);
                 const double cj = d.c64[row], lo = d.l64[row], hi = d.u64[row];
                 const bool lf = isfinite(lo), uf = isfinite(hi);
                 const double dd = cj - a;
                 // proj_Lambda: {0} free, R^- upper only, R^+ lower only, R boxed
                 const double lam = (!lf && !uf) ? 0.0 : (!lf ? fmin(dd, 0.0) : (!uf ? fmax(dd, 0.0) : dd));
                 const double t = lam > 0.0 ? lo * lam : (lam < 0.0 ? hi * lam : 0.0);
-                v += t - cj * (double)X[row * PS + q];
+                if (sl == 0) v += t - cj * (double)X[row * PS + q];
             }
         } else {
-            const int64_t g = (it - gT) * rpw + rl;
-            if (g < d.K.nrows) {
-                const int64_t row = f.rowK[g];
-                v += d.q64[row] * (double)Y[row * PS + q];
-            }
+            const int64_t g = (it - gT) * WG + tid;  // one row per lane and point
+            const int64_t row = g >> lj;
+            if (row < d.K.nrows) v += d.q64[row] * (double)Y[row * PS + q];
         }
     }
     // lanes of one point: across the rows of a wavefront, then the four wavefronts
@@ -290,14 +352,33 @@ static inline unsigned fish_groups(int64_t rows, int lj)
     return (unsigned)((rows + rpw - 1) / rpw);
 }
 
+// log2 of the lanes per point of a short task: doubled (up to 8) until the
+// launch has FISH_LANES lanes.  More lanes shorten a task's chain of loads and
+// fill the chip; past that they only add shuffles and repeat the task's set-up.
+// 32 points on 41k + 30k rows, ms for 512 iterations with 1 / 2 / 8 lanes
+// throughout and with this rule: 18.2 / 17.8 / 22.5 / 17.7; 16 points on 8k + 6k
+// rows: 8.8 / 6.3 / 5.2 / 5.1; 4 points on 100k + 72k rows: 5.8 / 4.6 / 6.5 / 4.7.
+static inline int fish_split(int64_t ntask, int lj)
+{
+    int ls = 0;
+    while (ls < 3 && lj + ls < 6 && (ntask << (lj + ls)) < FISH_LANES) ++ls;
+    return ls;
+}
+
+static inline unsigned fish_blocks(int64_t ntask, int64_t nlong, int lg)
+{
+    return (unsigned)nlong + fish_groups(ntask - nlong, lg);
+}
+
 template <typename T>
 void launch_fish_step(const Dev &d, const FishDev &f, int lj, double tau, double sigma, int64_t m1, hipStream_t s)
 {
-    const unsigned tT = fish_groups(f.ntaskT, lj), cT = fish_groups(f.nsplitT, lj);
-    const unsigned tK = fish_groups(f.ntaskK, lj), cK = fish_groups(f.nsplitK, lj);
-    if (tT) hipLaunchKernelGGL(k_fish_primal<T>, dim3(tT), dim3(WG), 0, s, d, f, lj, tau);
+    const int lsT = fish_split(f.ntaskT, lj), lsK = fish_split(f.ntaskK, lj);
+    const unsigned tT = fish_blocks(f.ntaskT, f.nlongT, lj + lsT), cT = fish_groups(f.nsplitT, lj);
+    const unsigned tK = fish_blocks(f.ntaskK, f.nlongK, lj + lsK), cK = fish_groups(f.nsplitK, lj);
+    if (tT) hipLaunchKernelGGL(k_fish_primal<T>, dim3(tT), dim3(WG), 0, s, d, f, lj, lsT, tau);
     if (cT) hipLaunchKernelGGL(k_fish_combine_primal<T>, dim3(cT), dim3(WG), 0, s, d, f, lj, tau);
-    if (tK) hipLaunchKernelGGL((k_fish_dual<T, 0>), dim3(tK), dim3(WG), 0, s, d, f, lj, sigma, m1);
+    if (tK) hipLaunchKernelGGL((k_fish_dual<T, 0>), dim3(tK), dim3(WG), 0, s, d, f, lj, lsK, sigma, m1);
     if (cK) hipLaunchKernelGGL((k_fish_combine_dual<T, 0>), dim3(cK), dim3(WG), 0, s, d, f, lj, sigma, m1);
 }
 
@@ -306,8 +387,9 @@ void launch_fish_init(const Dev &d, const FishDev &f, int lp, double sc, hipStre
 {
     const int64_t tot = d.N << lp;
     if (tot > 0) hipLaunchKernelGGL(k_fish_init<T>, dim3((unsigned)((tot + WG - 1) / WG)), dim3(WG), 0, s, d, f, lp, sc);
-    const unsigned tK = fish_groups(f.ntaskK, lp), cK = fish_groups(f.nsplitK, lp);
-    if (tK) hipLaunchKernelGGL((k_fish_dual<T, 1>), dim3(tK), dim3(WG), 0, s, d, f, lp, 0.0, (int64_t)0);
+    const int ls = fish_split(f.ntaskK, lp);
+    const unsigned tK = fish_blocks(f.ntaskK, f.nlongK, lp + ls), cK = fish_groups(f.nsplitK, lp);
+    if (tK) hipLaunchKernelGGL((k_fish_dual<T, 1>), dim3(tK), dim3(WG), 0, s, d, f, lp, ls, 0.0, (int64_t)0);
     if (cK) hipLaunchKernelGGL((k_fish_combine_dual<T, 1>), dim3(cK), dim3(WG), 0, s, d, f, lp, 0.0, (int64_t)0);
 }
 
@@ -315,10 +397,11 @@ template <typename T>
 int launch_fish_gap_rank(const Dev &d, const FishDev &f, int lj, int round, int repop, int half, int64_t wpos,
                          hipStream_t s)
 {
-    const int64_t gT = fish_groups(d.Kt.nrows, lj), gK = fish_groups(d.K.nrows, lj);
+    const int ls = fish_split(f.ntaskT, lj);
+    const int64_t gT = fish_groups(d.Kt.nrows, lj + ls), gK = fish_groups(d.K.nrows, lj);
     const int64_t items = gT + gK;
     const int grid = (int)(items < FISH_GRID ? (items > 0 ? items : 1) : FISH_GRID);
-    hipLaunchKernelGGL(k_fish_gap<T>, dim3(grid), dim3(WG), 0, s, d, f, lj, gT, gK);
+    hipLaunchKernelGGL(k_fish_gap<T>, dim3(grid), dim3(WG), 0, s, d, f, lj, ls, gT, gK);
     hipLaunchKernelGGL(k_fish_rank, dim3(1), dim3(WG), 0, s, f, lj, grid, round, repop, half, wpos);
     return grid;
 }

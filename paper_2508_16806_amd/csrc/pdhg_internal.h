@@ -196,6 +196,7 @@ struct FishDev {
     const int4 *taskK, *taskT;
     const int4 *splitK, *splitT;
     int64_t ntaskK, ntaskT, nsplitK, nsplitT;
+    int64_t nlongK, nlongT;     // tasks (the first ones) longer than FISH_LONG entries
     double *cpart;              // chunk partials, slots x PS
     double *part;               // per-workgroup gap partials, FISH_GRID x PS
     double *wmat;               // repopulation weights, (PS/2) x (PS/2)
@@ -206,7 +207,9 @@ struct FishDev {
     int32_t *rec_keep;          // nrec x PS
 };
 constexpr int FISH_GRID = 512;  // workgroups of the gap pass
-constexpr int FISH_CHUNK = 256; // longest row a lane group sums in one pass
+constexpr int FISH_CHUNK = 1024; // longest task: a row, or a piece of one
+constexpr int64_t FISH_LANES = 512 * 1024; // lanes that fill the chip (8 wavefronts a SIMD)
+constexpr int FISH_LONG = 128;  // longest task of a lane group; longer ones take a workgroup
 
 // Small LPs (small.hip): one workgroup iterates a whole instance out of LDS.
 // Index 0 is K^T (primal sweep), 1 is K.

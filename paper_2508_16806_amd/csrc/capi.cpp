@@ -551,6 +551,7 @@ struct pdhg_handle {
     void *noalloc_owner = nullptr;    // its claim on that workspace
     int64_t rec_steps = 0;  // steps recorded by the last recording pdhg_iterate
     int rec_valid = 0;      // the tape matches the handle's data (cleared by pdhg_set_data)
+    int64_t rec_mask = 0;   // the tape's steps from this one on have their masks held
     int64_t rec_gen = 0;    // bumped by every recording pdhg_iterate and by pdhg_set_data
     std::vector<InstState> rec_st;  // step parameters of the recorded steps
 };
@@ -1788,7 +1789,7 @@ static CtlParams ctl_params(const pdhg_handle *h)
 // the sweeps of a fixed step: tile.hip for the tiled operators, the row-binned
 // sweeps for the others
 template <typename T>
-static void enqueue_primal(const pdhg_handle *h, const Dev &d, int j, int avg, uint8_t *mask, hipStream_t s)
+static void enqueue_primal(const pdhg_handle *h, const Dev &d, int j, int avg, Mask mask, hipStream_t s)
 {
     const TileOp &t = h->buf.tile[0];
     if (t.nblk > 0) launch_primal_tile<T>(d, t, j, avg, mask, s);
@@ -1796,7 +1797,7 @@ static void enqueue_primal(const pdhg_handle *h, const Dev &d, int j, int avg, u
 }
 
 template <typename T>
-static void enqueue_dual(const pdhg_handle *h, const Dev &d, int j, int avg, uint8_t *mask, hipStream_t s)
+static void enqueue_dual(const pdhg_handle *h, const Dev &d, int j, int avg, Mask mask, hipStream_t s)
 {
     const TileOp &t = h->buf.tile[1];
     if (t.nblk > 0) launch_dual_tile<T>(d, t, j, avg, mask, s);
@@ -1811,6 +1812,18 @@ static void enqueue_active(const pdhg_handle *h, const Dev &d, hipStream_t s, in
         launch_act_tile(d, h->buf.tile[1], h->buf.tile[0], s);
 }
 
+// where the masks of recorded step t lie, counting from a step whose masks start
+// a byte: C bytes a row, so MASK_PACK * C steps
+static Mask mask_x(const pdhg_handle *h, int64_t t)
+{
+    return Mask{h->buf.maskx + t / MASK_PACK * h->d.N, (int)(2 * (t % MASK_PACK))};
+}
+
+static Mask mask_y(const pdhg_handle *h, int64_t t)
+{
+    return Mask{h->buf.masky + t / (2 * MASK_PACK) * h->d.M, (int)(t % (2 * MASK_PACK))};
+}
+
 // fixed-step iterations j0 .. j0 + count - 1 of a check period
 template <typename T>
 static void enqueue_steps(const pdhg_handle *h, const Dev &d, int j0, int count, int avg, hipStream_t s)
@@ -1820,8 +1833,8 @@ static void enqueue_steps(const pdhg_handle *h, const Dev &d, int j0, int count,
         return;
     }
     for (int j = j0; j < j0 + count; ++j) {
-        enqueue_primal<T>(h, d, j, avg, nullptr, s);
-        enqueue_dual<T>(h, d, j, avg, nullptr, s);
+        enqueue_primal<T>(h, d, j, avg, Mask{}, s);
+        enqueue_dual<T>(h, d, j, avg, Mask{}, s);
     }
 }
 
@@ -2047,6 +2060,14 @@ static int iterate_impl(pdhg_handle *h, int64_t k, int32_t record, hipStream_t s
     enqueue_active(h, d, s);
     const int64_t C = std::max(1, h->opts.unroll_checkpoint);
     const size_t es = elem_size(h->prec);
+    // The masks of the last steps, as many as there is room for from a
+    // checkpoint on, are stored now: the reverse steps then need no second run
+    // of that part (42 of a step's 130 us on 8 dispatch LPs of 1.5M nonzeros;
+    // the mask bits cost a recorded step 1 us).  Small LPs take all steps of a
+    // segment in one launch that keeps no masks.
+    const int64_t hold = h->sz.small ? 0 : MASK_PACK * C;
+    const int64_t m0 = !record || hold == 0 ? k : (std::max<int64_t>(0, k - hold) + C - 1) / C * C;
+    if (record) h->rec_mask = INT64_MAX;
     // steps up to the next checkpoint, in launches of a bounded length
     int run = 1;
     for (int64_t t = 0; t < k; t += run) {
@@ -2057,11 +2078,19 @@ static int iterate_impl(pdhg_handle *h, int64_t k, int32_t record, hipStream_t s
         }
         run = (int)std::min<int64_t>(SMALL_STEPS, k - t);
         if (record) run = (int)std::min<int64_t>(run, C - t % C);
-        enqueue_steps<T>(h, d, 0, run, 0, s);
+        if (t < m0) {
+            enqueue_steps<T>(h, d, 0, run, 0, s);
+            continue;
+        }
+        for (int64_t i = t; i < t + run; ++i) {
+            enqueue_primal<T>(h, d, (int)(i & 1), 0, mask_x(h, i - m0), s);
+            enqueue_dual<T>(h, d, (int)(i & 1), 0, mask_y(h, i - m0), s);
+        }
     }
     HIPCHK(hipGetLastError());
     if (record) {
         h->rec_steps = k;
+        h->rec_mask = m0;
         h->rec_valid = 1;
         h->rec_gen += 1;
         h->rec_st = st;
@@ -2097,19 +2126,26 @@ static int backward_impl(pdhg_handle *h, const double *gx, const double *gy, dou
     HIPCHK(hipMemcpyAsync(bx, d.x, N * es, hipMemcpyDeviceToDevice, s));
     HIPCHK(hipMemcpyAsync(by, d.y, M * es, hipMemcpyDeviceToDevice, s));
     launch_adj_init(d, a, gxd, gyd, s);
-    for (int64_t sg = nseg - 1; sg >= 0; --sg) {
-        const int64_t len = std::min(C, K - sg * C);
+    // reverse steps t1 - 1 .. t0, whose masks are held from step t0 on
+    auto reverse = [&](int64_t t0, int64_t t1) {
+        launch_adj_w(d, a, mask_y(h, t1 - 1 - t0), s);
+        for (int64_t t = t1 - 1; t >= t0; --t) {
+            launch_rev_primal<T>(d, a, mask_x(h, t - t0), s);
+            launch_rev_dual<T>(d, a, t > t0 ? mask_y(h, t - 1 - t0) : Mask{}, s);
+        }
+    };
+    const int64_t m0 = std::min(h->rec_mask, K);
+    if (m0 < K) reverse(m0, K);
+    if (m0 > 0) h->rec_mask = INT64_MAX;  // the runs below store other steps' masks
+    for (int64_t sg = (m0 + C - 1) / C - 1; sg >= 0; --sg) {
+        const int64_t t1 = std::min(m0, (sg + 1) * C);
         HIPCHK(hipMemcpyAsync(d.x, (char *)b.ckx + sg * N * es, N * es, hipMemcpyDeviceToDevice, s));
         HIPCHK(hipMemcpyAsync(d.y, (char *)b.cky + sg * M * es, M * es, hipMemcpyDeviceToDevice, s));
-        for (int64_t t = 0; t < len; ++t) {
-            enqueue_primal<T>(h, d, 0, 0, b.maskx + t * N, s);
-            enqueue_dual<T>(h, d, 0, 0, b.masky + t * M, s);
+        for (int64_t t = sg * C; t < t1; ++t) {
+            enqueue_primal<T>(h, d, 0, 0, mask_x(h, t - sg * C), s);
+            enqueue_dual<T>(h, d, 0, 0, mask_y(h, t - sg * C), s);
         }
-        for (int64_t t = len - 1; t >= 0; --t) {
-            launch_adj_w(d, a, b.masky + t * M, s);
-            launch_rev_primal<T>(d, a, b.maskx + t * N, s);
-            launch_rev_dual<T>(d, a, s);
-        }
+        reverse(sg * C, t1);
     }
     HIPCHK(hipMemcpyAsync(d.x, bx, N * es, hipMemcpyDeviceToDevice, s));
     HIPCHK(hipMemcpyAsync(d.y, by, M * es, hipMemcpyDeviceToDevice, s));
@@ -2560,8 +2596,8 @@ static int time_impl(pdhg_handle *h, int32_t reps, pdhg_kernel_times *out, hipSt
     // the two sweeps alternate as in the iteration (each one finds the caches
     // as the other leaves them)
     time_seq(2, [&](int k, int r) {
-        if (k == 0) enqueue_primal<T>(h, d, r, avg, nullptr, s);
-        else enqueue_dual<T>(h, d, r, avg, nullptr, s);
+        if (k == 0) enqueue_primal<T>(h, d, r, avg, Mask{}, s);
+        else enqueue_dual<T>(h, d, r, avg, Mask{}, s);
     }, ms);
     // once-per-chunk kernels, back to back, each on the path a check takes
     // when it restarts: the control kernel runs a whole check decision (a

@@ -7,13 +7,13 @@
 namespace pdhg {
 
 template <typename T>
-void launch_primal(const Dev &d, int j, int avg, uint8_t *mask, hipStream_t s, int untiled = 0);
+void launch_primal(const Dev &d, int j, int avg, Mask mask, hipStream_t s, int untiled = 0);
 template <typename T>
-void launch_dual(const Dev &d, int j, int avg, uint8_t *mask, hipStream_t s, int untiled = 0);
+void launch_dual(const Dev &d, int j, int avg, Mask mask, hipStream_t s, int untiled = 0);
 template <typename T>
-void launch_primal_tile(const Dev &d, const TileOp &op, int j, int avg, uint8_t *mask, hipStream_t s);
+void launch_primal_tile(const Dev &d, const TileOp &op, int j, int avg, Mask mask, hipStream_t s);
 template <typename T>
-void launch_dual_tile(const Dev &d, const TileOp &op, int j, int avg, uint8_t *mask, hipStream_t s);
+void launch_dual_tile(const Dev &d, const TileOp &op, int j, int avg, Mask mask, hipStream_t s);
 template <typename T>
 void launch_tile_build(const OpDev &op, const TileOp &to, hipStream_t s);
 template <typename T>
@@ -92,11 +92,11 @@ template <typename T>
 void launch_fish_out(const Dev &d, const FishDev &f, hipStream_t s);
 
 void launch_adj_init(const Dev &d, const AdjBufs &a, const double *gx, const double *gy, hipStream_t s);
-void launch_adj_w(const Dev &d, const AdjBufs &a, const uint8_t *mask_y, hipStream_t s);
+void launch_adj_w(const Dev &d, const AdjBufs &a, Mask mask, hipStream_t s);
 template <typename T>
-void launch_rev_primal(const Dev &d, const AdjBufs &a, const uint8_t *mask_x, hipStream_t s);
+void launch_rev_primal(const Dev &d, const AdjBufs &a, Mask mask, hipStream_t s);
 template <typename T>
-void launch_rev_dual(const Dev &d, const AdjBufs &a, hipStream_t s);
+void launch_rev_dual(const Dev &d, const AdjBufs &a, Mask next, hipStream_t s);
 void launch_adj_out(const Dev &d, const AdjBufs &a, double *gc, double *gq, double *gl, double *gu,
                     double *gx0, double *gy0, hipStream_t s);
 void launch_set_raw(const Dev &d, const double *c, const double *q, const double *l, const double *u,

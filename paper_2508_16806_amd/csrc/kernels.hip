@@ -74,8 +74,8 @@ __device__ __forceinline__ void slice_partial(const OpDev &op, const Seg &s, int
     }
 }
 
-// MASK: also record the clip region of x (0 interior, 1 at l, 2 at u) for the
-// adjoint replay (whole rows only).
+// MASK: also record the clip region of x (0 interior, 1 at l, 2 at u) at bit
+// `pass` of the row's mask byte, for the adjoint (whole rows only).
 template <typename T, int AVG, int MASK, int RM, int SLX>
 __global__ __launch_bounds__(WG) void k_primal(Dev d, int j_in_chunk, uint8_t *__restrict__ mask, int pass)
 {
@@ -140,7 +140,7 @@ __global__ __launch_bounds__(WG) void k_primal(Dev d, int j_in_chunk, uint8_t *_
                     x[j] = xnT;
                     xb[j] = (T)(2.0 * (double)xnT - xo);
                     if (AVG) xa[j] = (T)(xav + (((double)xnT - (double)r_0[r]) - xav) * w);
-                    if (MASK) mask[j] = (uint8_t)(v <= lo ? 1 : (v >= hi ? 2 : 0));
+                    if (MASK) mask_put(mask, j, pass, v <= lo ? 1 : (v >= hi ? 2 : 0));
                 }
             }
         });
@@ -201,7 +201,7 @@ __global__ __launch_bounds__(WG) void k_dual(Dev d, int j_in_chunk, uint8_t *__r
                     const T ynT = (T)yn;
                     y[i] = ynT;
                     if (AVG) ya[i] = (T)(yav + (((double)ynT - (double)r_0[r]) - yav) * w);
-                    if (MASK) mask[i] = (uint8_t)((!ineq || wv > 0.0) ? 1 : 0);
+                    if (MASK) mask_put(mask, i, pass, (!ineq || wv > 0.0) ? 1 : 0);
                 }
             }
         });
@@ -1667,18 +1667,21 @@ __global__ void k_adj_init(Dev d, AdjBufs a, const double *gx, const double *gy)
 }
 
 // aw = mask_y * ay ; aq += sigma * aw
-__global__ void k_adj_w(Dev d, AdjBufs a, const uint8_t *__restrict__ mask_y)
+__device__ __forceinline__ void adj_w(const AdjBufs &a, int64_t i, double ay, double sigma, const Mask &mask)
 {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= d.M) return;
-    const double sigma = d.st[d.inst_of_row[i]].sigma;
-    const double w = mask_y[i] ? a.ay[i] : 0.0;
+    const double w = (mask.p[i] >> mask.sh) & 1 ? ay : 0.0;
     a.aw[i] = w;
     a.aq[i] += sigma * w;
 }
 
+__global__ void k_adj_w(Dev d, AdjBufs a, Mask mask)
+{
+    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i < d.M) adj_w(a, i, a.ay[i], d.st[d.inst_of_row[i]].sigma, mask);
+}
+
 template <typename T, int RM>
-__global__ __launch_bounds__(WG) void k_rev_primal(Dev d, AdjBufs a, const uint8_t *__restrict__ mask_x)
+__global__ __launch_bounds__(WG) void k_rev_primal(Dev d, AdjBufs a, Mask mask)
 {
     __shared__ double red[8];
     const int lb = logical_block(d.remap);
@@ -1692,7 +1695,7 @@ __global__ __launch_bounds__(WG) void k_rev_primal(Dev d, AdjBufs a, const uint8
         sweep_rows<L, 1, T, double, R>(op, s, bi, a.aw, nullptr, nullptr, red, [&](int64_t j, const double *acc) {
             const double axb = -sigma * acc[0];
             const double g = a.ax[j] + 2.0 * axb;
-            const uint8_t code = mask_x[j];
+            const int code = (mask.p[j] >> mask.sh) & 3;
             double av = 0.0;
             if (code == 1)
                 a.al[j] += g;
@@ -1707,19 +1710,27 @@ __global__ __launch_bounds__(WG) void k_rev_primal(Dev d, AdjBufs a, const uint8
     });
 }
 
-template <typename T, int RM>
-__global__ __launch_bounds__(WG) void k_rev_dual(Dev d, AdjBufs a)
+// FUSE: the preceding step's aw from its mask, in place of ay (a pass of its own
+// over three vectors took 5.3 us of a step's 50 on 8 dispatch LPs of 30k rows).
+template <typename T, int RM, int FUSE>
+__global__ __launch_bounds__(WG) void k_rev_dual(Dev d, AdjBufs a, Mask next)
 {
     __shared__ double red[8];
     const int lb = logical_block(d.remap);
     const OpDev &op = d.K;
     const Seg s = block_seg(op, lb);
-    const double tau = d.st[s.inst].tau;
+    const double tau = d.st[s.inst].tau, sigma = d.st[s.inst].sigma;
     const int bi = lb - s.blk0;
     dispatch_lanes<RM>(s.lanes_log2, [&](auto tag, auto rtag) {
         constexpr int L = decltype(tag)::value, R = decltype(rtag)::value;
         sweep_rows<L, 1, T, double, R>(op, s, bi, a.av, nullptr, nullptr, red,
-                                       [&](int64_t i, const double *acc) { a.ay[i] = a.aw[i] + tau * acc[0]; });
+                                       [&](int64_t i, const double *acc) {
+                                           const double ay = a.aw[i] + tau * acc[0];
+                                           if (FUSE)
+                                               adj_w(a, i, ay, sigma, next);
+                                           else
+                                               a.ay[i] = ay;
+                                       });
     });
 }
 
@@ -1798,10 +1809,10 @@ static inline unsigned sweep_grid(const Dev &d, int64_t nitems)
     } while (0)
 
 template <typename T>
-void launch_primal(const Dev &d, int j, int avg, uint8_t *mask, hipStream_t s, int untiled)
+void launch_primal(const Dev &d, int j, int avg, Mask mask, hipStream_t s, int untiled)
 {
     const unsigned g = sweep_grid(d, d.Kt.nblk);
-    if (d.Kt.slices > 1 && !mask) {
+    if (d.Kt.slices > 1 && !mask.p) {
         // column-sliced sweep: S launches (the recorded steps sweep whole rows)
         const int last = d.Kt.slices - 1;
         RM_SWITCH(d.Kt.rmax, {
@@ -1819,27 +1830,27 @@ void launch_primal(const Dev &d, int j, int avg, uint8_t *mask, hipStream_t s, i
         return;
     }
     RM_SWITCH(d.Kt.rmax, {
-        if (untiled && mask) {
-            LAUNCH((k_primal<T, 0, 1, RMV, 4>), g, d, j, mask, 0);
+        if (untiled && mask.p) {
+            LAUNCH((k_primal<T, 0, 1, RMV, 4>), g, d, j, mask.p, mask.sh);
         } else if (untiled && avg) {
-            LAUNCH((k_primal<T, 1, 0, RMV, 4>), g, d, j, mask, 0);
+            LAUNCH((k_primal<T, 1, 0, RMV, 4>), g, d, j, nullptr, 0);
         } else if (untiled) {
-            LAUNCH((k_primal<T, 0, 0, RMV, 4>), g, d, j, mask, 0);
-        } else if (mask) {
-            LAUNCH((k_primal<T, 0, 1, RMV, 0>), g, d, j, mask, 0);
+            LAUNCH((k_primal<T, 0, 0, RMV, 4>), g, d, j, nullptr, 0);
+        } else if (mask.p) {
+            LAUNCH((k_primal<T, 0, 1, RMV, 0>), g, d, j, mask.p, mask.sh);
         } else if (avg) {
-            LAUNCH((k_primal<T, 1, 0, RMV, 0>), g, d, j, mask, 0);
+            LAUNCH((k_primal<T, 1, 0, RMV, 0>), g, d, j, nullptr, 0);
         } else {
-            LAUNCH((k_primal<T, 0, 0, RMV, 0>), g, d, j, mask, 0);
+            LAUNCH((k_primal<T, 0, 0, RMV, 0>), g, d, j, nullptr, 0);
         }
     });
 }
 
 template <typename T>
-void launch_dual(const Dev &d, int j, int avg, uint8_t *mask, hipStream_t s, int untiled)
+void launch_dual(const Dev &d, int j, int avg, Mask mask, hipStream_t s, int untiled)
 {
     const unsigned g = sweep_grid(d, d.K.nblk);
-    if (d.K.slices > 1 && !mask) {
+    if (d.K.slices > 1 && !mask.p) {
         const int last = d.K.slices - 1;
         RM_SWITCH(d.K.rmax, {
             for (int pass = 0; pass < last; ++pass) LAUNCH((k_dual<T, 0, 0, RMV, 1>), g, d, j, nullptr, pass);
@@ -1856,18 +1867,18 @@ void launch_dual(const Dev &d, int j, int avg, uint8_t *mask, hipStream_t s, int
         return;
     }
     RM_SWITCH(d.K.rmax, {
-        if (untiled && mask) {
-            LAUNCH((k_dual<T, 0, 1, RMV, 4>), g, d, j, mask, 0);
+        if (untiled && mask.p) {
+            LAUNCH((k_dual<T, 0, 1, RMV, 4>), g, d, j, mask.p, mask.sh);
         } else if (untiled && avg) {
-            LAUNCH((k_dual<T, 1, 0, RMV, 4>), g, d, j, mask, 0);
+            LAUNCH((k_dual<T, 1, 0, RMV, 4>), g, d, j, nullptr, 0);
         } else if (untiled) {
-            LAUNCH((k_dual<T, 0, 0, RMV, 4>), g, d, j, mask, 0);
-        } else if (mask) {
-            LAUNCH((k_dual<T, 0, 1, RMV, 0>), g, d, j, mask, 0);
+            LAUNCH((k_dual<T, 0, 0, RMV, 4>), g, d, j, nullptr, 0);
+        } else if (mask.p) {
+            LAUNCH((k_dual<T, 0, 1, RMV, 0>), g, d, j, mask.p, mask.sh);
         } else if (avg) {
-            LAUNCH((k_dual<T, 1, 0, RMV, 0>), g, d, j, mask, 0);
+            LAUNCH((k_dual<T, 1, 0, RMV, 0>), g, d, j, nullptr, 0);
         } else {
-            LAUNCH((k_dual<T, 0, 0, RMV, 0>), g, d, j, mask, 0);
+            LAUNCH((k_dual<T, 0, 0, RMV, 0>), g, d, j, nullptr, 0);
         }
     });
 }
@@ -2127,22 +2138,27 @@ void launch_adj_init(const Dev &d, const AdjBufs &a, const double *gx, const dou
     LAUNCH(k_adj_init, nblk_elem(d.N > d.M ? d.N : d.M), d, a, gx, gy);
 }
 
-void launch_adj_w(const Dev &d, const AdjBufs &a, const uint8_t *mask_y, hipStream_t s)
+void launch_adj_w(const Dev &d, const AdjBufs &a, Mask mask, hipStream_t s)
 {
-    LAUNCH(k_adj_w, nblk_elem(d.M), d, a, mask_y);
+    LAUNCH(k_adj_w, nblk_elem(d.M), d, a, mask);
 }
 #endif
 
 template <typename T>
-void launch_rev_primal(const Dev &d, const AdjBufs &a, const uint8_t *mask_x, hipStream_t s)
+void launch_rev_primal(const Dev &d, const AdjBufs &a, Mask mask, hipStream_t s)
 {
-    RM_SWITCH(d.Kt.rmax, { LAUNCH((k_rev_primal<T, RMV>), (unsigned)d.Kt.nblk, d, a, mask_x); });
+    RM_SWITCH(d.Kt.rmax, { LAUNCH((k_rev_primal<T, RMV>), (unsigned)d.Kt.nblk, d, a, mask); });
 }
 
 template <typename T>
-void launch_rev_dual(const Dev &d, const AdjBufs &a, hipStream_t s)
+void launch_rev_dual(const Dev &d, const AdjBufs &a, Mask next, hipStream_t s)
 {
-    RM_SWITCH(d.K.rmax, { LAUNCH((k_rev_dual<T, RMV>), (unsigned)d.K.nblk, d, a); });
+    RM_SWITCH(d.K.rmax, {
+        if (next.p)
+            LAUNCH((k_rev_dual<T, RMV, 1>), (unsigned)d.K.nblk, d, a, next);
+        else
+            LAUNCH((k_rev_dual<T, RMV, 0>), (unsigned)d.K.nblk, d, a, next);
+    });
 }
 
 #if PDHG_PART == 0
@@ -2173,16 +2189,16 @@ void launch_set_raw(const Dev &d, const double *c, const double *q, const double
     template void launch_set_point<T>(const Dev &, int64_t, int64_t, int64_t, int64_t, int64_t, \
                                       const double *, const double *, hipStream_t);
 #define INST_STEP(T)                                                                        \
-    template void launch_primal<T>(const Dev &, int, int, uint8_t *, hipStream_t, int);      \
-    template void launch_dual<T>(const Dev &, int, int, uint8_t *, hipStream_t, int);
+    template void launch_primal<T>(const Dev &, int, int, Mask, hipStream_t, int);      \
+    template void launch_dual<T>(const Dev &, int, int, Mask, hipStream_t, int);
 #define INST_AD(T)                                                                          \
     template void launch_primal_ad<T>(const Dev &, hipStream_t);                             \
     template void launch_dual_ad<T>(const Dev &, hipStream_t);                               \
     template void launch_kx_ad<T>(const Dev &, int, hipStream_t);
 #define INST_INFEAS_REV(T)                                                                  \
     template void launch_infeas<T>(const Dev &, const void *, const void *, hipStream_t);    \
-    template void launch_rev_primal<T>(const Dev &, const AdjBufs &, const uint8_t *, hipStream_t); \
-    template void launch_rev_dual<T>(const Dev &, const AdjBufs &, hipStream_t);
+    template void launch_rev_primal<T>(const Dev &, const AdjBufs &, Mask, hipStream_t); \
+    template void launch_rev_dual<T>(const Dev &, const AdjBufs &, Mask, hipStream_t);
 #define INST_CHECK(T) template void launch_check<T>(const Dev &, int, hipStream_t, bool);
 #if PDHG_PART == 0
 INST_ELEM(float)

@@ -279,4 +279,13 @@ struct AdjBufs {
     double *ay, *aw, *aq;            // length M
 };
 
+// Clip masks of recorded steps: the bits of one step, at bit sh of byte i for
+// row i.  Two bits a step and row of K^T (0 interior, 1 at l, 2 at u), one a
+// row of K, so a byte holds 4 / 8 steps.
+struct Mask {
+    uint8_t *p = nullptr;
+    int sh = 0;
+};
+constexpr int MASK_PACK = 4; // recorded steps whose masks lie in one byte of a column
+
 }  // namespace pdhg

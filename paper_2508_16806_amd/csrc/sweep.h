@@ -128,6 +128,12 @@ __device__ __forceinline__ void sto(V *base, uint32_t idx, V v)
     *(V *)((char *)base + idx * (uint32_t)sizeof(V)) = v;
 }
 
+// Adds a row's bits to its mask byte; the step at bit 0 starts the byte.
+__device__ __forceinline__ void mask_put(uint8_t *mask, int64_t i, int sh, int code)
+{
+    mask[i] = (uint8_t)(sh ? mask[i] | (code << sh) : code);
+}
+
 // Sum (or max when MAXABS) of a value across the L lanes of a group.
 template <int L, bool MAXABS>
 __device__ __forceinline__ double group_reduce(double v)

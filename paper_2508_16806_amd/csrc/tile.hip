@@ -229,7 +229,7 @@ __device__ __forceinline__ void tile_blocks(const TileOp &op, int cnt, F &&f)
 }
 
 template <int W, typename T, int AVG, int MASK>
-__global__ __launch_bounds__(W) void k_primal_tile(Dev d, TileOp op, int j_in_chunk, uint8_t *__restrict__ mask)
+__global__ __launch_bounds__(W) void k_primal_tile(Dev d, TileOp op, int j_in_chunk, Mask mask)
 {
     T *__restrict__ x = (T *)d.x;
     T *__restrict__ xb = (T *)d.xbar;
@@ -257,13 +257,13 @@ __global__ __launch_bounds__(W) void k_primal_tile(Dev d, TileOp op, int j_in_ch
             x[j] = p.x;
             xb[j] = p.xbar;
             if (AVG) xa[j] = average_step<T>(v_a, p.x, v_0, w);
-            if (MASK) mask[j] = (uint8_t)p.clip;
+            if (MASK) mask_put(mask.p, j, mask.sh, p.clip);
         }
     });
 }
 
 template <int W, typename T, int AVG, int MASK>
-__global__ __launch_bounds__(W) void k_dual_tile(Dev d, TileOp op, int j_in_chunk, uint8_t *__restrict__ mask)
+__global__ __launch_bounds__(W) void k_dual_tile(Dev d, TileOp op, int j_in_chunk, Mask mask)
 {
     T *__restrict__ y = (T *)d.y;
     T *__restrict__ ya = (T *)d.yavg;
@@ -285,7 +285,7 @@ __global__ __launch_bounds__(W) void k_dual_tile(Dev d, TileOp op, int j_in_chun
             const DualStep<T> p = dual_step<T>(v_y, tile_sum()[r], v_q, sigma, r < b.nineq);
             y[i] = p.y;
             if (AVG) ya[i] = average_step<T>(v_a, p.y, v_0, w);
-            if (MASK) mask[i] = (uint8_t)p.pass;
+            if (MASK) mask_put(mask.p, i, mask.sh, p.pass);
         }
     });
 }
@@ -420,10 +420,10 @@ __global__ __launch_bounds__(TILE_WG) void k_act_tile(Dev d, TileOp K, TileOp Kt
 }  // namespace
 
 template <int W, typename T>
-static void primal_tile(const Dev &d, const TileOp &op, int j, int avg, uint8_t *mask, hipStream_t s)
+static void primal_tile(const Dev &d, const TileOp &op, int j, int avg, Mask mask, hipStream_t s)
 {
     const dim3 g(op.nblk < TILE_GRID ? op.nblk : TILE_GRID), wg(W);
-    if (mask)
+    if (mask.p)
         hipLaunchKernelGGL((k_primal_tile<W, T, 0, 1>), g, wg, op.lds, s, d, op, j, mask);
     else if (avg)
         hipLaunchKernelGGL((k_primal_tile<W, T, 1, 0>), g, wg, op.lds, s, d, op, j, mask);
@@ -432,10 +432,10 @@ static void primal_tile(const Dev &d, const TileOp &op, int j, int avg, uint8_t 
 }
 
 template <int W, typename T>
-static void dual_tile(const Dev &d, const TileOp &op, int j, int avg, uint8_t *mask, hipStream_t s)
+static void dual_tile(const Dev &d, const TileOp &op, int j, int avg, Mask mask, hipStream_t s)
 {
     const dim3 g(op.nblk < TILE_GRID ? op.nblk : TILE_GRID), wg(W);
-    if (mask)
+    if (mask.p)
         hipLaunchKernelGGL((k_dual_tile<W, T, 0, 1>), g, wg, op.lds, s, d, op, j, mask);
     else if (avg)
         hipLaunchKernelGGL((k_dual_tile<W, T, 1, 0>), g, wg, op.lds, s, d, op, j, mask);
@@ -444,7 +444,7 @@ static void dual_tile(const Dev &d, const TileOp &op, int j, int avg, uint8_t *m
 }
 
 template <typename T>
-void launch_primal_tile(const Dev &d, const TileOp &op, int j, int avg, uint8_t *mask, hipStream_t s)
+void launch_primal_tile(const Dev &d, const TileOp &op, int j, int avg, Mask mask, hipStream_t s)
 {
     if (op.direct)
         primal_tile<256, T>(d, op, j, avg, mask, s);
@@ -453,7 +453,7 @@ void launch_primal_tile(const Dev &d, const TileOp &op, int j, int avg, uint8_t 
 }
 
 template <typename T>
-void launch_dual_tile(const Dev &d, const TileOp &op, int j, int avg, uint8_t *mask, hipStream_t s)
+void launch_dual_tile(const Dev &d, const TileOp &op, int j, int avg, Mask mask, hipStream_t s)
 {
     if (op.direct)
         dual_tile<256, T>(d, op, j, avg, mask, s);
@@ -493,8 +493,8 @@ void launch_act_tile(const Dev &d, const TileOp &K, const TileOp &Kt, hipStream_
 }
 
 #define TILE_INST(T)                                                                                   \
-    template void launch_primal_tile<T>(const Dev &, const TileOp &, int, int, uint8_t *, hipStream_t); \
-    template void launch_dual_tile<T>(const Dev &, const TileOp &, int, int, uint8_t *, hipStream_t);   \
+    template void launch_primal_tile<T>(const Dev &, const TileOp &, int, int, Mask, hipStream_t); \
+    template void launch_dual_tile<T>(const Dev &, const TileOp &, int, int, Mask, hipStream_t);   \
     template void launch_tile_build<T>(const OpDev &, const TileOp &, hipStream_t);                     \
     template hipError_t tile_prepare<T>();
 TILE_INST(float)

@@ -11,7 +11,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libpdhg.so")
-SOURCES = [os.path.join(CSRC, f) for f in ("kernels.hip", "small.hip", "tile.hip", "fishnet.hip", "noalloc.hip", "capi.cpp")]
+SOURCES = [os.path.join(CSRC, f) for f in ("kernels.hip", "small.hip", "tile.hip", "spread.hip", "fishnet.hip", "noalloc.hip", "capi.cpp")]
 PARTS = {"kernels.hip": 9}  # compiled once per PDHG_PART, in parallel
 HEADERS = [os.path.join(CSRC, f) for f in ("pdhg_internal.h", "sweep.h", "kernels.h")] + \
     [os.path.join(ROOT, "include", "pdhg.h")]

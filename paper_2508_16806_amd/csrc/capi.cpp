@@ -221,6 +221,10 @@ struct InstPlan {
     // sampled entries within 32 columns (rows) of the entry before them in their
     // row (column), minus the others
     int64_t local[2] = {0, 0};
+    // sampled entries that are the first of their group of rows in a run of 16
+    // columns, doubled, minus all (negative: neighbouring rows, and columns, gather
+    // from the same lines)
+    int64_t apart = 0;
     TilePlan tile[2];
     SmallPlan small;
 };
@@ -309,15 +313,23 @@ static void plan_instance(const HostLP &h, const Bins &bins, const Bins &tbins, 
     constexpr int64_t STRETCH = 65536;
     const int64_t ns = h.nnz > 4 * STRETCH ? 4 : 1;
     std::vector<int32_t> last(h.n, INT32_MIN / 2);  // row of the column's entry before
+    std::vector<int32_t> line(h.n / 16 + 1, 0);     // last group with an entry in these columns
+    int32_t group = 0;
     for (int64_t w = 0; w < ns; ++w) {
-        int64_t left = ns > 1 ? STRETCH : h.nnz;
+        int64_t left = ns > 1 ? STRETCH : h.nnz, rows = 0, entries = 0;
+        ++group;
         for (int64_t i = h.m * w / ns; i < h.m * (w + 1) / ns && left > 0; ++i) {
             for (int64_t k = h.rp[i]; k < h.rp[i + 1]; ++k) {
                 const int32_t c = h.ci[k];
                 p.local[0] += (int32_t)i - last[c] < 32 ? 1 : -1;
                 last[c] = (int32_t)i;
                 if (k > h.rp[i]) p.local[1] += std::abs((int64_t)c - h.ci[k - 1]) < 32 ? 1 : -1;
+                p.apart += line[c >> 4] != group ? 1 : -1;
+                line[c >> 4] = group;
             }
+            ++rows;
+            entries += h.rp[i + 1] - h.rp[i];
+            if (rows >= 16 || (rows >= 4 && entries >= 16384)) ++group, rows = entries = 0;
             left -= h.rp[i + 1] - h.rp[i];
         }
     }
@@ -497,13 +509,18 @@ struct Sizes {
     // tile.hip: blocks, runs, quad ranges and quads of K^T (0) and K (1)
     int64_t tile_blk[2] = {0, 0}, tile_run[2] = {0, 0}, tile_sp[2] = {0, 0}, tile_q[2] = {0, 0};
     bool untiled[2] = {false, false};  // some instance's operator takes the row-binned sweeps
+    // spread.hip: windows, tiles and entries of K^T and K, and whether some rows are in no window
+    int64_t win[2] = {0, 0}, win_nt[2] = {0, 0}, win_n[2] = {0, 0};
+    bool unspread[2] = {false, false};
 };
 
-// The blocks of the tiled operators.
+// The blocks of the tiled operators and the windows of the spread ones.
 struct TileBlocks {
     std::vector<TileBlk> blk[2];
     std::vector<int4> run[2];
     std::vector<int2> inst[2];  // block range of every instance
+    std::vector<int4> win[2];   // windows of the spread operators
+    std::vector<char> spread[2]; // per segment of the instance: its rows are in windows
 };
 
 struct Buffers {
@@ -524,7 +541,8 @@ struct Buffers {
     int32_t *Ksb, *Ktsb;     // column-slice starts of every row of K / K^T (col_slices(_t) > 1)
     double *Kpart, *Ktpart;  // FP64 partial products of the sliced rows
     SmallDev small;
-    TileOp tile[2];  // K^T, K
+    TileOp tile[2];
+    SpreadOp spread[2];
 };
 
 struct pdhg_handle {
@@ -640,6 +658,24 @@ static void carve(Carve &cv, const Sizes &sz, int prec, const pdhg_opts &o, Dev 
         t.val = cv.take<char>(sz.tile_q[op] * 4 * es);
         t.inst = cv.take<int2>(sz.batch);
         t.act = cv.take<int32_t>(t.nblk);
+    }
+    b.spread[0] = b.spread[1] = SpreadOp{};
+    const int64_t gathered = std::max(sz.win_n[0], sz.win_n[1]);
+    void *g = gathered > 0 ? cv.take<char>(gathered * es) : nullptr;
+    for (int op = 0; op < 2; ++op) {
+        SpreadOp &w = b.spread[op];
+        w.nwin = (int32_t)sz.win[op];
+        if (w.nwin == 0) continue;
+        w.nt = (int32_t)sz.win_nt[op];
+        w.ncol = (int32_t)(op == 0 ? sz.M : sz.N);
+        w.n = (uint32_t)sz.win_n[op];
+        w.win = cv.take<int4>(w.nwin);
+        w.start = cv.take<uint32_t>((int64_t)w.nwin * w.nt);
+        w.lofs = cv.take<uint32_t>((int64_t)w.nwin * (w.nt + 1));
+        w.tb = cv.take<uint32_t>(w.nt + 1);
+        w.idx = cv.take<uint16_t>(sz.win_n[op] + 1);
+        w.place = cv.take<uint16_t>(sz.NNZ + 1);
+        w.g = g;
     }
     if (sz.small) {
         b.small.inst = cv.take<SmallInst>(sz.batch);
@@ -931,7 +967,53 @@ static void tile_blocks(const std::vector<InstPlan> &plans, const pdhg_opts *o, 
     }
 }
 
-// layouts: also plan the operators' second layouts (small.hip, tile.hip),
+// The windows of an operator that sweeps in two passes: rows in order, as many
+// as fit, of one segment each (so of one lane count); a segment with a row that
+// fits no window stays with the row-binned sweeps.  One LP per handle: its rows'
+// sums are the row-binned ones to the bit, so a batch need not follow.  Taken
+// where the gathered vector is long for a 4 MB L2 shared with the matrix stream
+// and the matrix pays for two launches and the tiles' copies.  Measured, us (row
+// bins / two passes): FP32, vector of 8 MB and 54M nonzeros 595 / 223, 4 MB and
+// 54M 379 / 236, 4 MB and 27M 211 / 113, 2 MB and 27M 177 / 119, 2 MB and 14M
+// 72 / 64, 1.6 MB and 8M 54 / 40, 1.6 MB and 4.8M 37 / 37, 1 MB and 14M 61 / 67,
+// 4 MB and 2M 24 / 26; FP64, 8 MB and 54M 478 / 465, 8 MB and 8M 105 / 74, 4 MB
+// and 27M 231 / 237, 3.2 MB and 8M 78 / 83.  Where rows near each other gather
+// from the same lines, L1 serves the row-binned sweeps: the dual sweep of a
+// dispatch LP of 15M nonzeros takes 26 so, 81 in two passes.
+static void spread_windows(const InstPlan &p, int64_t es, Sizes &sz, TileBlocks &tb)
+{
+    const int64_t cap = SPREAD_BYTES / es, width = SPREAD_TILE / es;
+    for (int op = 0; op < 2; ++op) {
+        const auto &segs = op == 0 ? p.segT : p.segK;
+        const int64_t cols = op == 0 ? p.m : p.n, nt = (cols + width - 1) / width;
+        if (sz.tile_blk[op] > 0 || p.local[op] > 0 || p.apart < 0 || nt > SPREAD_TILES || p.nnz >= INT32_MAX) continue;
+        if (cols * es < (es == 4 ? 1500000 : 5000000) || p.nnz < 5000000) continue;
+        if (std::any_of(segs.begin(), segs.end(), [](const SegH &g) { return g.sliced != 0; })) continue;
+        auto &win = tb.win[op];
+        int64_t entries = 0;
+        for (const SegH &g : segs) {
+            const int32_t *len = p.len[op].data() + g.row0;
+            const bool fits = std::all_of(len, len + g.nrows, [&](int32_t l) { return l <= cap; });
+            tb.spread[op].push_back(fits);
+            sz.unspread[op] |= !fits;
+            int64_t n = 0, r0 = 0;
+            for (int64_t r = 0; fits && r <= g.nrows; ++r) {
+                if (r == g.nrows || n + len[r] > cap || r - r0 == cap) {
+                    if (r > r0) win.push_back(make_int4((int)(g.row0 + r0), (int)(r - r0), g.lanes_log2 & 15, 0));
+                    entries += n;
+                    n = 0, r0 = r;
+                }
+                if (r < g.nrows) n += len[r];
+            }
+        }
+        sz.win[op] = (int64_t)win.size();
+        sz.win_nt[op] = nt;
+        sz.win_n[op] = entries;
+        if (win.empty()) tb.spread[op].clear();
+    }
+}
+
+// layouts: also plan the operators' second layouts (small.hip, tile.hip, spread.hip),
 // which take workspace of their own
 static int plan_all(const pdhg_lp *lp, int32_t batch, const pdhg_opts *o, std::vector<HostLP> &hosts,
                     std::vector<InstPlan> &plans, Sizes &sz, bool pattern_only, bool layouts = true,
@@ -999,6 +1081,7 @@ static int plan_all(const pdhg_lp *lp, int32_t batch, const pdhg_opts *o, std::v
     if (layouts && !sz.small && sz.NNZ <= TILE_MAX_NNZ) {
         TileBlocks tb;
         tile_blocks(plans, o, sz, tb);
+        if (batch == 1) spread_windows(plans[0], (int64_t)elem_size(o->precision), sz, tb);
         if (tiles) *tiles = std::move(tb);
     }
     // sweeps address the gathered vectors with 32-bit byte offsets
@@ -1277,7 +1360,7 @@ static int upload(pdhg_handle *h, std::vector<HostLP> &hosts, const TileBlocks &
             sg.inst = bi;
             sg.ineq = sh.ineq;
             sg.sliced = sh.sliced;
-            sg.tiled = sz.tile_blk[1] > 0 && p.tile[1].ntile > 0;
+            sg.tiled = sz.tile_blk[1] > 0 ? p.tile[1].ntile > 0 : sz.win[1] > 0 && tiles.spread[1][si];
             for (int t = 0; t < sg.nblk; ++t) {
                 Kbs[blkK + t] = (int32_t)Kseg.size();
                 const int G = seg_group(sg.lanes_log2);
@@ -1300,7 +1383,7 @@ static int upload(pdhg_handle *h, std::vector<HostLP> &hosts, const TileBlocks &
             sg.lanes_log2 = sh.lanes_log2;
             sg.inst = bi;
             sg.ineq = 0;
-            sg.tiled = sz.tile_blk[0] > 0 && p.tile[0].ntile > 0;
+            sg.tiled = sz.tile_blk[0] > 0 ? p.tile[0].ntile > 0 : sz.win[0] > 0 && tiles.spread[0][si];
             for (int t = 0; t < sg.nblk; ++t) {
                 Ktbs[blkT + t] = (int32_t)Ktseg.size();
                 const int G = seg_group(sg.lanes_log2);
@@ -1375,6 +1458,8 @@ static int upload(pdhg_handle *h, std::vector<HostLP> &hosts, const TileBlocks &
             (rc = h2d((int2 *)t.inst, tiles.inst[op].data(), tiles.inst[op].size(), s)))
             return rc;
     }
+    for (int op = 0; op < 2; ++op)
+        if (sz.win[op] > 0 && (rc = h2d((int4 *)b.spread[op].win, tiles.win[op].data(), tiles.win[op].size(), s))) return rc;
     // small instances: their tasks, row numbers and slots, concatenated
     std::vector<SmallInst> sinst(sz.small ? h->batch : 0);
     if (sz.small) {
@@ -1438,6 +1523,8 @@ static int device_setup(pdhg_handle *h, hipStream_t s)
             HIPCHK(tile_prepare<T>());
             launch_tile_build<T>(op == 0 ? d.Kt : d.K, h->buf.tile[op], s);
         }
+    for (int op = 0; op < 2; ++op)
+        if (h->buf.spread[op].nwin > 0) launch_spread_build<T>(op == 0 ? d.Kt : d.K, h->buf.spread[op], s);
     HIPCHK(hipGetLastError());
     // norms of the scaled cost and right-hand side (primal weight, Section 2.4.3)
     std::vector<double> cn2(B), qn2(B);
@@ -1792,6 +1879,12 @@ template <typename T>
 static void enqueue_primal(const pdhg_handle *h, const Dev &d, int j, int avg, Mask mask, hipStream_t s)
 {
     const TileOp &t = h->buf.tile[0];
+    const SpreadOp &w = h->buf.spread[0];
+    if (w.nwin > 0) {
+        launch_spread_primal<T>(d, w, j, avg, mask, s);
+        if (h->sz.unspread[0]) launch_primal<T>(d, j, avg, mask, s, 1);
+        return;
+    }
     if (t.nblk > 0) launch_primal_tile<T>(d, t, j, avg, mask, s);
     if (t.nblk == 0 || h->sz.untiled[0]) launch_primal<T>(d, j, avg, mask, s, t.nblk > 0);
 }
@@ -1800,6 +1893,12 @@ template <typename T>
 static void enqueue_dual(const pdhg_handle *h, const Dev &d, int j, int avg, Mask mask, hipStream_t s)
 {
     const TileOp &t = h->buf.tile[1];
+    const SpreadOp &w = h->buf.spread[1];
+    if (w.nwin > 0) {
+        launch_spread_dual<T>(d, w, j, avg, h->info[0].m1, mask, s);
+        if (h->sz.unspread[1]) launch_dual<T>(d, j, avg, mask, s, 1);
+        return;
+    }
     if (t.nblk > 0) launch_dual_tile<T>(d, t, j, avg, mask, s);
     if (t.nblk == 0 || h->sz.untiled[1]) launch_dual<T>(d, j, avg, mask, s, t.nblk > 0);
 }
@@ -2817,6 +2916,9 @@ static int autotune_impl(const pdhg_lp *lp, int32_t batch, const pdhg_opts *base
                     bound.tile_run[op] = std::max(bound.tile_run[op], sz.tile_run[op]);
                     bound.tile_sp[op] = std::max(bound.tile_sp[op], sz.tile_sp[op]);
                     bound.tile_q[op] = std::max(bound.tile_q[op], sz.tile_q[op]);
+                    bound.win[op] = std::max(bound.win[op], sz.win[op]);
+                    bound.win_nt[op] = std::max(bound.win_nt[op], sz.win_nt[op]);
+                    bound.win_n[op] = std::max(bound.win_n[op], sz.win_n[op]);
                 }
                 for (int op = 0; op < 2; ++op) {
                     bound.small_tasks[op] = std::max(bound.small_tasks[op], sz.small_tasks[op]);

@@ -20,6 +20,12 @@ template <typename T>
 hipError_t tile_prepare();
 void launch_act_tile(const Dev &d, const TileOp &K, const TileOp &Kt, hipStream_t s);
 template <typename T>
+void launch_spread_primal(const Dev &d, const SpreadOp &so, int j, int avg, Mask mask, hipStream_t s);
+template <typename T>
+void launch_spread_dual(const Dev &d, const SpreadOp &so, int j, int avg, int64_t m1, Mask mask, hipStream_t s);
+template <typename T>
+void launch_spread_build(const OpDev &op, const SpreadOp &so, hipStream_t s);
+template <typename T>
 void launch_small(const Dev &d, const SmallDev &sd, int j0, int count, int avg, hipStream_t s);
 template <typename T>
 void launch_small_fill(const Dev &d, const SmallDev &sd, hipStream_t s);

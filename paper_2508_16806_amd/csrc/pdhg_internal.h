@@ -273,6 +273,26 @@ struct TileOp {
     int32_t *act;       // blocks of the running instances
 };
 
+// Operators whose sweeps run in two passes (spread.hip): gather by column tile,
+// sum by window of rows.
+constexpr int SPREAD_WG = 1024;
+constexpr int SPREAD_GRID = 512;           // workgroups of the gather pass: two per CU
+constexpr int SPREAD_TILE = 64 * 1024;     // bytes of the vector in a tile
+constexpr int SPREAD_BYTES = 62 * 1024;    // bytes of gathered values in a window
+constexpr int SPREAD_TILES = 1024;         // tiles at most
+struct SpreadOp {
+    int32_t nwin;       // 0: not spread
+    int32_t nt, ncol;
+    uint32_t n;         // entries in the windows
+    const int4 *win;    // {first row, rows, lanes_log2, 0}
+    uint32_t *start;    // where window w's run of tile t begins: [w * nt + t]
+    uint32_t *lofs;     // and its place in the window: [w * (nt + 1) + t]
+    uint32_t *tb;       // first entry of each tile, nt + 1
+    uint16_t *idx;      // column within the tile, in tile order
+    uint16_t *place;    // place in the window, in the operator's order
+    void *g;            // gathered values, in tile order (both operators')
+};
+
 // FP64 adjoint vectors of the unrolled-step backward pass.
 struct AdjBufs {
     double *ax, *av, *ac, *al, *au;  // length N

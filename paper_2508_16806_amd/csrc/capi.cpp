@@ -545,6 +545,11 @@ struct Buffers {
     SpreadOp spread[2];
 };
 
+// Longest point (n + m) that goes through the handle's pinned memory (512 KB).
+// set_state / get_solution, us, there and by copies: 20 / 19 and 44 / 44 at 700
+// values, 32 / 39 at 32,000 there, 62 / 87 at 90,000 by copies.
+constexpr int64_t IO_LEN = 65536;
+
 struct pdhg_handle {
     int32_t batch = 0;
     int32_t prec = PDHG_PREC_F32;
@@ -558,6 +563,12 @@ struct pdhg_handle {
     std::vector<int32_t> sol_avg;  // returned point of the last solve
     std::vector<double> knorm;
     int32_t *hdone_host = nullptr;
+    // Pinned memory behind the flags for one instance's point, read and written by
+    // the kernels themselves: set_state and get_solution of a small instance are one
+    // launch and one wait, 44 us before with a pageable copy each for x and y and
+    // three kernels (one over the whole batch).
+    double *io_host = nullptr, *io_dev = nullptr;
+    int64_t io_len = 0;
     size_t ws_bytes = 0;
     double setup_seconds = 0;
     double setup_phase[5] = {0, 0, 0, 0, 0};  // plan, host images, copies, device, power iteration
@@ -1709,7 +1720,10 @@ static int setup_impl(const pdhg_lp *lp, int32_t batch, const pdhg_opts *o, void
     if (dev_done) {
         d.hdone = dev_done;
     } else {
-        if (hipHostMalloc((void **)&h->hdone_host, sizeof(int32_t) * batch,
+        const size_t flags = (sizeof(int32_t) * batch + 255) / 256 * 256;
+        for (const InstPlan &p : h->plan)
+            if (p.n + p.m <= IO_LEN) h->io_len = std::max(h->io_len, p.n + p.m);
+        if (hipHostMalloc((void **)&h->hdone_host, flags + sizeof(double) * h->io_len,
                           hipHostMallocMapped | hipHostMallocCoherent) != hipSuccess) {
             delete h;
             return fail(PDHG_ERR_HIP, "hipHostMalloc failed");
@@ -1720,6 +1734,8 @@ static int setup_impl(const pdhg_lp *lp, int32_t batch, const pdhg_opts *o, void
             delete h;
             return fail(PDHG_ERR_HIP, "hipHostGetDevicePointer failed");
         }
+        h->io_host = (double *)((char *)h->hdone_host + flags);
+        h->io_dev = (double *)((char *)d.hdone + flags);
     }
     rc = upload(h, hosts, tiles, stream);
     hosts.clear();
@@ -2294,6 +2310,18 @@ extern "C" int pdhg_get_solution(pdhg_handle *h, int32_t inst, int32_t which, do
     const Dev &d = h->d;
     const InstInfo &in = h->info[inst];
     const int avg = which == PDHG_SOL_AVERAGE || (which == PDHG_SOL_RESULT && h->sol_avg[inst]);
+    if (mem == PDHG_MEM_HOST && !lambda && (int64_t)in.n + in.m <= h->io_len) {
+        if (h->prec == PDHG_PREC_F32)
+            launch_point_out<float>(d, avg, in.xoff, in.n, in.yoff, in.m, h->io_dev, s);
+        else
+            launch_point_out<double>(d, avg, in.xoff, in.n, in.yoff, in.m, h->io_dev, s);
+        HIPCHK(hipGetLastError());
+        HIPCHK(hipStreamSynchronize(s));
+        const InstPlan &p = h->plan[inst];
+        for (int64_t t = 0; x && t < in.n; ++t) x[p.col_order[t]] = h->io_host[t];
+        for (int64_t t = 0; y && t < in.m; ++t) y[p.row_order[t]] = h->io_host[in.n + t];
+        return PDHG_OK;
+    }
     if (h->prec == PDHG_PREC_F32)
         launch_point_to64<float>(d, avg, d.vecN64, d.vecM64, s);
     else
@@ -2347,9 +2375,21 @@ extern "C" int pdhg_set_state(pdhg_handle *h, int32_t inst, const double *x, con
                               hipStream_t s)
 {
     if (!h || inst < 0 || inst >= h->batch || !x || !y) return fail(PDHG_ERR_INVALID_ARG, "bad arguments");
+    const InstInfo &in = h->info[inst];
+    if (mem != PDHG_MEM_DEVICE && (int64_t)in.n + in.m <= h->io_len) {
+        const InstPlan &p = h->plan[inst];
+        for (int64_t t = 0; t < in.n; ++t) h->io_host[t] = x[p.col_order[t]];
+        for (int64_t t = 0; t < in.m; ++t) h->io_host[in.n + t] = y[p.row_order[t]];
+        if (h->prec == PDHG_PREC_F32)
+            launch_point_in<float>(h->d, in.xoff, in.n, in.yoff, in.m, in.m1, h->io_dev, s);
+        else
+            launch_point_in<double>(h->d, in.xoff, in.n, in.yoff, in.m, in.m1, h->io_dev, s);
+        HIPCHK(hipGetLastError());
+        HIPCHK(hipStreamSynchronize(s));
+        return PDHG_OK;
+    }
     int rc = scale_caller_point(h, inst, x, y, mem, s);
     if (rc) return rc;
-    const InstInfo &in = h->info[inst];
     if (h->prec == PDHG_PREC_F32)
         launch_set_point<float>(h->d, in.xoff, in.n, in.yoff, in.m, in.m1, h->d.vecN64, h->d.vecM64, s);
     else

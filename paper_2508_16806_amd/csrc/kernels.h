@@ -81,6 +81,12 @@ void launch_permute_out(const int32_t *perm, int64_t off, int64_t n, const doubl
 void launch_scale_in(const Dev &d, int64_t xoff, int64_t n, int64_t yoff, int64_t m, const double *xin,
                      const double *yin, double *xs, double *ys, hipStream_t s);
 template <typename T>
+void launch_point_in(const Dev &d, int64_t xoff, int64_t n, int64_t yoff, int64_t m, int64_t m1, const double *in,
+                     hipStream_t s);
+template <typename T>
+void launch_point_out(const Dev &d, int which, int64_t xoff, int64_t n, int64_t yoff, int64_t m, double *out,
+                      hipStream_t s);
+template <typename T>
 void launch_set_point(const Dev &d, int64_t xoff, int64_t n, int64_t yoff, int64_t m, int64_t m1,
                       const double *xs, const double *ys, hipStream_t s);
 void launch_kkt_final(const Dev &d, int inst, double *out9, hipStream_t s);

@@ -1624,6 +1624,54 @@ __global__ void k_set_point(Dev d, int64_t xoff, int64_t n, int64_t yoff, int64_
     }
 }
 
+// The two for a small instance in one launch each, in internal order (the host
+// permutes) straight from and to pinned memory.
+template <typename T>
+__global__ void k_point_in(Dev d, int64_t xoff, int64_t n, int64_t yoff, int64_t m, int64_t m1,
+                           const double *__restrict__ in)
+{
+    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (t < n) {
+        const int64_t j = xoff + t;
+        double v = in[t] / d.kap[j];
+        const double l = d.l64[j], u = d.u64[j];
+        v = v < l ? l : (v > u ? u : v);
+        ((T *)d.x)[j] = (T)v;
+        ((T *)d.x0)[j] = (T)v;
+        ((T *)d.xavg)[j] = (T)0;
+    }
+    if (t < m) {
+        const int64_t i = yoff + t;
+        double v = in[n + t] / d.rho[i];
+        if (t < m1 && v < 0.0) v = 0.0;
+        ((T *)d.y)[i] = (T)v;
+        ((T *)d.y0)[i] = (T)v;
+        ((T *)d.yavg)[i] = (T)0;
+    }
+}
+
+template <typename T>
+__global__ void k_point_out(Dev d, int which, int64_t xoff, int64_t n, int64_t yoff, int64_t m,
+                            double *__restrict__ out)
+{
+    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (t < n) {
+        const int64_t j = xoff + t;
+        const double xs = which ? (double)(T)((double)((const T *)d.x0)[j] + (double)((const T *)d.xavg)[j])
+                                : (double)((const T *)d.x)[j];
+        double v = d.kap[j] * xs;
+        const double l = d.lraw[j], u = d.uraw[j];
+        v = v < l ? l : (v > u ? u : v);
+        out[t] = v;
+    }
+    if (t < m) {
+        const int64_t i = yoff + t;
+        const double ys = which ? (double)(T)((double)((const T *)d.y0)[i] + (double)((const T *)d.yavg)[i])
+                                : (double)((const T *)d.y)[i];
+        out[n + t] = d.rho[i] * ys;
+    }
+}
+
 // KKT terms of a single candidate for one instance from the check partials
 __global__ __launch_bounds__(WG) void k_kkt_final(Dev d, int inst, double *out9)
 {
@@ -2126,6 +2174,20 @@ void launch_set_point(const Dev &d, int64_t xoff, int64_t n, int64_t yoff, int64
     LAUNCH(k_set_point<T>, nblk_elem(n > m ? n : m), d, xoff, n, yoff, m, m1, xs, ys);
 }
 
+template <typename T>
+void launch_point_in(const Dev &d, int64_t xoff, int64_t n, int64_t yoff, int64_t m, int64_t m1, const double *in,
+                     hipStream_t s)
+{
+    LAUNCH(k_point_in<T>, nblk_elem(n > m ? n : m), d, xoff, n, yoff, m, m1, in);
+}
+
+template <typename T>
+void launch_point_out(const Dev &d, int which, int64_t xoff, int64_t n, int64_t yoff, int64_t m, double *out,
+                      hipStream_t s)
+{
+    LAUNCH(k_point_out<T>, nblk_elem(n > m ? n : m), d, which, xoff, n, yoff, m, out);
+}
+
 #if PDHG_PART == 0
 void launch_kkt_final(const Dev &d, int inst, double *out9, hipStream_t s)
 {
@@ -2186,6 +2248,9 @@ void launch_set_raw(const Dev &d, const double *c, const double *q, const double
     template void launch_init_point<T>(const Dev &, hipStream_t);                            \
     template void launch_epoch_start<T>(const Dev &, hipStream_t);                           \
     template void launch_point_to64<T>(const Dev &, int, double *, double *, hipStream_t);   \
+    template void launch_point_in<T>(const Dev &, int64_t, int64_t, int64_t, int64_t, int64_t, const double *, \
+                                     hipStream_t);                                           \
+    template void launch_point_out<T>(const Dev &, int, int64_t, int64_t, int64_t, int64_t, double *, hipStream_t); \
     template void launch_set_point<T>(const Dev &, int64_t, int64_t, int64_t, int64_t, int64_t, \
                                       const double *, const double *, hipStream_t);
 #define INST_STEP(T)                                                                        \

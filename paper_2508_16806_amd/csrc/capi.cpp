@@ -539,7 +539,7 @@ struct Buffers {
     int32_t *l2inst;
     int64_t *bcumK, *bcumT;  // block cost prefix sums
     int32_t *Ksb, *Ktsb;     // column-slice starts of every row of K / K^T (col_slices(_t) > 1)
-    double *Kpart, *Ktpart;  // FP64 partial products of the sliced rows
+    double *Kpart, *Ktpart;  // FP64 partial products of the sliced rows, a check's products of rows in windows
     SmallDev small;
     TileOp tile[2];
     SpreadOp spread[2];
@@ -652,10 +652,11 @@ static void carve(Carve &cv, const Sizes &sz, int prec, const pdhg_opts &o, Dev 
     const int S = o.col_slices > 1 ? o.col_slices : 1, St = o.col_slices_t > 1 ? o.col_slices_t : 1;
     b.Ksb = S > 1 ? cv.take<int32_t>((size_t)M * (S - 1)) : nullptr;
     // the sweeps' partials (M), and the solve-time check's for its two
-    // candidates (2 M, the first M shared: the check runs between chunks)
-    b.Kpart = S > 1 ? cv.take<double>(2 * (size_t)M) : nullptr;
+    // candidates (2 M, the first M shared: the check runs between chunks);
+    // the check's products of operators in windows
+    b.Kpart = S > 1 || sz.win[1] > 0 ? cv.take<double>(2 * (size_t)M) : nullptr;
     b.Ktsb = St > 1 ? cv.take<int32_t>((size_t)N * (St - 1)) : nullptr;
-    b.Ktpart = St > 1 ? cv.take<double>(N) : nullptr;
+    b.Ktpart = sz.win[0] > 0 ? cv.take<double>(2 * (size_t)N) : (St > 1 ? cv.take<double>(N) : nullptr);
     b.small = SmallDev{};
     b.tile[0] = b.tile[1] = TileOp{};
     for (int op = 0; op < 2; ++op) {
@@ -1980,7 +1981,7 @@ static void enqueue_chunk(const pdhg_handle *h, hipStream_t s)
     }
     const bool small = h->sz.small;
     // the small instances' launches leave the average point ready
-    launch_check<T>(d, avg, s, !(small && !h->opts.adaptive_step));
+    launch_check<T>(d, avg, s, !(small && !h->opts.adaptive_step), h->buf.spread);
     // Algorithm 6 on the difference of the last step: the iterate before it is
     // in (xavg1, y1) with fixed steps, in buffer 1 (xbar, y1) with adaptive ones
     if (detect) launch_infeas<T>(d, h->opts.adaptive_step ? d.xbar : d.xavg1, d.y1, s);
@@ -2045,7 +2046,7 @@ static int solve_impl(pdhg_handle *h, pdhg_result *res, hipStream_t s)
     HIPCHK(hipMemcpyAsync(d.st, st.data(), B * sizeof(InstState), hipMemcpyHostToDevice, s));
     enqueue_active(h, d, s);
     launch_epoch_start<T>(d, s);
-    launch_check<T>(d, 0, s);
+    launch_check<T>(d, 0, s, true, h->buf.spread);
     launch_control<T>(d, ctl_params(h), 0, s);
     if (B > 1) enqueue_active(h, d, s);
     if (h->opts.adaptive_step) launch_kx_ad<T>(d, 1, s);
@@ -2762,7 +2763,7 @@ static int time_impl(pdhg_handle *h, int32_t reps, pdhg_kernel_times *out, hipSt
         (void)hipEventRecord(ev[0], s);
         for (int r = 0; r < reps; ++r) {
             switch (phase) {
-                case 2: launch_check<T>(d, avg, s); break;
+                case 2: launch_check<T>(d, avg, s, true, h->buf.spread); break;
                 case 3: launch_control<T>(d, Pr, h->opts.check_every, s); break;
                 default: launch_restart<T>(d, s); break;
             }

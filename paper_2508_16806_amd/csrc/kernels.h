@@ -24,6 +24,8 @@ void launch_spread_primal(const Dev &d, const SpreadOp &so, int j, int avg, Mask
 template <typename T>
 void launch_spread_dual(const Dev &d, const SpreadOp &so, int j, int avg, int64_t m1, Mask mask, hipStream_t s);
 template <typename T>
+void launch_spread_products(const Dev &d, const SpreadOp &so, int onK, const void *v, double *out, hipStream_t s);
+template <typename T>
 void launch_spread_build(const OpDev &op, const SpreadOp &so, hipStream_t s);
 template <typename T>
 void launch_small(const Dev &d, const SmallDev &sd, int j0, int count, int avg, hipStream_t s);
@@ -44,7 +46,7 @@ void launch_infeas(const Dev &d, const void *xp, const void *yp, hipStream_t s);
 template <typename T>
 void launch_save_prev(const Dev &d, hipStream_t s);
 template <typename T>
-void launch_check(const Dev &d, int avg, hipStream_t s, bool avg_point = true);
+void launch_check(const Dev &d, int avg, hipStream_t s, bool avg_point, const SpreadOp *spread);
 void launch_check64(const Dev &d, const double *xs, const double *ys, hipStream_t s);
 template <typename T>
 void launch_control(const Dev &d, const CtlParams &P, int iters_done, hipStream_t s, int copy = 0);

@@ -41,12 +41,11 @@ __device__ __forceinline__ void wave_copy(const T *src, T *to, int n)
 // Pass 1.  Every workgroup takes an equal run of the entries in tile order and
 // the tiles (1.2 on average at two workgroups per CU) they lie in.
 template <typename T, int OP>
-__global__ __launch_bounds__(SPREAD_WG, 8) void k_spread(Dev d, SpreadOp op)
+__global__ __launch_bounds__(SPREAD_WG, 8) void k_spread(Dev d, SpreadOp op, const T *__restrict__ v)
 {
     constexpr int WIDTH = SPREAD_TILE / (int)sizeof(T);
     __shared__ __align__(16) T tile[WIDTH];
     if (d.act_cnt[OP == 0 ? 1 : 0] == 0) return;
-    const T *__restrict__ v = (const T *)(OP == 0 ? d.y : d.xbar);
     const uint16_t *__restrict__ idx = op.idx;
     T *__restrict__ g = (T *)op.g;
     const int tid = threadIdx.x;
@@ -106,7 +105,7 @@ __global__ __launch_bounds__(SPREAD_WG, 8) void k_spread(Dev d, SpreadOp op)
 
 // Pass 2: pre(row) loads the operands of a row ahead of its sum and returns the
 // update as a function of that sum.
-template <typename T, typename Pre>
+template <typename T, typename MV, typename Pre>
 __device__ __forceinline__ void spread_rows(const OpDev &op, const SpreadOp &so, Pre &&pre)
 {
     __shared__ __align__(16) T win[SPREAD_BYTES / sizeof(T)];
@@ -133,7 +132,7 @@ __device__ __forceinline__ void spread_rows(const OpDev &op, const SpreadOp &so,
     const int64_t *__restrict__ rp = op.rp + b.x;
     const int64_t p0 = rp[0];
     const uint16_t *__restrict__ place = so.place + p0;
-    const T *__restrict__ va = op_vals<T>(op) + p0;
+    const MV *__restrict__ va = op_vals<MV>(op) + p0;
     const int lg = b.z, L = 1 << lg, G = SPREAD_WG >> lg, gl = tid & (L - 1);
     for (int r0 = 0; r0 < b.y; r0 += G) {
         const int r = r0 + (tid >> lg);
@@ -145,7 +144,7 @@ __device__ __forceinline__ void spread_rows(const OpDev &op, const SpreadOp &so,
         double acc = 0.0;
         for (uint32_t p = o0 + gl; p < o1; p += 4 * L) {
             uint32_t at[4];
-            T a[4];
+            MV a[4];
 #pragma unroll
             for (int k = 0; k < 4; ++k) {
                 const uint32_t q = p + k * L < o1 ? p + k * L : p;
@@ -179,7 +178,7 @@ __global__ __launch_bounds__(SPREAD_WG, 8) void k_spread_primal(Dev d, SpreadOp 
     T *__restrict__ xa = (T *)d.xavg;
     const double tau = d.st->tau;
     const double w = AVG ? 1.0 / (double)(d.st->t_inner + j_in_chunk + 1) : 0.0;
-    spread_rows<T>(d.Kt, so, [&](int64_t j) {
+    spread_rows<T, T>(d.Kt, so, [&](int64_t j) {
         const T v_x = x[j], v_c = ((const T *)d.c)[j], v_l = ((const T *)d.l)[j], v_u = ((const T *)d.u)[j];
         const T v_a = AVG ? xa[j] : T(0), v_0 = AVG ? ((const T *)d.x0)[j] : T(0);
         return [=](double g) {
@@ -201,7 +200,7 @@ __global__ __launch_bounds__(SPREAD_WG, 8) void k_spread_dual(Dev d, SpreadOp so
     T *__restrict__ ya = (T *)d.yavg;
     const double sigma = d.st->sigma;
     const double w = AVG ? 1.0 / (double)(d.st->t_inner + j_in_chunk + 1) : 0.0;
-    spread_rows<T>(d.K, so, [&](int64_t i) {
+    spread_rows<T, T>(d.K, so, [&](int64_t i) {
         const T v_y = y[i], v_q = ((const T *)d.q)[i];
         const T v_a = AVG ? ya[i] : T(0), v_0 = AVG ? ((const T *)d.y0)[i] : T(0);
         return [=](double r) {
@@ -211,6 +210,15 @@ __global__ __launch_bounds__(SPREAD_WG, 8) void k_spread_dual(Dev d, SpreadOp so
             if (MASK) mask_put(mask.p, i, mask.sh, p.pass);
         };
     });
+}
+
+// The FP64 products a check needs (k_check's sums to the bit: the same values in
+// the same order), one per row.
+template <typename T, int OP>
+__global__ __launch_bounds__(SPREAD_WG, 8) void k_spread_products(Dev d, SpreadOp so, double *__restrict__ out)
+{
+    if (d.act_cnt[OP == 0 ? 1 : 0] == 0) return;
+    spread_rows<T, double>(OP == 0 ? d.Kt : d.K, so, [&](int64_t r) { return [=](double g) { out[r] = g; }; });
 }
 
 // The layout, from the CSR operator: entries per window and tile with their
@@ -309,7 +317,7 @@ template <typename T>
 void launch_spread_primal(const Dev &d, const SpreadOp &so, int j, int avg, Mask mask, hipStream_t s)
 {
     const dim3 g(so.nwin), wg(SPREAD_WG);
-    hipLaunchKernelGGL((k_spread<T, 0>), dim3(SPREAD_GRID), wg, 0, s, d, so);
+    hipLaunchKernelGGL((k_spread<T, 0>), dim3(SPREAD_GRID), wg, 0, s, d, so, (const T *)d.y);
     if (mask.p)
         hipLaunchKernelGGL((k_spread_primal<T, 0, 1>), g, wg, 0, s, d, so, j, mask);
     else if (avg)
@@ -322,13 +330,26 @@ template <typename T>
 void launch_spread_dual(const Dev &d, const SpreadOp &so, int j, int avg, int64_t m1, Mask mask, hipStream_t s)
 {
     const dim3 g(so.nwin), wg(SPREAD_WG);
-    hipLaunchKernelGGL((k_spread<T, 1>), dim3(SPREAD_GRID), wg, 0, s, d, so);
+    hipLaunchKernelGGL((k_spread<T, 1>), dim3(SPREAD_GRID), wg, 0, s, d, so, (const T *)d.xbar);
     if (mask.p)
         hipLaunchKernelGGL((k_spread_dual<T, 0, 1>), g, wg, 0, s, d, so, j, m1, mask);
     else if (avg)
         hipLaunchKernelGGL((k_spread_dual<T, 1, 0>), g, wg, 0, s, d, so, j, m1, mask);
     else
         hipLaunchKernelGGL((k_spread_dual<T, 0, 0>), g, wg, 0, s, d, so, j, m1, mask);
+}
+
+template <typename T>
+void launch_spread_products(const Dev &d, const SpreadOp &so, int onK, const void *v, double *out, hipStream_t s)
+{
+    const dim3 g(so.nwin), wg(SPREAD_WG);
+    if (onK) {
+        hipLaunchKernelGGL((k_spread<T, 1>), dim3(SPREAD_GRID), wg, 0, s, d, so, (const T *)v);
+        hipLaunchKernelGGL((k_spread_products<T, 1>), g, wg, 0, s, d, so, out);
+    } else {
+        hipLaunchKernelGGL((k_spread<T, 0>), dim3(SPREAD_GRID), wg, 0, s, d, so, (const T *)v);
+        hipLaunchKernelGGL((k_spread_products<T, 0>), g, wg, 0, s, d, so, out);
+    }
 }
 
 template <typename T>
@@ -344,6 +365,7 @@ void launch_spread_build(const OpDev &op, const SpreadOp &so, hipStream_t s)
 #define SPREAD_INST(T)                                                                                      \
     template void launch_spread_primal<T>(const Dev &, const SpreadOp &, int, int, Mask, hipStream_t);       \
     template void launch_spread_dual<T>(const Dev &, const SpreadOp &, int, int, int64_t, Mask, hipStream_t); \
+    template void launch_spread_products<T>(const Dev &, const SpreadOp &, int, const void *, double *, hipStream_t); \
     template void launch_spread_build<T>(const OpDev &, const SpreadOp &, hipStream_t);
 SPREAD_INST(float)
 SPREAD_INST(double)

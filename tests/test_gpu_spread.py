@@ -32,7 +32,8 @@ def _lp(m, n, nnz, longest, seed, transpose):
 @pytest.mark.parametrize("longest", [3000, 40000])
 def test_steps_equal_the_row_binned_ones(prec, transpose, longest):
     """One LP per handle takes the two passes, the same LP in a batch the
-    row-binned sweeps: equal iterates, averages and gradients.  With a row too
+    row-binned sweeps: equal iterates, averages, gradients and
+    residuals.  With a row too
     long for a window its segment stays row-binned on both."""
     import paper_2508_16806_amd as pd
 
@@ -51,7 +52,8 @@ def test_steps_equal_the_row_binned_ones(prec, transpose, longest):
     ga, gb = one.backward(gx, gy), two.backward(pad(gx, other.n), pad(gy, other.m))
     for k in ga:
         assert np.array_equal(ga[k], gb[k][:ga[k].size]), k
-    one.solve(), two.solve()
+    r1, r2 = one.solve()[0], two.solve()[0]
+    assert r1["kkt"] == r2["kkt"] and r1["iters"] == r2["iters"]
     for which in (pd.SOL_CURRENT, pd.SOL_AVERAGE):
         for a, b in zip(one.solution(which=which), two.solution(which=which)):
             assert np.array_equal(a, b)

@@ -17,9 +17,10 @@
 // entry in FP32 instead of 8, 10 instead of 12 in FP64.
 //
 // 256 blocks (one per CU) measured best at 31M nonzeros (us, 256 / 512 / 1,024:
-// 36 / 40 / 56): more blocks load the vector more often.  2^lg lanes per row such that a lane has 2 to 4
-// quads (tile_lg()).  Measured, us per sweep (row bins / here): FP32, 50,000
-// rows over 125,000 columns, 31M nonzeros 190 / 52; its transpose 195 / 46.
+// 36 / 40 / 56): more blocks load the vector more often.  2^lg lanes per row such
+// that a lane has 2 to 4 quads (tile_lg()).  Measured, us per sweep (row bins /
+// here): FP32, 50,000 rows over 125,000 columns, 31M nonzeros 190 / 52; its
+// transpose 195 / 46.
 #include <hip/hip_runtime.h>
 
 #include "kernels.h"

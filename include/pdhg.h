@@ -320,9 +320,11 @@ int pdhg_setup(const pdhg_lp *lp, int32_t batch, const pdhg_opts *o, void *ws, s
  * the fixed array and pdhg_solve copies them out after each chunk, which ends
  * its overlap of chunks).  Same arguments, results and errors as pdhg_setup
  * without ws / ws_bytes; the device is the calling thread's current device and
- * `stream` (NULL: the null stream) must belong to it.  Errors besides
- * pdhg_setup's: PDHG_ERR_NOMEM when pdhg_workspace_bytes plus the done flags
- * exceed PDHG_NOALLOC_MAX_BYTES; PDHG_ERR_STATE while a handle from this call
+ * `stream` (NULL: the null stream) must belong to it.  An LP that fits only
+ * without the sweeps' second layouts is set up without them: its sums are then
+ * taken in another order.  Errors besides pdhg_setup's: PDHG_ERR_NOMEM when the
+ * workspace without those layouts plus the done flags exceed
+ * PDHG_NOALLOC_MAX_BYTES; PDHG_ERR_STATE while a handle from this call
  * is still live on the device (one at a time per device: the array keeps the
  * last handle's contents; pdhg_destroy frees it for the next call).  Calls
  * that overlap on one device (a second thread setting up while the first

@@ -409,10 +409,12 @@ int pdhg_kkt(pdhg_handle *h, int32_t inst, const double *x, const double *y, int
  * gx = dL/dx_K and gy = dL/dy_K (original variables, concatenated over the
  * batch, y parts in caller row order), writes dL/dc, dL/drhs, dL/dl, dL/du,
  * dL/dx_0 and dL/dy_0 in the original variables (tau, sigma and the Ruiz
- * factors are constants).  Output pointers may be NULL.  Steps before the last
- * 4 * unroll_checkpoint ones (whose clip masks are kept as they run) are run
- * again from the checkpoints stored every unroll_checkpoint steps.  PDHG_ERR_STATE when no
- * recording pdhg_iterate ran since setup or since the last pdhg_set_data
+ * factors are constants).  Output pointers may be NULL.  The clip masks of the
+ * last steps (from a checkpoint on, at most 4 * unroll_checkpoint steps) are
+ * kept as they run; the steps before them are run again, with the sums they
+ * had, from the checkpoints stored every unroll_checkpoint steps.
+ * PDHG_ERR_STATE when no recording pdhg_iterate ran since setup or since the
+ * last pdhg_set_data
  * (the tape would replay against other data); pdhg_info.record_generation
  * tells a caller whether a later recording call replaced its tape. */
 int pdhg_backward(pdhg_handle *h, const double *gx, const double *gy, double *gc, double *grhs,

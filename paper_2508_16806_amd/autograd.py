@@ -5,8 +5,8 @@ PDHGUnroll.apply(solver, K, c, rhs, l, u, x0, y0) -> (x_K, y_K)
 Forward: installs (c, rhs, l, u) in the handle (pdhg_set_data), starts every
 instance at (x0, y0) (pdhg_set_state), and runs K recorded fixed-step
 iterations (pdhg_iterate with record = 1: checkpoints every
-opts.unroll_checkpoint steps, and the clip masks of the last 4 times as many
-steps).  Backward: pdhg_backward replays the checkpoint segments whose masks
+opts.unroll_checkpoint steps, and the clip masks of at most the last 4 times as
+many steps).  Backward: pdhg_backward replays the checkpoint segments whose masks
 are not held and runs the reverse steps on the GPU.
 A handle keeps one tape: backward raises PDHGError (PDHG_ERR_STATE) when a
 later forward call or set_data on the same handle has replaced it.

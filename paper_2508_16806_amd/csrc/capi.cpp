@@ -1928,17 +1928,8 @@ static void enqueue_active(const pdhg_handle *h, const Dev &d, hipStream_t s, in
         launch_act_tile(d, h->buf.tile[1], h->buf.tile[0], s);
 }
 
-// where the masks of recorded step t lie, counting from a step whose masks start
-// a byte: C bytes a row, so MASK_PACK * C steps
-static Mask mask_x(const pdhg_handle *h, int64_t t)
-{
-    return Mask{h->buf.maskx + t / MASK_PACK * h->d.N, (int)(2 * (t % MASK_PACK))};
-}
-
-static Mask mask_y(const pdhg_handle *h, int64_t t)
-{
-    return Mask{h->buf.masky + t / (2 * MASK_PACK) * h->d.M, (int)(t % (2 * MASK_PACK))};
-}
+// the handle's mask buffers: C bytes a row, so the masks of MASK_PACK * C steps
+static Masks masks_of(const pdhg_handle *h) { return Masks{h->buf.maskx, h->buf.masky, h->d.N, h->d.M}; }
 
 // fixed-step iterations j0 .. j0 + count - 1 of a check period
 template <typename T>
@@ -1951,6 +1942,22 @@ static void enqueue_steps(const pdhg_handle *h, const Dev &d, int j0, int count,
     for (int j = j0; j < j0 + count; ++j) {
         enqueue_primal<T>(h, d, j, avg, Mask{}, s);
         enqueue_dual<T>(h, d, j, avg, Mask{}, s);
+    }
+}
+
+// steps t0 .. t0 + count - 1 of the mask buffers, their clips stored: the sums, and
+// so the points, of enqueue_steps
+template <typename T>
+static void enqueue_masked(const pdhg_handle *h, const Dev &d, int64_t t0, int count, hipStream_t s)
+{
+    const Masks masks = masks_of(h);
+    if (h->sz.small) {
+        launch_small_masked<T>(d, h->buf.small, masks, t0, count, s);
+        return;
+    }
+    for (int64_t t = t0; t < t0 + count; ++t) {
+        enqueue_primal<T>(h, d, (int)(t & 1), 0, masks.x(t), s);
+        enqueue_dual<T>(h, d, (int)(t & 1), 0, masks.y(t), s);
     }
 }
 
@@ -2179,10 +2186,9 @@ static int iterate_impl(pdhg_handle *h, int64_t k, int32_t record, hipStream_t s
     // The masks of the last steps, as many as there is room for from a
     // checkpoint on, are stored now: the reverse steps then need no second run
     // of that part (42 of a step's 130 us on 8 dispatch LPs of 1.5M nonzeros;
-    // the mask bits cost a recorded step 1 us).  Small LPs take all steps of a
-    // segment in one launch that keeps no masks.
-    const int64_t hold = h->sz.small ? 0 : MASK_PACK * C;
-    const int64_t m0 = !record || hold == 0 ? k : (std::max<int64_t>(0, k - hold) + C - 1) / C * C;
+    // the mask bits cost a recorded step 1 us).
+    const int64_t hold = MASK_PACK * C;
+    const int64_t m0 = !record ? k : (std::max<int64_t>(0, k - hold) + C - 1) / C * C;
     if (record) h->rec_mask = INT64_MAX;
     // steps up to the next checkpoint, in launches of a bounded length
     int run = 1;
@@ -2194,14 +2200,10 @@ static int iterate_impl(pdhg_handle *h, int64_t k, int32_t record, hipStream_t s
         }
         run = (int)std::min<int64_t>(SMALL_STEPS, k - t);
         if (record) run = (int)std::min<int64_t>(run, C - t % C);
-        if (t < m0) {
+        if (t < m0)
             enqueue_steps<T>(h, d, 0, run, 0, s);
-            continue;
-        }
-        for (int64_t i = t; i < t + run; ++i) {
-            enqueue_primal<T>(h, d, (int)(i & 1), 0, mask_x(h, i - m0), s);
-            enqueue_dual<T>(h, d, (int)(i & 1), 0, mask_y(h, i - m0), s);
-        }
+        else
+            enqueue_masked<T>(h, d, t - m0, run, s);
     }
     HIPCHK(hipGetLastError());
     if (record) {
@@ -2243,11 +2245,12 @@ static int backward_impl(pdhg_handle *h, const double *gx, const double *gy, dou
     HIPCHK(hipMemcpyAsync(by, d.y, M * es, hipMemcpyDeviceToDevice, s));
     launch_adj_init(d, a, gxd, gyd, s);
     // reverse steps t1 - 1 .. t0, whose masks are held from step t0 on
+    const Masks masks = masks_of(h);
     auto reverse = [&](int64_t t0, int64_t t1) {
-        launch_adj_w(d, a, mask_y(h, t1 - 1 - t0), s);
+        launch_adj_w(d, a, masks.y(t1 - 1 - t0), s);
         for (int64_t t = t1 - 1; t >= t0; --t) {
-            launch_rev_primal<T>(d, a, mask_x(h, t - t0), s);
-            launch_rev_dual<T>(d, a, t > t0 ? mask_y(h, t - 1 - t0) : Mask{}, s);
+            launch_rev_primal<T>(d, a, masks.x(t - t0), s);
+            launch_rev_dual<T>(d, a, t > t0 ? masks.y(t - 1 - t0) : Mask{}, s);
         }
     };
     const int64_t m0 = std::min(h->rec_mask, K);
@@ -2257,10 +2260,7 @@ static int backward_impl(pdhg_handle *h, const double *gx, const double *gy, dou
         const int64_t t1 = std::min(m0, (sg + 1) * C);
         HIPCHK(hipMemcpyAsync(d.x, (char *)b.ckx + sg * N * es, N * es, hipMemcpyDeviceToDevice, s));
         HIPCHK(hipMemcpyAsync(d.y, (char *)b.cky + sg * M * es, M * es, hipMemcpyDeviceToDevice, s));
-        for (int64_t t = sg * C; t < t1; ++t) {
-            enqueue_primal<T>(h, d, 0, 0, mask_x(h, t - sg * C), s);
-            enqueue_dual<T>(h, d, 0, 0, mask_y(h, t - sg * C), s);
-        }
+        enqueue_masked<T>(h, d, 0, (int)(t1 - sg * C), s);
         reverse(sg * C, t1);
     }
     HIPCHK(hipMemcpyAsync(d.x, bx, N * es, hipMemcpyDeviceToDevice, s));

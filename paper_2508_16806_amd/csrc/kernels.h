@@ -30,6 +30,8 @@ void launch_spread_build(const OpDev &op, const SpreadOp &so, hipStream_t s);
 template <typename T>
 void launch_small(const Dev &d, const SmallDev &sd, int j0, int count, int avg, hipStream_t s);
 template <typename T>
+void launch_small_masked(const Dev &d, const SmallDev &sd, const Masks &masks, int64_t t0, int count, hipStream_t s);
+template <typename T>
 void launch_small_fill(const Dev &d, const SmallDev &sd, hipStream_t s);
 hipError_t small_prepare(uint32_t lds_bytes);
 template <typename T>

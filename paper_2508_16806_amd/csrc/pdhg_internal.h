@@ -308,4 +308,12 @@ struct Mask {
 };
 constexpr int MASK_PACK = 4; // recorded steps whose masks lie in one byte of a column
 
+// Mask bytes of consecutive steps, N / M a byte of steps; step 0 starts a byte.
+struct Masks {
+    uint8_t *px = nullptr, *py = nullptr;
+    int64_t N = 0, M = 0;
+    __host__ __device__ Mask x(int64_t t) const { return Mask{px + t / MASK_PACK * N, (int)(2 * (t % MASK_PACK))}; }
+    __host__ __device__ Mask y(int64_t t) const { return Mask{py + t / (2 * MASK_PACK) * M, (int)(t % (2 * MASK_PACK))}; }
+};
+
 }  // namespace pdhg

@@ -155,9 +155,11 @@ __device__ __forceinline__ X *lds_copy(X *&at, const X *src, int cnt)
     return to;
 }
 
-// LV: 1 K^T in LDS, 2 K too, 3 the updates' operands too
-template <typename T, bool AVG, int LV>
-__device__ void small_run(const Dev &d, const SmallDev &sd, const InstInfo &in, const SmallInst &si, int j0, int count)
+// LV: 1 K^T in LDS, 2 K too, 3 the updates' operands too.  MASK: the clips of step
+// j go to masks.x / y(j0 + j); the lane that owns a row adds all of its bits.
+template <typename T, bool AVG, bool MASK, int LV>
+__device__ void small_run(const Dev &d, const SmallDev &sd, const InstInfo &in, const SmallInst &si, int j0, int count,
+                          const Masks &masks)
 {
     extern __shared__ __align__(16) unsigned char lds[];
     const int n = in.n, m = in.m, m1 = in.m1, tid = threadIdx.x;
@@ -200,6 +202,7 @@ __device__ void small_run(const Dev &d, const SmallDev &sd, const InstInfo &in, 
     __syncthreads();
     for (int j = 0; j < count; ++j) {
         const double w = AVG ? wt[j] : 0.0;
+        const Mask mx = MASK ? masks.x(j0 + j) : Mask{}, my = MASK ? masks.y(j0 + j) : Mask{};
         small_sweep<T>(
             oT, y, [&](int r) -> PreX<T> { return {x[r], c[r], l[r], u[r], AVG ? xa[r] : T(0), AVG ? x0[r] : T(0)}; },
             [&](int r, double g, const PreX<T> &p) {
@@ -207,6 +210,7 @@ __device__ void small_run(const Dev &d, const SmallDev &sd, const InstInfo &in, 
                 x[r] = s.x;
                 xb[r] = s.xbar;
                 if (AVG) xa[r] = average_step<T>(p.xa, s.x, p.x0, w);
+                if (MASK) mask_put(mx.p, in.xoff + r, mx.sh, s.clip);
             });
         __syncthreads();
         small_sweep<T>(
@@ -215,6 +219,7 @@ __device__ void small_run(const Dev &d, const SmallDev &sd, const InstInfo &in, 
                 const DualStep<T> s = dual_step<T>(p.y, a, p.q, sigma, r < m1);
                 y[r] = s.y;
                 if (AVG) ya[r] = average_step<T>(p.ya, s.y, p.y0, w);
+                if (MASK) mask_put(my.p, in.yoff + r, my.sh, s.pass);
             });
         __syncthreads();
     }
@@ -236,18 +241,18 @@ __device__ void small_run(const Dev &d, const SmallDev &sd, const InstInfo &in, 
 }
 
 // Iterations j0 .. j0 + count - 1 (1 <= count <= SMALL_STEPS) of the current
-// check period, one workgroup per instance.
-template <typename T, bool AVG>
-__global__ __launch_bounds__(SMALL_WG) void k_small(Dev d, SmallDev sd, int j0, int count)
+// check period (MASK: of the steps of `masks`), one workgroup per instance.
+template <typename T, bool AVG, bool MASK>
+__global__ __launch_bounds__(SMALL_WG) void k_small(Dev d, SmallDev sd, int j0, int count, Masks masks)
 {
     const SmallInst si = sd.inst[blockIdx.x];
     if (d.st[blockIdx.x].done) return;
     const InstInfo in = d.info[blockIdx.x];
     switch (si.level) {
-        case 0: small_run<T, AVG, 0>(d, sd, in, si, j0, count); break;
-        case 1: small_run<T, AVG, 1>(d, sd, in, si, j0, count); break;
-        case 2: small_run<T, AVG, 2>(d, sd, in, si, j0, count); break;
-        default: small_run<T, AVG, 3>(d, sd, in, si, j0, count); break;
+        case 0: small_run<T, AVG, MASK, 0>(d, sd, in, si, j0, count, masks); break;
+        case 1: small_run<T, AVG, MASK, 1>(d, sd, in, si, j0, count, masks); break;
+        case 2: small_run<T, AVG, MASK, 2>(d, sd, in, si, j0, count, masks); break;
+        default: small_run<T, AVG, MASK, 3>(d, sd, in, si, j0, count, masks); break;
     }
 }
 
@@ -276,9 +281,19 @@ void launch_small(const Dev &d, const SmallDev &sd, int j0, int count, int avg, 
     for (int j = 0; j < count; j += SMALL_STEPS) {
         const int k = count - j < SMALL_STEPS ? count - j : SMALL_STEPS;
         if (avg)
-            hipLaunchKernelGGL((k_small<T, true>), dim3(d.batch), dim3(SMALL_WG), sd.lds, s, d, sd, j0 + j, k);
+            hipLaunchKernelGGL((k_small<T, true, false>), dim3(d.batch), dim3(SMALL_WG), sd.lds, s, d, sd, j0 + j, k, Masks{});
         else
-            hipLaunchKernelGGL((k_small<T, false>), dim3(d.batch), dim3(SMALL_WG), sd.lds, s, d, sd, j0 + j, k);
+            hipLaunchKernelGGL((k_small<T, false, false>), dim3(d.batch), dim3(SMALL_WG), sd.lds, s, d, sd, j0 + j, k, Masks{});
+    }
+}
+
+// Steps t0 .. t0 + count - 1 of `masks`, which receives their clips.
+template <typename T>
+void launch_small_masked(const Dev &d, const SmallDev &sd, const Masks &masks, int64_t t0, int count, hipStream_t s)
+{
+    for (int j = 0; j < count; j += SMALL_STEPS) {
+        const int k = count - j < SMALL_STEPS ? count - j : SMALL_STEPS;
+        hipLaunchKernelGGL((k_small<T, false, true>), dim3(d.batch), dim3(SMALL_WG), sd.lds, s, d, sd, (int)t0 + j, k, masks);
     }
 }
 
@@ -293,8 +308,9 @@ void launch_small_fill(const Dev &d, const SmallDev &sd, hipStream_t s)
 // lets the kernels take lds_bytes of dynamic LDS on the current device
 hipError_t small_prepare(uint32_t lds_bytes)
 {
-    const void *k[4] = {(const void *)k_small<float, true>, (const void *)k_small<float, false>,
-                        (const void *)k_small<double, true>, (const void *)k_small<double, false>};
+    const void *k[6] = {(const void *)k_small<float, true, false>,  (const void *)k_small<float, false, false>,
+                        (const void *)k_small<float, false, true>,  (const void *)k_small<double, true, false>,
+                        (const void *)k_small<double, false, false>, (const void *)k_small<double, false, true>};
     for (const void *f : k) {
         const hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes);
         if (e != hipSuccess) return e;
@@ -302,8 +318,9 @@ hipError_t small_prepare(uint32_t lds_bytes)
     return hipSuccess;
 }
 
-#define SMALL_INST(T)                                                                          \
+#define SMALL_INST(T)                                                                                              \
     template void launch_small<T>(const Dev &, const SmallDev &, int, int, int, hipStream_t); \
+    template void launch_small_masked<T>(const Dev &, const SmallDev &, const Masks &, int64_t, int, hipStream_t); \
     template void launch_small_fill<T>(const Dev &, const SmallDev &, hipStream_t);
 SMALL_INST(float)
 SMALL_INST(double)

@@ -408,7 +408,9 @@ static void plan_tile(int64_t es, InstPlan &p)
 // many lanes (a power of two) as keep its entries per lane within `cap`, at
 // most its lanes in tile.hip and at least a quarter of them (a lane adds up
 // to 4 of their partial sums).  cap starts at 16 and halves while each task
-// still has a wavefront of its own.  Entries go to the lanes by fours.
+// still has a wavefront of its own.  Entries go to the lanes by fours; what is
+// missing in a shorter row is a zero times the row's own first column, and rows
+// without entries have tasks of their own, so that no row gathers another's.
 static void small_rows_layout(const std::vector<int32_t> &len, const std::vector<int32_t> &sweep, int o, SmallPlan &sp)
 {
     const int nr = (int)len.size();
@@ -430,7 +432,9 @@ static void small_rows_layout(const std::vector<int32_t> &len, const std::vector
         for (int k = 0; k < nr; ++cnt) {
             const int l = lanes_log2(ord[k], cap), most = 64 >> l;
             int g = 0;
-            while (k + g < nr && g < most && lanes_log2(ord[k + g], cap) == l && sweep[ord[k + g]] == sweep[ord[k]]) ++g;
+            while (k + g < nr && g < most && lanes_log2(ord[k + g], cap) == l && sweep[ord[k + g]] == sweep[ord[k]] &&
+                   (len[ord[k + g]] > 0) == (len[ord[k]] > 0))
+                ++g;
             f(k, g, l);
             k += g;
         }

@@ -1531,7 +1531,7 @@ static int device_setup(pdhg_handle *h, hipStream_t s)
     launch_scale_vals(d.Kt, h->buf.Ktv64, h->buf.Ktv32, false, d.kap, d.rho, s);
     launch_scale_data<T>(d, s);
     if (h->sz.small) {
-        HIPCHK(small_prepare(h->buf.small.lds));
+        HIPCHK(small_prepare());
         launch_small_fill<T>(d, h->buf.small, s);
     }
     for (int op = 0; op < 2; ++op)

@@ -33,7 +33,7 @@ template <typename T>
 void launch_small_masked(const Dev &d, const SmallDev &sd, const Masks &masks, int64_t t0, int count, hipStream_t s);
 template <typename T>
 void launch_small_fill(const Dev &d, const SmallDev &sd, hipStream_t s);
-hipError_t small_prepare(uint32_t lds_bytes);
+hipError_t small_prepare();
 template <typename T>
 void launch_primal_ad(const Dev &d, hipStream_t s);
 template <typename T>

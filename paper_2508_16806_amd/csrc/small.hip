@@ -305,14 +305,15 @@ void launch_small_fill(const Dev &d, const SmallDev &sd, hipStream_t s)
                            sd.src[o], (T *)sd.val[o], sd.col[o]);
 }
 
-// lets the kernels take lds_bytes of dynamic LDS on the current device
-hipError_t small_prepare(uint32_t lds_bytes)
+// lets the kernels take a CU's whole LDS on the current device (the limit is the
+// kernel's, not a handle's: the same for handles of all sizes)
+hipError_t small_prepare()
 {
     const void *k[6] = {(const void *)k_small<float, true, false>,  (const void *)k_small<float, false, false>,
                         (const void *)k_small<float, false, true>,  (const void *)k_small<double, true, false>,
                         (const void *)k_small<double, false, false>, (const void *)k_small<double, false, true>};
     for (const void *f : k) {
-        const hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes);
+        const hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)SMALL_LDS);
         if (e != hipSuccess) return e;
     }
     return hipSuccess;

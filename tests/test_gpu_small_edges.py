@@ -1,5 +1,5 @@
 """Small LPs (small.hip) at the edges: rows without entries beside infinite
-iterates."""
+iterates, handles of different LDS sizes side by side."""
 import numpy as np
 import pytest
 
@@ -35,3 +35,25 @@ def test_empty_rows_ignore_the_others(prec):
         got.append((x[cols], y[rows]))
     for a, b in zip(*got):
         np.testing.assert_array_equal(a, b)
+
+
+@pytest.mark.parametrize("prec", ["f32", "f64"])
+def test_a_smaller_handle_beside_a_larger_one(prec):
+    """A handle whose LP fills most of the LDS launches as before after one with
+    a tiny LP was set up, with and without recorded launches (graphs)."""
+    import paper_2508_16806_amd as pd
+
+    lp = lpgen.planted(1003, 2501, 0.005, 6, ge_frac=0.5)
+    for graph in (0, 1):
+        kw = dict(precision=prec, max_iters=128, use_graph=graph, unroll_capacity=8, unroll_checkpoint=2)
+        a = pd.Solver(lp, **kw)
+        a.solve()
+        want = a.solution()
+        a = pd.Solver(lp, **kw)
+        b = pd.Solver(lpgen.tiny(3, n=5, m=3), **kw)
+        b.solve()
+        a.solve()
+        for u, v in zip(a.solution(), want):
+            np.testing.assert_array_equal(u, v)
+        a.iterate(8, record=True)
+        assert np.isfinite(a.backward(np.ones(lp.n), np.ones(lp.m))["c"]).all()

@@ -234,24 +234,14 @@ struct Bins {
     int32_t code[NBIN];  // lanes_log2 | rows_log2 << 4
 };
 
-// lim: row-length limits; rows: rows per lane group (1, 2, 4; only for bins
-// of at most 16 lanes).  The default gives a lane 5..8 entries of a row, two
-// quads: a lane's second quad costs one load's issue, twice the lanes cost a
-// row another shuffle stage and its share of the per-row work twice the waves.
-// Primal / dual / check us with the limits 4 * 2^k, 8 * 2^k and 16 * 2^k:
-//   dispatch LP, 15.2M nonzeros (124 a row): 38.5 / 26 / 218, 30 / 26 / 151,
-//     30 / 26 / 118;  its quarter: 11.1 / 10.9 / 58, 10.3 / 10.6 / 48,
-//     11.4 / 11 / 47
-//   Zipf rows, 54M nonzeros: 395 / 573 / 3640, 363 / 573 / 2880,
-//     396 / 575 / 2970;  its tenth: 24.6 / 31.9 / 158, 21.8 / 31.7 / 107,
-//     26 / 31.7 / 116
-static Bins make_bins(const int32_t *lim, const int32_t *rows)
+// lim: row-length limits (0: the default f * 2^k, k = 0 .. 5, and 512); rows: rows
+// per lane group (1, 2, 4; only for bins of at most 16 lanes).
+static Bins make_bins(const int32_t *lim, const int32_t *rows, int f)
 {
-    static const int32_t def_len[NBIN] = {8, 16, 32, 64, 128, 256, 512, INT32_MAX};
     static const int32_t lanes[NBIN] = {0, 1, 2, 3, 4, 5, 6, 8};
     Bins b;
     for (int k = 0; k < NBIN; ++k) {
-        b.max_len[k] = (lim && lim[k] > 0) ? lim[k] : def_len[k];
+        b.max_len[k] = (lim && lim[k] > 0) ? lim[k] : (k < 6 ? f << k : 512);
         if (k > 0 && b.max_len[k] < b.max_len[k - 1]) b.max_len[k] = b.max_len[k - 1];
         int rl = 0;
         if (rows && k <= 4) rl = rows[k] >= 4 ? 2 : (rows[k] >= 2 ? 1 : 0);
@@ -259,6 +249,39 @@ static Bins make_bins(const int32_t *lim, const int32_t *rows)
     }
     b.max_len[NBIN - 1] = INT32_MAX;
     return b;
+}
+
+// The default limits of an operator whose rows have lengths len(0 .. rows - 1).
+// 8 * 2^k gives a lane 5..8 entries of a row, two quads: a lane's second quad costs
+// one load's issue, twice the lanes cost a row another shuffle stage and its share
+// of the per-row work twice the waves.  Primal / dual / check us with the limits
+// 4 * 2^k, 8 * 2^k and 16 * 2^k:
+//   dispatch LP, 15.2M nonzeros (124 a row): 38.5 / 26 / 218, 30 / 26 / 151,
+//     30 / 26 / 118;  its quarter: 11.1 / 10.9 / 58, 10.3 / 10.6 / 48,
+//     11.4 / 11 / 47
+//   Zipf rows, 54M nonzeros: 395 / 573 / 3640, 363 / 573 / 2880,
+//     396 / 575 / 2970;  its tenth: 24.6 / 31.9 / 158, 21.8 / 31.7 / 107,
+//     26 / 31.7 / 116
+// 4 * 2^k halves a row's chain of loads, which is what a sweep costs while the chip
+// has lanes to spare: adaptive primal + dual sweep with 4 * 2^k and 8 * 2^k, random
+// LPs of 12k nonzeros 12.3 / 16.6, 50k 10.7 / 12.5, 250k 12.2 / 13.9, 0.5M 13.2 / 15.4,
+// 0.8M 12.8 / 13.7, 1.0M 15.2 / 15.6, 2.0M 26.6 / 24.8.  The two differ in the lanes
+// of rows of 5 to 256 entries only: where these hold less than half of the entries,
+// 8 * 2^k everywhere (60,000 rows of 2 entries 5.4 / 4.7 and 5.6 / 5.6).  Sliced
+// rows are gathered a piece at a time and take 4 * 2^k: 4 / 2 slices on 5.3M
+// nonzeros 22.2 / 27.1 us primal, on 1.1M dual 21.8 / 22.8.
+constexpr int64_t SHORT_CHAIN_NNZ = 1000000;
+template <typename F>
+static int default_limits(int64_t nnz, int S, int64_t rows, F &&len)
+{
+    if (S > 1) return 4;
+    if (nnz >= SHORT_CHAIN_NNZ) return 8;
+    int64_t in = 0;
+    for (int64_t r = 0; r < rows; ++r) {
+        const int64_t l = len(r);
+        if (l > 4 && l <= 256) in += l;
+    }
+    return 2 * in >= nnz ? 4 : 8;
 }
 
 static int bin_of(const Bins &b, int64_t len)
@@ -275,12 +298,15 @@ static int seg_group(int code)
     return (lanes_log2 >= 8 ? 1 : (WG >> lanes_log2)) << rows_log2;
 }
 
-static void plan_instance(const HostLP &h, const Bins &bins, const Bins &tbins, int S, int St, InstPlan &p)
+static void plan_instance(const HostLP &h, const pdhg_opts &o, InstPlan &p)
 {
+    const int S = o.col_slices, St = o.col_slices_t;
     p.n = h.n;
     p.m = h.m;
     p.m1 = h.m1;
     p.nnz = h.nnz;
+    const Bins bins = make_bins(o.bin_len_dual, o.bin_rows_dual,
+                                default_limits(h.nnz, S, h.m, [&](int64_t i) { return h.rp[i + 1] - h.rp[i]; }));
     // rows: ">=" group then "=" group, each split into whole rows and rows
     // swept in S column slices (binned by their per-slice length), each
     // ordered by bin, stable
@@ -308,6 +334,8 @@ static void plan_instance(const HostLP &h, const Bins &bins, const Bins &tbins, 
     // their per-slice count), each ordered by bin of their entry count, stable
     std::vector<int64_t> cnt(h.n, 0);
     for (int64_t k = 0; k < h.nnz; ++k) cnt[h.ci[k]]++;
+    const Bins tbins = make_bins(o.bin_len_primal, o.bin_rows_primal,
+                                 default_limits(h.nnz, St, h.n, [&](int64_t j) { return cnt[j]; }));
     // how many neighbouring entries of a row (of a column) share a line of the
     // gathered vector, on four stretches of consecutive rows
     constexpr int64_t STRETCH = 65536;
@@ -1040,8 +1068,6 @@ static int plan_all(const pdhg_lp *lp, int32_t batch, const pdhg_opts *o, std::v
     if (rc) return rc;
     hosts.resize(batch);
     plans.resize(batch);
-    const Bins bins = make_bins(o->bin_len_dual, o->bin_rows_dual);
-    const Bins tbins = make_bins(o->bin_len_primal, o->bin_rows_primal);
     sz = Sizes{};
     sz.batch = batch;
     // validation and binning of each instance: on host threads, one
@@ -1058,7 +1084,7 @@ static int plan_all(const pdhg_lp *lp, int32_t batch, const pdhg_opts *o, std::v
                 msgs[b] = g_err;  // the message is per thread
                 return;
             }
-            plan_instance(hosts[b], bins, tbins, o->col_slices, o->col_slices_t, plans[b]);
+            plan_instance(hosts[b], *o, plans[b]);
             if (layouts) {
                 plan_tile((int64_t)elem_size(o->precision), plans[b]);
                 plan_small(hosts[b], (int64_t)elem_size(o->precision), plans[b]);

@@ -1175,6 +1175,33 @@ static int h2d(X *dst, const X *src, size_t cnt, hipStream_t s)
     return PDHG_OK;
 }
 
+// Workgroups of a sweep over a tiled operator: the blocks that can run at once, so
+// that a batch that runs a few instances at a time launches no idle ones (128
+// iterations of each of 24 LPs of 60k to 150k nonzeros, one after another: 26.4 ms
+// with the whole batch's blocks in each launch and the lists written by one lane per
+// instance, 24.9 ms so).  The admission budget holds the running instances'
+// bytes; the bound takes the instances with most blocks per byte, the last one whole.
+static int32_t tile_grid(const pdhg_handle *h, const std::vector<int2> &inst, int32_t nblk)
+{
+    if (h->batch == 1 || h->opts.batch_resident_bytes <= 0) return std::min(nblk, TILE_GRID);
+    auto blocks = [&](int b) { return (int64_t)(inst[b].y - inst[b].x); };
+    auto bytes = [&](int b) { return h->info[b].sweep_bytes; };
+    std::vector<int> ord(h->batch);
+    for (int b = 0; b < h->batch; ++b) ord[b] = b;
+    std::sort(ord.begin(), ord.end(), [&](int a, int b) {
+        const double ka = (double)blocks(a) * (double)bytes(b), kb = (double)blocks(b) * (double)bytes(a);
+        return ka != kb ? ka > kb : a < b;
+    });
+    int64_t most = 1, sum = 0, left = h->opts.batch_resident_bytes;
+    for (int b : ord) {
+        most = std::max(most, blocks(b));
+        if (left <= 0) continue;
+        sum += blocks(b);
+        left -= bytes(b);
+    }
+    return (int32_t)std::min<int64_t>({std::max(most, sum), nblk, TILE_GRID});
+}
+
 // builds the host images of both operators and all vectors, then uploads
 static int upload(pdhg_handle *h, std::vector<HostLP> &hosts, const TileBlocks &tiles, hipStream_t s)
 {
@@ -1491,6 +1518,7 @@ static int upload(pdhg_handle *h, std::vector<HostLP> &hosts, const TileBlocks &
         // FP32 on 256 blocks: 90 fours a block 5.4 / 5.7 / 4.1, 250 5.1 / 6.4 / 5.5 and
         // 5.3 / 5.8 / 4.7, 900 6.5 / 5.7 / 5.6, 1,200 8.3 / 6.2 / 8.5.
         b.tile[op].direct = sz.tile_q[op] < 1000 * sz.tile_blk[op];
+        b.tile[op].grid = tile_grid(h, tiles.inst[op], t.nblk);
         int32_t widest = 0;
         for (const TileBlk &k : tiles.blk[op]) widest = std::max(widest, k.width);
         b.tile[op].lds = TILE_LDS - TILE_BYTES;

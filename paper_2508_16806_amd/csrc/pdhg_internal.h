@@ -248,7 +248,7 @@ constexpr int TILE_LDS = TILE_BYTES + 8 * TILE_ROWS + 4 * (TILE_ROWS + 4);  // o
 constexpr int TILE_SPLIT = 8;                  // tiles of an operator at most
 constexpr int TILE_SEGS = 10240;               // rows x tiles of a block at most
 constexpr int TILE_BLOCKS = 256;               // blocks of a lone LP's operator (one per CU)
-constexpr int TILE_GRID = 4096;                // workgroups of a launch at most
+constexpr int TILE_GRID = 4096;                // workgroups of a launch at most (tile_grid())
 struct TileBlk {
     int64_t sp0;        // first quad range in sp (tile by tile, row by row; relative to q0)
     int64_t q0;         // first quad
@@ -262,6 +262,7 @@ struct TileBlk {
 };
 struct TileOp {
     int32_t nblk;       // 0: no instance's operator is tiled
+    int32_t grid;       // workgroups of a launch
     int32_t direct;     // gathers from global memory, 256 lanes a workgroup (few entries per block)
     int32_t lds;        // dynamic LDS of a workgroup
     const TileBlk *blk;

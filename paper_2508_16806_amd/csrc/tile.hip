@@ -216,14 +216,17 @@ __device__ __forceinline__ TileBlk tile_blk(const TileBlk *p)
 
 // f(block) for the blocks of the running instances
 template <typename F>
-__device__ __forceinline__ void tile_blocks(const TileOp &op, int cnt, F &&f)
+__device__ __forceinline__ void tile_blocks(const TileOp &op, const int32_t *cntp, F &&f)
 {
-    // the block is loaded beside the count: with every block active the list is
-    // the identity (the grid has at most nblk workgroups)
+    // the block and its list entry are loaded beside the count: with every block
+    // active the list is the identity (the grid has at most nblk workgroups)
     TileBlk b = tile_blk(op.blk + blockIdx.x);
+    int next = uniform_i(op.act[blockIdx.x]);
+    const int cnt = *cntp;
     const bool full = cnt == op.nblk;
     for (int it = blockIdx.x; it < cnt; it += gridDim.x) {
-        if (!full || it >= (int)gridDim.x) b = tile_blk(op.blk + uniform_i(full ? it : op.act[it]));
+        if (it >= (int)gridDim.x) next = uniform_i(op.act[it]);
+        if (!full || it >= (int)gridDim.x) b = tile_blk(op.blk + (full ? it : next));
         f(b);
         __syncthreads();
     }
@@ -239,7 +242,7 @@ __global__ __launch_bounds__(W) void k_primal_tile(Dev d, TileOp op, int j_in_ch
     const T *__restrict__ c = (const T *)d.c;
     const T *__restrict__ l = (const T *)d.l;
     const T *__restrict__ u = (const T *)d.u;
-    tile_blocks(op, d.act_cnt[3], [&](const TileBlk &b) {
+    tile_blocks(op, d.act_cnt + 3, [&](const TileBlk &b) {
         const InstState *st = d.st + b.inst;
         const double tau = st->tau;
         const double w = AVG ? 1.0 / (double)(st->t_inner + j_in_chunk + 1) : 0.0;
@@ -270,7 +273,7 @@ __global__ __launch_bounds__(W) void k_dual_tile(Dev d, TileOp op, int j_in_chun
     T *__restrict__ ya = (T *)d.yavg;
     const T *__restrict__ y0 = (const T *)d.y0;
     const T *__restrict__ q = (const T *)d.q;
-    tile_blocks(op, d.act_cnt[2], [&](const TileBlk &b) {
+    tile_blocks(op, d.act_cnt + 2, [&](const TileBlk &b) {
         const InstState *st = d.st + b.inst;
         const double sigma = st->sigma;
         const double w = AVG ? 1.0 / (double)(st->t_inner + j_in_chunk + 1) : 0.0;
@@ -387,11 +390,12 @@ __global__ __launch_bounds__(TILE_WG) void k_tile_build(OpDev op, TileOp to)
     }
 }
 
-// block lists of the running instances (one workgroup), for both operators
+// block lists of the running instances (one workgroup), for both operators: a
+// scan over the instances' block counts, then a wavefront per instance
 __global__ __launch_bounds__(TILE_WG) void k_act_tile(Dev d, TileOp K, TileOp Kt)
 {
-    __shared__ int32_t s[TILE_WG];
-    const int tid = threadIdx.x;
+    __shared__ int32_t s[TILE_WG], first[TILE_WG], num[TILE_WG];
+    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
     for (int o = 0; o < 2; ++o) {
         const TileOp &op = o == 0 ? K : Kt;
         if (op.nblk == 0) continue;
@@ -401,6 +405,8 @@ __global__ __launch_bounds__(TILE_WG) void k_act_tile(Dev d, TileOp K, TileOp Kt
             const int2 rg = b < d.batch ? op.inst[b] : make_int2(0, 0);
             const int n = b < d.batch && d.st[b].done == 0 ? rg.y - rg.x : 0;
             s[tid] = n;
+            first[tid] = rg.x;
+            num[tid] = n;
             __syncthreads();
             for (int off = 1; off < TILE_WG; off <<= 1) {
                 const int32_t a = tid >= off ? s[tid - off] : 0;
@@ -408,13 +414,12 @@ __global__ __launch_bounds__(TILE_WG) void k_act_tile(Dev d, TileOp K, TileOp Kt
                 s[tid] += a;
                 __syncthreads();
             }
-            const int32_t at = carry + s[tid] - n;
-            for (int k = 0; k < n; ++k) op.act[at + k] = rg.x + k;
+            for (int k = wave; k < min(TILE_WG, d.batch - b0); k += TILE_WG / 64)
+                for (int j = lane; j < num[k]; j += 64) op.act[carry + s[k] - num[k] + j] = first[k] + j;
             carry += s[TILE_WG - 1];
             __syncthreads();
         }
         if (tid == 0) d.act_cnt[2 + o] = carry;
-        __syncthreads();
     }
 }
 
@@ -423,7 +428,7 @@ __global__ __launch_bounds__(TILE_WG) void k_act_tile(Dev d, TileOp K, TileOp Kt
 template <int W, typename T>
 static void primal_tile(const Dev &d, const TileOp &op, int j, int avg, Mask mask, hipStream_t s)
 {
-    const dim3 g(op.nblk < TILE_GRID ? op.nblk : TILE_GRID), wg(W);
+    const dim3 g(op.grid), wg(W);
     if (mask.p)
         hipLaunchKernelGGL((k_primal_tile<W, T, 0, 1>), g, wg, op.lds, s, d, op, j, mask);
     else if (avg)
@@ -435,7 +440,7 @@ static void primal_tile(const Dev &d, const TileOp &op, int j, int avg, Mask mas
 template <int W, typename T>
 static void dual_tile(const Dev &d, const TileOp &op, int j, int avg, Mask mask, hipStream_t s)
 {
-    const dim3 g(op.nblk < TILE_GRID ? op.nblk : TILE_GRID), wg(W);
+    const dim3 g(op.grid), wg(W);
     if (mask.p)
         hipLaunchKernelGGL((k_dual_tile<W, T, 0, 1>), g, wg, op.lds, s, d, op, j, mask);
     else if (avg)

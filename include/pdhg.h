@@ -441,7 +441,11 @@ int pdhg_backward(pdhg_handle *h, const double *gx, const double *gy, double *gc
  * packet gets its proportional share of the unseparated total instead (so
  * every figure is positive).  The check,
  * control and restart kernels, which run once per check interval, are timed
- * back to back.  The sweeps advance the iterate (fixed steps); solver counters
+ * back to back.  On a handle of small LPs (PDHG_SWEEP_SMALL) a launch runs both
+ * sweeps of min(check_every, 256) iterations: ms_primal and ms_dual are each half
+ * of an iteration's time; ms_control includes the restart copies, which
+ * pdhg_solve leaves to it there (ms_restart is then a kernel that it does not
+ * launch).  The sweeps advance the iterate (fixed steps); solver counters
  * are restored.  1 <= reps <= 10000 (one event per launch is created),
  * else PDHG_ERR_INVALID_ARG.  Synchronous. */
 int pdhg_time_kernels(pdhg_handle *h, int32_t reps, pdhg_kernel_times *out, hipStream_t stream);

@@ -2077,9 +2077,9 @@ static void enqueue_chunk(const pdhg_handle *h, hipStream_t s)
             enqueue_steps<T>(h, d, 0, last + 1, avg, s);
         }
     }
-    const bool small = h->sz.small;
-    // the small instances' launches leave the average point ready
-    launch_check<T>(d, avg, s, !(small && !h->opts.adaptive_step), h->buf.spread);
+    // the small instances' launches of fixed steps leave the average point ready
+    const bool small = h->sz.small, folded = small && !h->opts.adaptive_step;
+    launch_check<T>(d, avg, s, !folded, h->buf.spread);
     // Algorithm 6 on the difference of the last step: the iterate before it is
     // in (xavg1, y1) with fixed steps, in buffer 1 (xbar, y1) with adaptive ones
     if (detect) launch_infeas<T>(d, h->opts.adaptive_step ? d.xbar : d.xavg1, d.y1, s);
@@ -2824,12 +2824,20 @@ static int time_impl(pdhg_handle *h, int32_t reps, pdhg_kernel_times *out, hipSt
         const double share = sep > 0.0 ? whole / sep : 1.0;
         for (int k = 0; k < nk; ++k) out[k] = std::max(out[k] / reps - excess, out[k] / reps * share);
     };
-    // the two sweeps alternate as in the iteration (each one finds the caches
-    // as the other leaves them)
-    time_seq(2, [&](int k, int r) {
-        if (k == 0) enqueue_primal<T>(h, d, r, avg, Mask{}, s);
-        else enqueue_dual<T>(h, d, r, avg, Mask{}, s);
-    }, ms);
+    const bool small = h->sz.small, folded = small && !h->opts.adaptive_step;
+    if (small) {
+        // many iterations of both sweeps in a launch: half of one's time each
+        const int n = std::min(h->opts.check_every, SMALL_STEPS);
+        time_seq(1, [&](int, int) { launch_small<T>(d, h->buf.small, 0, n, avg, s); }, ms);
+        ms[0] = ms[1] = ms[0] / (2.0 * n);
+    } else {
+        // the two sweeps alternate as in the iteration (each one finds the caches
+        // as the other leaves them)
+        time_seq(2, [&](int k, int r) {
+            if (k == 0) enqueue_primal<T>(h, d, r, avg, Mask{}, s);
+            else enqueue_dual<T>(h, d, r, avg, Mask{}, s);
+        }, ms);
+    }
     // once-per-chunk kernels, back to back, each on the path a check takes
     // when it restarts: the control kernel runs a whole check decision (a
     // check interval done, no stop: eps 0, no iteration limit, and the long
@@ -2854,8 +2862,8 @@ static int time_impl(pdhg_handle *h, int32_t reps, pdhg_kernel_times *out, hipSt
         (void)hipEventRecord(ev[0], s);
         for (int r = 0; r < reps; ++r) {
             switch (phase) {
-                case 2: launch_check<T>(d, avg, s, true, h->buf.spread); break;
-                case 3: launch_control<T>(d, Pr, h->opts.check_every, s); break;
+                case 2: launch_check<T>(d, avg, s, !folded, h->buf.spread); break;
+                case 3: launch_control<T>(d, Pr, h->opts.check_every, s, small); break;
                 default: launch_restart<T>(d, s); break;
             }
         }

@@ -132,15 +132,11 @@ __global__ __launch_bounds__(WG) void k_primal(Dev d, int j_in_chunk, uint8_t *_
                     if (r >= ps.nvalid) break;
                     const int64_t j = ps.row0 + r;
                     const double g = (SL == 2 && s.sliced) ? op.part[j] + acc[r][0] : acc[r][0];
-                    const double xo = (double)r_x[r], cj = (double)r_c[r], lo = (double)r_l[r];
-                    const double hi = (double)r_u[r], xav = (double)r_a[r];
-                    const double v = xo - tau * (cj - g);
-                    const double xn = v < lo ? lo : (v > hi ? hi : v);
-                    const T xnT = (T)xn;
-                    x[j] = xnT;
-                    xb[j] = (T)(2.0 * (double)xnT - xo);
-                    if (AVG) xa[j] = (T)(xav + (((double)xnT - (double)r_0[r]) - xav) * w);
-                    if (MASK) mask_put(mask, j, pass, v <= lo ? 1 : (v >= hi ? 2 : 0));
+                    const PrimalStep<T> p = primal_step<T>(r_x[r], g, r_c[r], r_l[r], r_u[r], tau);
+                    x[j] = p.x;
+                    xb[j] = p.xbar;
+                    if (AVG) xa[j] = average_step<T>(r_a[r], p.x, r_0[r], w);
+                    if (MASK) mask_put(mask, j, pass, p.clip);
                 }
             }
         });
@@ -195,13 +191,10 @@ __global__ __launch_bounds__(WG) void k_dual(Dev d, int j_in_chunk, uint8_t *__r
                     if (r >= ps.nvalid) break;
                     const int64_t i = ps.row0 + r;
                     const double a = (SL == 2 && s.sliced) ? op.part[i] + acc[r][0] : acc[r][0];
-                    const double yo = (double)r_y[r], qi = (double)r_q[r], yav = (double)r_a[r];
-                    const double wv = yo + sigma * (qi - a);
-                    const double yn = (ineq && wv < 0.0) ? 0.0 : wv;
-                    const T ynT = (T)yn;
-                    y[i] = ynT;
-                    if (AVG) ya[i] = (T)(yav + (((double)ynT - (double)r_0[r]) - yav) * w);
-                    if (MASK) mask_put(mask, i, pass, (!ineq || wv > 0.0) ? 1 : 0);
+                    const DualStep<T> p = dual_step<T>(r_y[r], a, r_q[r], sigma, ineq);
+                    y[i] = p.y;
+                    if (AVG) ya[i] = average_step<T>(r_a[r], p.y, r_0[r], w);
+                    if (MASK) mask_put(mask, i, pass, p.pass);
                 }
             }
         });

@@ -65,3 +65,35 @@ def test_masks_are_the_recorded_steps(name, C):
         out = r.backward(gx, gy)
         for key, want in (("c", gc), ("l", gl), ("x0", ax), ("y0", ay)):
             np.testing.assert_allclose(out[key], want, rtol=0, atol=1e-11 * (1 + np.abs(want).max()), err_msg=key)
+
+
+@pytest.mark.parametrize("C", [16, 2])
+def test_batch_equals_solo(C):
+    """Small, tiled and row-binned LPs with ties in one handle: points and gradients
+    of each as alone, bit for bit."""
+    import paper_2508_16806_amd as pd
+
+    parts = [_tied(*LPS[k], seed=5) for k in ("small", "tile", "rows", "tall")]
+    kw = dict(precision="f64", ruiz_iters=0, step_size=0.01, primal_weight=1.4, unroll_capacity=16, unroll_checkpoint=C)
+    rng = np.random.default_rng(2)
+    g = [(rng.standard_normal(lp.n), rng.standard_normal(lp.m)) for lp, _, _ in parts]
+
+    def adjoint(sel):
+        s = pd.Solver([parts[i][0] for i in sel], **kw)
+        for b, i in enumerate(sel):
+            s.set_state(np.zeros(parts[i][0].n), parts[i][2], inst=b)
+        s.iterate(16, record=True)
+        pts = [s.solution(inst=b, which=pd.SOL_CURRENT) for b in range(len(sel))]
+        return pts, s.backward(np.concatenate([g[i][0] for i in sel]), np.concatenate([g[i][1] for i in sel]))
+
+    pts, grads = adjoint(range(len(parts)))
+    at = {"n": 0, "m": 0}
+    for i, (lp, _, _) in enumerate(parts):
+        p1, g1 = adjoint([i])
+        for u, v in zip(pts[i], p1[0]):
+            np.testing.assert_array_equal(u, v)
+        for key, want in g1.items():
+            dim = "m" if key in ("rhs", "y0") else "n"
+            np.testing.assert_array_equal(grads[key][at[dim]:at[dim] + want.size], want, err_msg=f"{i} {key}")
+        at["n"] += lp.n
+        at["m"] += lp.m

@@ -298,6 +298,14 @@ static int seg_group(int code)
     return (lanes_log2 >= 8 ? 1 : (WG >> lanes_log2)) << rows_log2;
 }
 
+// logical blocks of the row-binned sweeps over these segments
+static int64_t row_blocks(const std::vector<SegH> &segs)
+{
+    int64_t n = 0;
+    for (const SegH &s : segs) n += (s.nrows + seg_group(s.lanes_log2) - 1) / seg_group(s.lanes_log2);
+    return n;
+}
+
 static void plan_instance(const HostLP &h, const pdhg_opts &o, InstPlan &p)
 {
     const int S = o.col_slices, St = o.col_slices_t;
@@ -544,6 +552,8 @@ struct Sizes {
     // spread.hip: windows, tiles and entries of K^T and K, and whether some rows are in no window
     int64_t win[2] = {0, 0}, win_nt[2] = {0, 0}, win_n[2] = {0, 0};
     bool unspread[2] = {false, false};
+    // row blocks of an operator with both kinds that the row-binned sweeps take
+    int64_t rest[2] = {0, 0};
 };
 
 // The blocks of the tiled operators and the windows of the spread ones.
@@ -575,6 +585,7 @@ struct Buffers {
     SmallDev small;
     TileOp tile[2];
     SpreadOp spread[2];
+    ActList rest[2];  // 0: K^T, 1: K
 };
 
 // Longest point (n + m) that goes through the handle's pinned memory (512 KB).
@@ -703,6 +714,15 @@ static void carve(Carve &cv, const Sizes &sz, int prec, const pdhg_opts &o, Dev 
         t.inst = cv.take<int2>(sz.batch);
         t.act = cv.take<int32_t>(t.nblk);
     }
+    b.rest[0] = b.rest[1] = ActList{};
+    for (int op = 0; op < 2; ++op) {
+        ActList &r = b.rest[op];
+        r.n = (int32_t)sz.rest[op];
+        if (r.n == 0) continue;
+        r.blk = cv.take<int32_t>(r.n);
+        r.inst = cv.take<int2>(sz.batch);
+        r.act = cv.take<int32_t>(r.n);
+    }
     b.spread[0] = b.spread[1] = SpreadOp{};
     const int64_t gathered = std::max(sz.win_n[0], sz.win_n[1]);
     void *g = gathered > 0 ? cv.take<char>(gathered * es) : nullptr;
@@ -733,7 +753,7 @@ static void carve(Carve &cv, const Sizes &sz, int prec, const pdhg_opts &o, Dev 
     }
     d.actK = cv.take<int32_t>(sz.nblkK + 1);
     d.actT = cv.take<int32_t>(sz.nblkT + 1);
-    d.act_cnt = cv.take<int32_t>(4);
+    d.act_cnt = cv.take<int32_t>(6);
     d.act_off = cv.take<int32_t>(2 * (size_t)sz.batch);
     d.act_coff = cv.take<int64_t>(2 * (size_t)sz.batch + 2);
     d.act_split = cv.take<int32_t>(18);
@@ -949,6 +969,7 @@ static void tile_blocks(const std::vector<InstPlan> &plans, const pdhg_opts *o, 
             const int first = (int)tb.blk[op].size();
             if (t.ntile == 0) {
                 sz.untiled[op] = true;
+                sz.rest[op] += row_blocks(op == 0 ? p.segT : p.segK);
                 tb.inst[op].push_back(make_int2(first, first));
                 continue;
             }
@@ -1008,6 +1029,7 @@ static void tile_blocks(const std::vector<InstPlan> &plans, const pdhg_opts *o, 
         }
         sz.tile_blk[op] = (int64_t)tb.blk[op].size();
         sz.tile_run[op] = (int64_t)tb.run[op].size();
+        if (sz.tile_blk[op] == 0) sz.rest[op] = 0;
     }
 }
 
@@ -1040,6 +1062,7 @@ static void spread_windows(const InstPlan &p, int64_t es, Sizes &sz, TileBlocks 
             const bool fits = std::all_of(len, len + g.nrows, [&](int32_t l) { return l <= cap; });
             tb.spread[op].push_back(fits);
             sz.unspread[op] |= !fits;
+            if (!fits) sz.rest[op] += row_blocks({g});
             int64_t n = 0, r0 = 0;
             for (int64_t r = 0; fits && r <= g.nrows; ++r) {
                 if (r == g.nrows || n + len[r] > cap || r - r0 == cap) {
@@ -1053,7 +1076,7 @@ static void spread_windows(const InstPlan &p, int64_t es, Sizes &sz, TileBlocks 
         sz.win[op] = (int64_t)win.size();
         sz.win_nt[op] = nt;
         sz.win_n[op] = entries;
-        if (win.empty()) tb.spread[op].clear();
+        if (win.empty()) tb.spread[op].clear(), sz.rest[op] = 0;
     }
 }
 
@@ -1104,11 +1127,8 @@ static int plan_all(const pdhg_lp *lp, int32_t batch, const pdhg_opts *o, std::v
         sz.N += hosts[b].n;
         sz.M += hosts[b].m;
         sz.NNZ += hosts[b].nnz;
-        int64_t pb = 0;
-        for (auto &s : plans[b].segK) pb += (s.nrows + seg_group(s.lanes_log2) - 1) / seg_group(s.lanes_log2);
+        const int64_t pb = row_blocks(plans[b].segK), pt = row_blocks(plans[b].segT);
         sz.nblkK += pb;
-        int64_t pt = 0;
-        for (auto &s : plans[b].segT) pt += (s.nrows + seg_group(s.lanes_log2) - 1) / seg_group(s.lanes_log2);
         sz.nblkT += pt;
         sz.nl2 += (pb + pt + L2CH - 1) / L2CH;
         sz.nsegK += plans[b].segK.size();
@@ -1185,13 +1205,13 @@ static int h2d(X *dst, const X *src, size_t cnt, hipStream_t s)
     return PDHG_OK;
 }
 
-// Workgroups of a sweep over a tiled operator: the blocks that can run at once, so
-// that a batch that runs a few instances at a time launches no idle ones (128
-// iterations of each of 24 LPs of 60k to 150k nonzeros, one after another: 26.4 ms
-// with the whole batch's blocks in each launch and the lists written by one lane per
-// instance, 24.9 ms so).  The admission budget holds the running instances'
-// bytes; the bound takes the instances with most blocks per byte, the last one whole.
-static int32_t tile_grid(const pdhg_handle *h, const std::vector<int2> &inst, int32_t nblk)
+// Workgroups of a sweep over a list of blocks: those that can run at once, so that
+// a batch that runs a few instances at a time launches no idle ones (128 iterations
+// of each of 24 LPs of 60k to 150k nonzeros, one after another: 26.4 ms with the
+// whole batch's blocks in each launch and the lists written by one lane per
+// instance, 24.9 ms so).  The admission budget holds the running instances' bytes;
+// the bound takes the instances with most blocks per byte, the last one whole.
+static int32_t run_grid(const pdhg_handle *h, const std::vector<int2> &inst, int32_t nblk)
 {
     if (h->batch == 1 || h->opts.batch_resident_bytes <= 0) return std::min(nblk, TILE_GRID);
     auto blocks = [&](int b) { return (int64_t)(inst[b].y - inst[b].x); };
@@ -1529,6 +1549,29 @@ static int upload(pdhg_handle *h, std::vector<HostLP> &hosts, const TileBlocks &
         return rc;
     d.tile_nblk[0] = b.tile[1].nblk;
     d.tile_nblk[1] = b.tile[0].nblk;
+    // the blocks that the row-binned sweeps keep of an operator with both kinds
+    std::vector<int32_t> rest_blk[2];
+    std::vector<int2> rest_inst[2];
+    for (int op = 0; op < 2; ++op) {
+        const ActList &r = b.rest[op];
+        const int on = 1 - op;  // the Dev's order: K, K^T
+        d.rest[on] = h->batch == 1 ? r.blk : r.act;
+        d.rest_nblk[on] = r.n;
+        d.rest_grid[on] = 0;
+        if (r.n == 0) continue;
+        const auto &bd = op == 0 ? Ktbd : Kbd;
+        rest_inst[op].assign(h->batch, make_int2(0, 0));
+        for (size_t k = 0; k < bd.size(); ++k) {
+            int2 &rg = rest_inst[op][bd[k].z];
+            if (rg.y == 0) rg.x = rg.y = (int32_t)rest_blk[op].size();
+            if ((bd[k].w >> 10 & 1) == 0) rest_blk[op].push_back((int32_t)k);
+            rg.y = (int32_t)rest_blk[op].size();
+        }
+        d.rest_grid[on] = std::min(run_grid(h, rest_inst[op], r.n), d.grid_cap);
+        if ((rc = h2d((int32_t *)r.blk, rest_blk[op].data(), rest_blk[op].size(), s)) ||
+            (rc = h2d((int2 *)r.inst, rest_inst[op].data(), rest_inst[op].size(), s)))
+            return rc;
+    }
     for (int op = 0; op < 2; ++op) {
         const TileOp &t = b.tile[op];
         if (t.nblk == 0) continue;
@@ -1537,7 +1580,7 @@ static int upload(pdhg_handle *h, std::vector<HostLP> &hosts, const TileBlocks &
         // FP32 on 256 blocks: 90 fours a block 5.4 / 5.7 / 4.1, 250 5.1 / 6.4 / 5.5 and
         // 5.3 / 5.8 / 4.7, 900 6.5 / 5.7 / 5.6, 1,200 8.3 / 6.2 / 8.5.
         b.tile[op].direct = sz.tile_q[op] < 1000 * sz.tile_blk[op];
-        b.tile[op].grid = tile_grid(h, tiles.inst[op], t.nblk);
+        b.tile[op].grid = run_grid(h, tiles.inst[op], t.nblk);
         int32_t widest = 0;
         for (const TileBlk &k : tiles.blk[op]) widest = std::max(widest, k.width);
         b.tile[op].lds = TILE_LDS - TILE_BYTES;
@@ -2015,8 +2058,10 @@ static void enqueue_dual(const pdhg_handle *h, const Dev &d, int j, int avg, Mas
 static void enqueue_active(const pdhg_handle *h, const Dev &d, hipStream_t s, int64_t budget = 0, int first = 0)
 {
     launch_active(d, s, budget, first);
-    if (h->batch > 1 && h->buf.tile[0].nblk + h->buf.tile[1].nblk > 0)
-        launch_act_tile(d, h->buf.tile[1], h->buf.tile[0], s);
+    const TileOp &tT = h->buf.tile[0], &tK = h->buf.tile[1];
+    if (h->batch > 1 && tT.nblk + tK.nblk > 0)
+        launch_act_lists(d, {{tK.nblk, tK.inst, nullptr, tK.act}, {tT.nblk, tT.inst, nullptr, tT.act}, h->buf.rest[1],
+                             h->buf.rest[0]}, s);
 }
 
 // the handle's mask buffers: C bytes a row, so the masks of MASK_PACK * C steps
@@ -3059,6 +3104,7 @@ static int autotune_impl(const pdhg_lp *lp, int32_t batch, const pdhg_opts *base
                     bound.win[op] = std::max(bound.win[op], sz.win[op]);
                     bound.win_nt[op] = std::max(bound.win_nt[op], sz.win_nt[op]);
                     bound.win_n[op] = std::max(bound.win_n[op], sz.win_n[op]);
+                    bound.rest[op] = std::max(bound.rest[op], sz.rest[op]);
                 }
                 for (int op = 0; op < 2; ++op) {
                     bound.small_tasks[op] = std::max(bound.small_tasks[op], sz.small_tasks[op]);

@@ -18,7 +18,7 @@ template <typename T>
 void launch_tile_build(const OpDev &op, const TileOp &to, hipStream_t s);
 template <typename T>
 hipError_t tile_prepare();
-void launch_act_tile(const Dev &d, const TileOp &K, const TileOp &Kt, hipStream_t s);
+void launch_act_lists(const Dev &d, const ActList (&lists)[4], hipStream_t s);
 template <typename T>
 void launch_spread_primal(const Dev &d, const SpreadOp &so, int j, int avg, Mask mask, hipStream_t s);
 template <typename T>

@@ -50,8 +50,10 @@ namespace {  // kernels a part does not launch are not emitted in it
 //   SL = 2  pass S-1: the sliced rows add their last slice to the partial,
 //           the rows of unsliced segments are swept whole, and every row is
 //           updated as with SL = 0.
-// SL + 4: the same without the rows that tile.hip sweeps (a batch of both kinds;
-// a role of its own, since the test of each block costs the sweeps 5%).
+// SL + 4: the same over the blocks that tile.hip (spread.hip) leaves, from a list
+// of their own (an operator with both kinds; a test of each block would cost the
+// sweeps 5%, and walking all blocks to skip most took 13.8 us a launch in a batch
+// of 64 LPs of up to 31M nonzeros with 4 such operators).
 // The partial store and the update stores are in different launches, so no
 // launch chooses between two store targets for one row.
 
@@ -90,13 +92,12 @@ __global__ __launch_bounds__(WG) void k_primal(Dev d, int j_in_chunk, uint8_t *_
     const T *__restrict__ l = (const T *)d.l;
     const T *__restrict__ u = (const T *)d.u;
     const T *__restrict__ y = (const T *)d.y;
-    const int cnt = d.act_cnt[1];
-    const bool full = cnt == op.nblk;  // every block active: the list is the identity
-    for_each_item_split(cnt, d.remap, d.act_split + 9, j_in_chunk & 1, [&](int it) {
-        const int lb = full ? it : d.actT[it];
+    const int cnt = d.act_cnt[(SLX & 4) ? 5 : 1];
+    const bool full = !(SLX & 4) && cnt == op.nblk;  // every block active: the list is the identity
+    auto item = [&](int it) {
+        const int lb = (SLX & 4) ? d.rest[1][it] : full ? it : d.actT[it];
         const Seg s = block_seg(op, lb);
         if (SL == 1 && !s.sliced) return;
-        if ((SLX & 4) && s.tiled) return;
         const InstState *st = d.st + s.inst;
         const double tau = st->tau;
         const double w = AVG ? 1.0 / (double)(st->t_inner + j_in_chunk + 1) : 0.0;
@@ -140,7 +141,11 @@ __global__ __launch_bounds__(WG) void k_primal(Dev d, int j_in_chunk, uint8_t *_
                 }
             }
         });
-    });
+    };
+    if constexpr (SLX & 4)
+        for_each_item(cnt, d.remap, item);
+    else
+        for_each_item_split(cnt, d.remap, d.act_split + 9, j_in_chunk & 1, item);
 }
 
 template <typename T, int AVG, int MASK, int RM, int SLX>
@@ -154,13 +159,12 @@ __global__ __launch_bounds__(WG) void k_dual(Dev d, int j_in_chunk, uint8_t *__r
     const T *__restrict__ y0 = (const T *)d.y0;
     const T *__restrict__ q = (const T *)d.q;
     const T *__restrict__ xb = (const T *)d.xbar;
-    const int cnt = d.act_cnt[0];
-    const bool full = cnt == op.nblk;
-    for_each_item_split(cnt, d.remap, d.act_split, j_in_chunk & 1, [&](int it) {
-        const int lb = full ? it : d.actK[it];
+    const int cnt = d.act_cnt[(SLX & 4) ? 4 : 0];
+    const bool full = !(SLX & 4) && cnt == op.nblk;  // every block active: the list is the identity
+    auto item = [&](int it) {
+        const int lb = (SLX & 4) ? d.rest[0][it] : full ? it : d.actK[it];
         const Seg s = block_seg(op, lb);
         if (SL == 1 && !s.sliced) return;
-        if ((SLX & 4) && s.tiled) return;
         const InstState *st = d.st + s.inst;
         const double sigma = st->sigma;
         const double w = AVG ? 1.0 / (double)(st->t_inner + j_in_chunk + 1) : 0.0;
@@ -198,7 +202,11 @@ __global__ __launch_bounds__(WG) void k_dual(Dev d, int j_in_chunk, uint8_t *__r
                 }
             }
         });
-    });
+    };
+    if constexpr (SLX & 4)
+        for_each_item(cnt, d.remap, item);
+    else
+        for_each_item_split(cnt, d.remap, d.act_split, j_in_chunk & 1, item);
 }
 
 // ---------------------------------------------------------------------------
@@ -1103,7 +1111,8 @@ __global__ __launch_bounds__(WG) void k_control(Dev d, CtlParams P, int iters_do
     reduce_instance(d, in, tot);
     if (threadIdx.x == 0) {
         control_decide(d, P, iters_done, b, st, in, tot);
-        if (d.batch == 1 && st.done) d.act_cnt[0] = d.act_cnt[1] = d.act_cnt[2] = d.act_cnt[3] = 0;
+        if (d.batch == 1 && st.done)
+            for (int k = 0; k < 6; ++k) d.act_cnt[k] = 0;
         restart = st.restart && !st.done;
         cand_avg = st.cand_avg;
     }
@@ -1254,8 +1263,11 @@ __global__ __launch_bounds__(ACT_T) void k_act_scan(Dev d)
     if (t == 0) {
         d.act_cnt[0] = (int32_t)carry[0];
         d.act_cnt[1] = (int32_t)carry[1];
-        if (B == 1)  // a batch's tile lists come from k_act_tile
-            for (int o = 0; o < 2; ++o) d.act_cnt[2 + o] = d.st[0].done == 0 ? d.tile_nblk[o] : 0;
+        if (B == 1)  // a batch's other lists come from k_act_lists
+            for (int o = 0; o < 2; ++o) {
+                d.act_cnt[2 + o] = d.st[0].done == 0 ? d.tile_nblk[o] : 0;
+                d.act_cnt[4 + o] = d.st[0].done == 0 ? d.rest_nblk[o] : 0;
+            }
         d.act_coff[2 * B] = carry[2];
         d.act_coff[2 * B + 1] = carry[3];
     }
@@ -1876,16 +1888,16 @@ static inline unsigned sweep_grid(const Dev &d, int64_t nitems)
 template <typename T>
 void launch_primal(const Dev &d, int j, int avg, Mask mask, hipStream_t s, int untiled)
 {
-    const unsigned g = sweep_grid(d, d.Kt.nblk);
+    const unsigned g = sweep_grid(d, d.Kt.nblk), gr = (unsigned)d.rest_grid[1];
     if (d.Kt.slices > 1 && !mask.p) {
         // column-sliced sweep: S launches (the recorded steps sweep whole rows)
         const int last = d.Kt.slices - 1;
         RM_SWITCH(d.Kt.rmax, {
             for (int pass = 0; pass < last; ++pass) LAUNCH((k_primal<T, 0, 0, RMV, 1>), g, d, j, nullptr, pass);
             if (untiled && avg) {
-                LAUNCH((k_primal<T, 1, 0, RMV, 6>), g, d, j, nullptr, last);
+                LAUNCH((k_primal<T, 1, 0, RMV, 6>), gr, d, j, nullptr, last);
             } else if (untiled) {
-                LAUNCH((k_primal<T, 0, 0, RMV, 6>), g, d, j, nullptr, last);
+                LAUNCH((k_primal<T, 0, 0, RMV, 6>), gr, d, j, nullptr, last);
             } else if (avg) {
                 LAUNCH((k_primal<T, 1, 0, RMV, 2>), g, d, j, nullptr, last);
             } else {
@@ -1896,11 +1908,11 @@ void launch_primal(const Dev &d, int j, int avg, Mask mask, hipStream_t s, int u
     }
     RM_SWITCH(d.Kt.rmax, {
         if (untiled && mask.p) {
-            LAUNCH((k_primal<T, 0, 1, RMV, 4>), g, d, j, mask.p, mask.sh);
+            LAUNCH((k_primal<T, 0, 1, RMV, 4>), gr, d, j, mask.p, mask.sh);
         } else if (untiled && avg) {
-            LAUNCH((k_primal<T, 1, 0, RMV, 4>), g, d, j, nullptr, 0);
+            LAUNCH((k_primal<T, 1, 0, RMV, 4>), gr, d, j, nullptr, 0);
         } else if (untiled) {
-            LAUNCH((k_primal<T, 0, 0, RMV, 4>), g, d, j, nullptr, 0);
+            LAUNCH((k_primal<T, 0, 0, RMV, 4>), gr, d, j, nullptr, 0);
         } else if (mask.p) {
             LAUNCH((k_primal<T, 0, 1, RMV, 0>), g, d, j, mask.p, mask.sh);
         } else if (avg) {
@@ -1914,15 +1926,15 @@ void launch_primal(const Dev &d, int j, int avg, Mask mask, hipStream_t s, int u
 template <typename T>
 void launch_dual(const Dev &d, int j, int avg, Mask mask, hipStream_t s, int untiled)
 {
-    const unsigned g = sweep_grid(d, d.K.nblk);
+    const unsigned g = sweep_grid(d, d.K.nblk), gr = (unsigned)d.rest_grid[0];
     if (d.K.slices > 1 && !mask.p) {
         const int last = d.K.slices - 1;
         RM_SWITCH(d.K.rmax, {
             for (int pass = 0; pass < last; ++pass) LAUNCH((k_dual<T, 0, 0, RMV, 1>), g, d, j, nullptr, pass);
             if (untiled && avg) {
-                LAUNCH((k_dual<T, 1, 0, RMV, 6>), g, d, j, nullptr, last);
+                LAUNCH((k_dual<T, 1, 0, RMV, 6>), gr, d, j, nullptr, last);
             } else if (untiled) {
-                LAUNCH((k_dual<T, 0, 0, RMV, 6>), g, d, j, nullptr, last);
+                LAUNCH((k_dual<T, 0, 0, RMV, 6>), gr, d, j, nullptr, last);
             } else if (avg) {
                 LAUNCH((k_dual<T, 1, 0, RMV, 2>), g, d, j, nullptr, last);
             } else {
@@ -1933,11 +1945,11 @@ void launch_dual(const Dev &d, int j, int avg, Mask mask, hipStream_t s, int unt
     }
     RM_SWITCH(d.K.rmax, {
         if (untiled && mask.p) {
-            LAUNCH((k_dual<T, 0, 1, RMV, 4>), g, d, j, mask.p, mask.sh);
+            LAUNCH((k_dual<T, 0, 1, RMV, 4>), gr, d, j, mask.p, mask.sh);
         } else if (untiled && avg) {
-            LAUNCH((k_dual<T, 1, 0, RMV, 4>), g, d, j, nullptr, 0);
+            LAUNCH((k_dual<T, 1, 0, RMV, 4>), gr, d, j, nullptr, 0);
         } else if (untiled) {
-            LAUNCH((k_dual<T, 0, 0, RMV, 4>), g, d, j, nullptr, 0);
+            LAUNCH((k_dual<T, 0, 0, RMV, 4>), gr, d, j, nullptr, 0);
         } else if (mask.p) {
             LAUNCH((k_dual<T, 0, 1, RMV, 0>), g, d, j, mask.p, mask.sh);
         } else if (avg) {

@@ -163,8 +163,13 @@ struct Dev {
     const int32_t *l2_inst;       // instance of each second-level row
     int32_t nl2;
     int32_t *actK, *actT;         // logical blocks of running instances (K, K^T sweeps)
-    int32_t *act_cnt;             // [4]: lengths of actK, actT and of the tile lists of K, K^T
+    // [6]: lengths of actK, actT, of the tile lists and of the lists `rest`
+    int32_t *act_cnt;
     int32_t tile_nblk[2];         // tile blocks of K, K^T
+    // Logical blocks of K, K^T that tile.hip (spread.hip) leaves to the row-binned
+    // sweeps, of the running instances, where an operator has both kinds
+    const int32_t *rest[2];
+    int32_t rest_nblk[2], rest_grid[2];
     int32_t *act_off;             // [2 * batch]: list offsets per instance
     // XCD split of the sweeps' active lists by cost: bcum = prefix sums of the
     // blocks' cost (entries + 4 per row) in block order, act_coff the list
@@ -248,7 +253,7 @@ constexpr int TILE_LDS = TILE_BYTES + 8 * TILE_ROWS + 4 * (TILE_ROWS + 4);  // o
 constexpr int TILE_SPLIT = 8;                  // tiles of an operator at most
 constexpr int TILE_SEGS = 10240;               // rows x tiles of a block at most
 constexpr int TILE_BLOCKS = 256;               // blocks of a lone LP's operator (one per CU)
-constexpr int TILE_GRID = 4096;                // workgroups of a launch at most (tile_grid())
+constexpr int TILE_GRID = 4096;                // workgroups of a launch at most (run_grid())
 struct TileBlk {
     int64_t sp0;        // first quad range in sp (tile by tile, row by row; relative to q0)
     int64_t q0;         // first quad
@@ -272,6 +277,15 @@ struct TileOp {
     void *val;          // four values per quad, iterate type
     const int2 *inst;   // block range per instance
     int32_t *act;       // blocks of the running instances
+};
+
+// A list of the running instances' blocks: those of instance b are blk[inst[b].x] ..
+// blk[inst[b].y - 1] (the numbers themselves without blk).
+struct ActList {
+    int32_t n;          // blocks of all instances; 0: no list
+    const int2 *inst;
+    const int32_t *blk;
+    int32_t *act;
 };
 
 // Operators whose sweeps run in two passes (spread.hip): gather by column tile,

@@ -390,15 +390,18 @@ __global__ __launch_bounds__(TILE_WG) void k_tile_build(OpDev op, TileOp to)
     }
 }
 
-// block lists of the running instances (one workgroup), for both operators: a
-// scan over the instances' block counts, then a wavefront per instance
-__global__ __launch_bounds__(TILE_WG) void k_act_tile(Dev d, TileOp K, TileOp Kt)
+// block lists of the running instances (one workgroup): a scan over the
+// instances' block counts, then a wavefront per instance
+struct ActLists {
+    ActList l[4];  // the tiles' of K, K^T, the other blocks' of K, K^T
+};
+__global__ __launch_bounds__(TILE_WG) void k_act_lists(Dev d, ActLists lists)
 {
     __shared__ int32_t s[TILE_WG], first[TILE_WG], num[TILE_WG];
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-    for (int o = 0; o < 2; ++o) {
-        const TileOp &op = o == 0 ? K : Kt;
-        if (op.nblk == 0) continue;
+    for (int o = 0; o < 4; ++o) {
+        const ActList &op = lists.l[o];
+        if (op.n == 0) continue;
         int32_t carry = 0;
         for (int b0 = 0; b0 < d.batch; b0 += TILE_WG) {
             const int b = b0 + tid;
@@ -415,7 +418,8 @@ __global__ __launch_bounds__(TILE_WG) void k_act_tile(Dev d, TileOp K, TileOp Kt
                 __syncthreads();
             }
             for (int k = wave; k < min(TILE_WG, d.batch - b0); k += TILE_WG / 64)
-                for (int j = lane; j < num[k]; j += 64) op.act[carry + s[k] - num[k] + j] = first[k] + j;
+                for (int j = lane; j < num[k]; j += 64)
+                    op.act[carry + s[k] - num[k] + j] = op.blk ? op.blk[first[k] + j] : first[k] + j;
             carry += s[TILE_WG - 1];
             __syncthreads();
         }
@@ -493,9 +497,9 @@ hipError_t tile_prepare()
     return e == hipSuccess ? tile_attr<1024, T>() : e;
 }
 
-void launch_act_tile(const Dev &d, const TileOp &K, const TileOp &Kt, hipStream_t s)
+void launch_act_lists(const Dev &d, const ActList (&lists)[4], hipStream_t s)
 {
-    hipLaunchKernelGGL(k_act_tile, dim3(1), dim3(TILE_WG), 0, s, d, K, Kt);
+    hipLaunchKernelGGL(k_act_lists, dim3(1), dim3(TILE_WG), 0, s, d, ActLists{{lists[0], lists[1], lists[2], lists[3]}});
 }
 
 #define TILE_INST(T)                                                                                   \

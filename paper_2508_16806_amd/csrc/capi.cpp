@@ -265,17 +265,21 @@ static Bins make_bins(const int32_t *lim, const int32_t *rows, int f)
 // 4 * 2^k halves a row's chain of loads, which is what a sweep costs while the chip
 // has lanes to spare: adaptive primal + dual sweep with 4 * 2^k and 8 * 2^k, random
 // LPs of 12k nonzeros 12.3 / 16.6, 50k 10.7 / 12.5, 250k 12.2 / 13.9, 0.5M 13.2 / 15.4,
-// 0.8M 12.8 / 13.7, 1.0M 15.2 / 15.6, 2.0M 26.6 / 24.8.  The two differ in the lanes
-// of rows of 5 to 256 entries only: where these hold less than half of the entries,
+// 0.8M 12.8 / 13.7, 1.0M 15.2 / 15.6, 2.0M 26.6 / 24.8.  With fixed steps, which the
+// limits concern where the rows are not tiled, and in the checks, it ends earlier:
+// primal + dual / check on 120k nonzeros over local columns 9.5 / 12.2 and 10.3 / 12.7,
+// a dispatch LP of 0.4M 10.2 / 14.9 and 10.1 / 13.5; checks of random LPs of 12k
+// 8.0 / 8.8, 40k 8.5 / 9.8, 200k 13.4 / 11.0, 0.8M 22.5 / 18.6.  The two differ in the
+// lanes of rows of 5 to 256 entries only: where these hold less than half of the entries,
 // 8 * 2^k everywhere (60,000 rows of 2 entries 5.4 / 4.7 and 5.6 / 5.6).  Sliced
 // rows are gathered a piece at a time and take 4 * 2^k: 4 / 2 slices on 5.3M
 // nonzeros 22.2 / 27.1 us primal, on 1.1M dual 21.8 / 22.8.
-constexpr int64_t SHORT_CHAIN_NNZ = 1000000;
+constexpr int64_t SHORT_CHAIN_NNZ = 200000, SHORT_CHAIN_NNZ_ADAPTIVE = 1000000;
 template <typename F>
-static int default_limits(int64_t nnz, int S, int64_t rows, F &&len)
+static int default_limits(int64_t nnz, int S, int adaptive, int64_t rows, F &&len)
 {
     if (S > 1) return 4;
-    if (nnz >= SHORT_CHAIN_NNZ) return 8;
+    if (nnz >= (adaptive ? SHORT_CHAIN_NNZ_ADAPTIVE : SHORT_CHAIN_NNZ)) return 8;
     int64_t in = 0;
     for (int64_t r = 0; r < rows; ++r) {
         const int64_t l = len(r);
@@ -314,7 +318,8 @@ static void plan_instance(const HostLP &h, const pdhg_opts &o, InstPlan &p)
     p.m1 = h.m1;
     p.nnz = h.nnz;
     const Bins bins = make_bins(o.bin_len_dual, o.bin_rows_dual,
-                                default_limits(h.nnz, S, h.m, [&](int64_t i) { return h.rp[i + 1] - h.rp[i]; }));
+                                default_limits(h.nnz, S, o.adaptive_step, h.m,
+                                               [&](int64_t i) { return h.rp[i + 1] - h.rp[i]; }));
     // rows: ">=" group then "=" group, each split into whole rows and rows
     // swept in S column slices (binned by their per-slice length), each
     // ordered by bin, stable
@@ -343,7 +348,7 @@ static void plan_instance(const HostLP &h, const pdhg_opts &o, InstPlan &p)
     std::vector<int64_t> cnt(h.n, 0);
     for (int64_t k = 0; k < h.nnz; ++k) cnt[h.ci[k]]++;
     const Bins tbins = make_bins(o.bin_len_primal, o.bin_rows_primal,
-                                 default_limits(h.nnz, St, h.n, [&](int64_t j) { return cnt[j]; }));
+                                 default_limits(h.nnz, St, o.adaptive_step, h.n, [&](int64_t j) { return cnt[j]; }));
     // how many neighbouring entries of a row (of a column) share a line of the
     // gathered vector, on four stretches of consecutive rows
     constexpr int64_t STRETCH = 65536;

@@ -34,8 +34,10 @@ def _lp(lens, n, seed=1):
 CASES = {
     "short": (np.full(1000, 12), 2400, {}, 4, 4),  # columns of 5
     "columns_of_4": (np.full(1000, 12), 3000, {}, 4, 8),
-    "999999": (np.full(999999 // 37, 37), 33333, {}, 4, 4),  # columns of 30
-    "1000036": (np.full(1000036 // 37, 37), 33333, {}, 8, 8),
+    "199985": (np.full(199985 // 37, 37), 6666, {}, 4, 4),  # columns of 30
+    "200022": (np.full(200022 // 37, 37), 6667, {}, 8, 8),
+    "999999": (np.full(999999 // 37, 37), 33333, dict(adaptive_step=1), 4, 4),
+    "1000036": (np.full(1000036 // 37, 37), 33333, dict(adaptive_step=1), 8, 8),
     "half_long": (np.r_[np.full(100, 30), np.full(10, 300)], 660, {}, 4, 4),  # 3,000 and 3,000 entries
     "more_long": (np.r_[np.full(100, 30), np.full(11, 300)], 700, {}, 8, 4),
     "sliced": (np.full(1000036 // 37, 37), 33333, dict(col_slices=2), 4, 8),

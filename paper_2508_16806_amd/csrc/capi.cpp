@@ -350,7 +350,9 @@ static void plan_instance(const HostLP &h, const pdhg_opts &o, InstPlan &p)
     const Bins tbins = make_bins(o.bin_len_primal, o.bin_rows_primal,
                                  default_limits(h.nnz, St, o.adaptive_step, h.n, [&](int64_t j) { return cnt[j]; }));
     // how many neighbouring entries of a row (of a column) share a line of the
-    // gathered vector, on four stretches of consecutive rows
+    // gathered vector, on four stretches of consecutive rows that start at the
+    // quarters of the entries (at the quarters of the rows, a dispatch LP's stretches
+    // mostly missed its 9% of rows with 92% of the entries)
     constexpr int64_t STRETCH = 65536;
     const int64_t ns = h.nnz > 4 * STRETCH ? 4 : 1;
     std::vector<int32_t> last(h.n, INT32_MIN / 2);  // row of the column's entry before
@@ -359,7 +361,8 @@ static void plan_instance(const HostLP &h, const pdhg_opts &o, InstPlan &p)
     for (int64_t w = 0; w < ns; ++w) {
         int64_t left = ns > 1 ? STRETCH : h.nnz, rows = 0, entries = 0;
         ++group;
-        for (int64_t i = h.m * w / ns; i < h.m * (w + 1) / ns && left > 0; ++i) {
+        int64_t i = std::lower_bound(h.rp, h.rp + h.m, h.nnz * w / ns) - h.rp;
+        for (; i < h.m && left > 0; ++i) {
             for (int64_t k = h.rp[i]; k < h.rp[i + 1]; ++k) {
                 const int32_t c = h.ci[k];
                 p.local[0] += (int32_t)i - last[c] < 32 ? 1 : -1;

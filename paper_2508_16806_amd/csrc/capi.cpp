@@ -2584,6 +2584,10 @@ static int fish_build_tables(pdhg_handle *h, hipStream_t s)
         std::stable_sort(splits.begin(), splits.end(), [](const int4 &a, const int4 &b) { return a.z > b.z; });
         const auto shrt = std::find_if(tasks.begin(), tasks.end(), [](const int4 &a) { return a.z - a.y <= FISH_LONG; });
         (op == 0 ? f.nlongK : f.nlongT) = shrt - tasks.begin();
+        int64_t entries = 0;
+        for (auto t = shrt; t != tasks.end(); ++t) entries += t->z - t->y;
+        const int64_t few = std::max<int64_t>(1, tasks.end() - shrt);
+        (op == 0 ? f.lenK : f.lenT) = (int32_t)((entries + few - 1) / few);
         int32_t *rows = (int32_t *)(op == 0 ? f.rowK : f.rowT);
         int4 *tk = (int4 *)(op == 0 ? f.taskK : f.taskT);
         int4 *sp = (int4 *)(op == 0 ? f.splitK : f.splitT);

@@ -358,10 +358,14 @@ static inline unsigned fish_groups(int64_t rows, int lj)
 // 32 points on 41k + 30k rows, ms for 512 iterations with 1 / 2 / 8 lanes
 // throughout and with this rule: 18.2 / 17.8 / 22.5 / 17.7; 16 points on 8k + 6k
 // rows: 8.8 / 6.3 / 5.2 / 5.1; 4 points on 100k + 72k rows: 5.8 / 4.6 / 6.5 / 4.7.
-static inline int fish_split(int64_t ntask, int lj)
+// A task of up to 8 entries is one step of a lane, which has two quads in flight,
+// and a longer one has quads for len / 4 lanes: 8 points on 20,000 rows of 8 entries
+// and 30,000 of 5, ms for 128 iterations with up to 8 lanes 4.00, with one 3.39.
+static inline int fish_split(int64_t ntask, int len, int lj)
 {
     int ls = 0;
-    while (ls < 3 && lj + ls < 6 && (ntask << (lj + ls)) < FISH_LANES) ++ls;
+    if (len <= 8) return ls;
+    while (ls < 3 && lj + ls < 6 && (ntask << (lj + ls)) < FISH_LANES && (4 << ls) < len) ++ls;
     return ls;
 }
 
@@ -373,7 +377,7 @@ static inline unsigned fish_blocks(int64_t ntask, int64_t nlong, int lg)
 template <typename T>
 void launch_fish_step(const Dev &d, const FishDev &f, int lj, double tau, double sigma, int64_t m1, hipStream_t s)
 {
-    const int lsT = fish_split(f.ntaskT, lj), lsK = fish_split(f.ntaskK, lj);
+    const int lsT = fish_split(f.ntaskT, f.lenT, lj), lsK = fish_split(f.ntaskK, f.lenK, lj);
     const unsigned tT = fish_blocks(f.ntaskT, f.nlongT, lj + lsT), cT = fish_groups(f.nsplitT, lj);
     const unsigned tK = fish_blocks(f.ntaskK, f.nlongK, lj + lsK), cK = fish_groups(f.nsplitK, lj);
     if (tT) hipLaunchKernelGGL(k_fish_primal<T>, dim3(tT), dim3(WG), 0, s, d, f, lj, lsT, tau);
@@ -387,7 +391,7 @@ void launch_fish_init(const Dev &d, const FishDev &f, int lp, double sc, hipStre
 {
     const int64_t tot = d.N << lp;
     if (tot > 0) hipLaunchKernelGGL(k_fish_init<T>, dim3((unsigned)((tot + WG - 1) / WG)), dim3(WG), 0, s, d, f, lp, sc);
-    const int ls = fish_split(f.ntaskK, lp);
+    const int ls = fish_split(f.ntaskK, f.lenK, lp);
     const unsigned tK = fish_blocks(f.ntaskK, f.nlongK, lp + ls), cK = fish_groups(f.nsplitK, lp);
     if (tK) hipLaunchKernelGGL((k_fish_dual<T, 1>), dim3(tK), dim3(WG), 0, s, d, f, lp, ls, 0.0, (int64_t)0);
     if (cK) hipLaunchKernelGGL((k_fish_combine_dual<T, 1>), dim3(cK), dim3(WG), 0, s, d, f, lp, 0.0, (int64_t)0);
@@ -397,7 +401,7 @@ template <typename T>
 int launch_fish_gap_rank(const Dev &d, const FishDev &f, int lj, int round, int repop, int half, int64_t wpos,
                          hipStream_t s)
 {
-    const int ls = fish_split(f.ntaskT, lj);
+    const int ls = fish_split(f.ntaskT, f.lenT, lj);
     const int64_t gT = fish_groups(d.Kt.nrows, lj + ls), gK = fish_groups(d.K.nrows, lj);
     const int64_t items = gT + gK;
     const int grid = (int)(items < FISH_GRID ? (items > 0 ? items : 1) : FISH_GRID);

@@ -1265,8 +1265,9 @@ __global__ __launch_bounds__(ACT_T) void k_act_scan(Dev d)
         d.act_cnt[1] = (int32_t)carry[1];
         if (B == 1)  // a batch's other lists come from k_act_lists
             for (int o = 0; o < 2; ++o) {
-                d.act_cnt[2 + o] = d.st[0].done == 0 ? d.tile_nblk[o] : 0;
-                d.act_cnt[4 + o] = d.st[0].done == 0 ? d.rest_nblk[o] : 0;
+                const bool run = carry[0] + carry[1] > 0;
+                d.act_cnt[2 + o] = run ? d.tile_nblk[o] : 0;
+                d.act_cnt[4 + o] = run ? d.rest_nblk[o] : 0;
             }
         d.act_coff[2 * B] = carry[2];
         d.act_coff[2 * B + 1] = carry[3];

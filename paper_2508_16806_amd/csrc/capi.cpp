@@ -217,6 +217,7 @@ struct InstPlan {
     std::vector<int32_t> row_order;  // internal row -> caller row
     std::vector<int32_t> col_order;  // internal col -> caller col
     std::vector<SegH> segK, segT;
+    bool second = false;  // its sizes allow second layouts; what follows is then filled in
     std::vector<int32_t> len[2];  // row lengths in internal order; 0: K^T, 1: K (as below)
     // sampled entries within 32 columns (rows) of the entry before them in their
     // row (column), minus the others
@@ -233,6 +234,82 @@ struct Bins {
     int32_t max_len[NBIN];
     int32_t code[NBIN];  // lanes_log2 | rows_log2 << 4
 };
+
+// Nonzeros of a handle whose operators are tiled at most: the tiles take about
+// 12 (FP32) or 20 bytes a nonzero beside the 32 of the row-binned operators, and
+// larger handles keep the card's memory for those.
+constexpr int64_t TILE_MAX_NNZ = (int64_t)4 << 30;
+
+// Whether small.hip iterates the instance: the vectors fit a CU's LDS, no column
+// slices apply, and an iteration on one CU, whose time grows with the entries, is
+// shorter than two launches (8.5-9 us).  Measured, us per iteration (launches /
+// one CU): FP32 12.5k nonzeros 9.5 / 4.0, 22k 8.8 / 6.2, 30k 8.6 / 7.6, 50k 8.9 / 10.8; FP64
+// 2k 7.7 / 1.4, 12.5k 9.8 / 5.8, 27k 9.1 / 10.3.
+constexpr int64_t SMALL_ENTRY_BYTES = 150000;
+static bool small_size(int64_t es, const InstPlan &p)
+{
+    return (es + 2) * p.nnz <= SMALL_ENTRY_BYTES && small_bytes(p.n, p.m, es, 0, 0, 0, 0) <= SMALL_LDS;
+}
+
+// Column tiles of an operator whose sizes let tile.hip sweep it, 0 for others: with
+// several tiles the matrix must pay for each tile's way through LDS.  Measured, us
+// (row bins / tiles), planted LPs in FP32: one tile, 0.9M nonzeros 6.5 / 6.0, 1.2M
+// 8.3 / 6.6, 5M 23 / 11; two tiles, 2.0M 12.4 / 15.1, 5.0M 26 / 12.3; four, 12M 57 /
+// 24; below 0.9M see tile_blocks().  Small LPs take it in any case, since small.hip
+// sums as it does.
+static int64_t tile_count(int64_t es, const InstPlan &p, int op)
+{
+    const int64_t cols = op == 0 ? p.m : p.n, rows = op == 0 ? p.n : p.m;
+    // a tile's first element lies anywhere in a 16-byte line, its width is a multiple of four
+    const int64_t cap = TILE_BYTES / es - 4, nt = (cols + cap - 1) / cap;
+    if (p.nnz == 0 || nt > TILE_SPLIT || (nt > 1 && p.nnz < 600000 + 2000000 * (nt - 1))) return 0;
+    return small_size(es, p) || p.nnz >= 4 * rows * nt ? nt : 0;
+}
+
+// Whether tile.hip sweeps an operator without sliced rows: its gathers must also
+// lack locality (most neighbouring entries of a row on different 128-byte lines of
+// the vector; over local columns the row-binned sweeps' gathers cost little, and
+// they took 11 us where tiles took 22-29 on a dispatch LP of 3.7M nonzeros).
+static bool tiled(int64_t es, const InstPlan &p, int op)
+{
+    return p.second && tile_count(es, p, op) > 0 && (small_size(es, p) || p.local[op] <= 0);
+}
+
+// Least nonzeros of an operator that spread.hip sweeps (spread_windows()).
+constexpr int64_t SPREAD_NNZ = 5000000;
+
+// The pattern's locality, where a second layout hangs on it.
+static void sample_locality(const HostLP &h, InstPlan &p)
+{
+    // how many neighbouring entries of a row (of a column) share a line of the
+    // gathered vector, on four stretches of consecutive rows that start at the
+    // quarters of the entries (at the quarters of the rows, a dispatch LP's stretches
+    // mostly missed its 9% of rows with 92% of the entries)
+    constexpr int64_t STRETCH = 65536;
+    const int64_t ns = h.nnz > 4 * STRETCH ? 4 : 1;
+    std::vector<int32_t> last(h.n, INT32_MIN / 2);  // row of the column's entry before
+    std::vector<int32_t> line(h.n / 16 + 1, 0);     // last group with an entry in these columns
+    int32_t group = 0;
+    for (int64_t w = 0; w < ns; ++w) {
+        int64_t left = ns > 1 ? STRETCH : h.nnz, rows = 0, entries = 0;
+        ++group;
+        int64_t i = std::lower_bound(h.rp, h.rp + h.m, h.nnz * w / ns) - h.rp;
+        for (; i < h.m && left > 0; ++i) {
+            for (int64_t k = h.rp[i]; k < h.rp[i + 1]; ++k) {
+                const int32_t c = h.ci[k];
+                p.local[0] += (int32_t)i - last[c] < 32 ? 1 : -1;
+                last[c] = (int32_t)i;
+                if (k > h.rp[i]) p.local[1] += std::abs((int64_t)c - h.ci[k - 1]) < 32 ? 1 : -1;
+                p.apart += line[c >> 4] != group ? 1 : -1;
+                line[c >> 4] = group;
+            }
+            ++rows;
+            entries += h.rp[i + 1] - h.rp[i];
+            if (rows >= 16 || (rows >= 4 && entries >= 16384)) ++group, rows = entries = 0;
+            left -= h.rp[i + 1] - h.rp[i];
+        }
+    }
+}
 
 // lim: row-length limits (0: the default f * 2^k, k = 0 .. 5, and 512); rows: rows
 // per lane group (1, 2, 4; only for bins of at most 16 lanes).
@@ -265,21 +342,20 @@ static Bins make_bins(const int32_t *lim, const int32_t *rows, int f)
 // 4 * 2^k halves a row's chain of loads, which is what a sweep costs while the chip
 // has lanes to spare: adaptive primal + dual sweep with 4 * 2^k and 8 * 2^k, random
 // LPs of 12k nonzeros 12.3 / 16.6, 50k 10.7 / 12.5, 250k 12.2 / 13.9, 0.5M 13.2 / 15.4,
-// 0.8M 12.8 / 13.7, 1.0M 15.2 / 15.6, 2.0M 26.6 / 24.8.  With fixed steps, which the
-// limits concern where the rows are not tiled, and in the checks, it ends earlier:
-// primal + dual / check on 120k nonzeros over local columns 9.5 / 12.2 and 10.3 / 12.7,
-// a dispatch LP of 0.4M 10.2 / 14.9 and 10.1 / 13.5; checks of random LPs of 12k
-// 8.0 / 8.8, 40k 8.5 / 9.8, 200k 13.4 / 11.0, 0.8M 22.5 / 18.6.  The two differ in the
-// lanes of rows of 5 to 256 entries only: where these hold less than half of the entries,
-// 8 * 2^k everywhere (60,000 rows of 2 entries 5.4 / 4.7 and 5.6 / 5.6).  Sliced
-// rows are gathered a piece at a time and take 4 * 2^k: 4 / 2 slices on 5.3M
-// nonzeros 22.2 / 27.1 us primal, on 1.1M dual 21.8 / 22.8.
-constexpr int64_t SHORT_CHAIN_NNZ = 200000, SHORT_CHAIN_NNZ_ADAPTIVE = 1000000;
+// 0.8M 12.8 / 13.7, 1.0M 15.2 / 15.6, 2.0M 26.6 / 24.8; fixed steps of a network LP
+// of 0.4M (256 and their checks, ms) 3.54 / 3.74.  Where fixed steps take tiles the
+// limits concern the checks, once in a check period, which gain earlier: random LPs
+// of 12k nonzeros 8.0 / 8.8, 40k 8.5 / 9.8, 200k 13.4 / 11.0, 0.8M 22.5 / 18.6.  The
+// two differ in the lanes of rows of 5 to 256 entries only: where these hold less than
+// half of the entries, 8 * 2^k everywhere (20,000 rows of 2 entries 5.4 / 4.7 and
+// 5.6 / 5.6).  Sliced rows are gathered a piece at a time and take 4 * 2^k: 4 / 2
+// slices on 5.3M nonzeros 22.2 / 27.1 us primal, on 1.1M dual 21.8 / 22.8.
+constexpr int64_t SHORT_CHAIN_NNZ = 1000000, SHORT_CHAIN_NNZ_TILED = 200000;
 template <typename F>
-static int default_limits(int64_t nnz, int S, int adaptive, int64_t rows, F &&len)
+static int default_limits(int64_t nnz, int S, int64_t long_chain, int64_t rows, F &&len)
 {
     if (S > 1) return 4;
-    if (nnz >= (adaptive ? SHORT_CHAIN_NNZ_ADAPTIVE : SHORT_CHAIN_NNZ)) return 8;
+    if (nnz >= long_chain) return 8;
     int64_t in = 0;
     for (int64_t r = 0; r < rows; ++r) {
         const int64_t l = len(r);
@@ -310,16 +386,24 @@ static int64_t row_blocks(const std::vector<SegH> &segs)
     return n;
 }
 
-static void plan_instance(const HostLP &h, const pdhg_opts &o, InstPlan &p)
+// second: also plan the operators' second layouts
+static void plan_instance(const HostLP &h, const pdhg_opts &o, bool second, InstPlan &p)
 {
     const int S = o.col_slices, St = o.col_slices_t;
+    const int64_t es = (int64_t)elem_size(o.precision);
     p.n = h.n;
     p.m = h.m;
     p.m1 = h.m1;
     p.nnz = h.nnz;
+    p.second = second && (small_size(es, p) || tile_count(es, p, 0) > 0 || tile_count(es, p, 1) > 0 ||
+                          p.nnz >= SPREAD_NNZ);
+    if (p.second && !small_size(es, p)) sample_locality(h, p);
+    // nonzeros from which on the operator's default limits are 8 * 2^k
+    auto long_chain = [&](int op) {
+        return o.adaptive_step || !tiled(es, p, op) ? SHORT_CHAIN_NNZ : SHORT_CHAIN_NNZ_TILED;
+    };
     const Bins bins = make_bins(o.bin_len_dual, o.bin_rows_dual,
-                                default_limits(h.nnz, S, o.adaptive_step, h.m,
-                                               [&](int64_t i) { return h.rp[i + 1] - h.rp[i]; }));
+                                default_limits(h.nnz, S, long_chain(1), h.m, [&](int64_t i) { return h.rp[i + 1] - h.rp[i]; }));
     // rows: ">=" group then "=" group, each split into whole rows and rows
     // swept in S column slices (binned by their per-slice length), each
     // ordered by bin, stable
@@ -348,35 +432,7 @@ static void plan_instance(const HostLP &h, const pdhg_opts &o, InstPlan &p)
     std::vector<int64_t> cnt(h.n, 0);
     for (int64_t k = 0; k < h.nnz; ++k) cnt[h.ci[k]]++;
     const Bins tbins = make_bins(o.bin_len_primal, o.bin_rows_primal,
-                                 default_limits(h.nnz, St, o.adaptive_step, h.n, [&](int64_t j) { return cnt[j]; }));
-    // how many neighbouring entries of a row (of a column) share a line of the
-    // gathered vector, on four stretches of consecutive rows that start at the
-    // quarters of the entries (at the quarters of the rows, a dispatch LP's stretches
-    // mostly missed its 9% of rows with 92% of the entries)
-    constexpr int64_t STRETCH = 65536;
-    const int64_t ns = h.nnz > 4 * STRETCH ? 4 : 1;
-    std::vector<int32_t> last(h.n, INT32_MIN / 2);  // row of the column's entry before
-    std::vector<int32_t> line(h.n / 16 + 1, 0);     // last group with an entry in these columns
-    int32_t group = 0;
-    for (int64_t w = 0; w < ns; ++w) {
-        int64_t left = ns > 1 ? STRETCH : h.nnz, rows = 0, entries = 0;
-        ++group;
-        int64_t i = std::lower_bound(h.rp, h.rp + h.m, h.nnz * w / ns) - h.rp;
-        for (; i < h.m && left > 0; ++i) {
-            for (int64_t k = h.rp[i]; k < h.rp[i + 1]; ++k) {
-                const int32_t c = h.ci[k];
-                p.local[0] += (int32_t)i - last[c] < 32 ? 1 : -1;
-                last[c] = (int32_t)i;
-                if (k > h.rp[i]) p.local[1] += std::abs((int64_t)c - h.ci[k - 1]) < 32 ? 1 : -1;
-                p.apart += line[c >> 4] != group ? 1 : -1;
-                line[c >> 4] = group;
-            }
-            ++rows;
-            entries += h.rp[i + 1] - h.rp[i];
-            if (rows >= 16 || (rows >= 4 && entries >= 16384)) ++group, rows = entries = 0;
-            left -= h.rp[i + 1] - h.rp[i];
-        }
-    }
+                                 default_limits(h.nnz, St, long_chain(0), h.n, [&](int64_t j) { return cnt[j]; }));
     std::vector<std::vector<int32_t>> cb(2 * NBIN);
     for (int64_t j = 0; j < h.n; ++j) {
         const int sl = row_sliced_t(cnt[j], St) ? 1 : 0;
@@ -394,16 +450,12 @@ static void plan_instance(const HostLP &h, const pdhg_opts &o, InstPlan &p)
             p.segT.push_back(sh);
             p.col_order.insert(p.col_order.end(), v.begin(), v.end());
         }
+    if (!p.second) return;
     p.len[0].resize(h.n);
     p.len[1].resize(h.m);
     for (int64_t j = 0; j < h.n; ++j) p.len[0][j] = (int32_t)cnt[p.col_order[j]];
     for (int64_t i = 0; i < h.m; ++i) p.len[1][i] = (int32_t)(h.rp[p.row_order[i] + 1] - h.rp[p.row_order[i]]);
 }
-
-// Nonzeros of a handle whose operators are tiled at most: the tiles take about
-// 12 (FP32) or 20 bytes a nonzero beside the 32 of the row-binned operators, and
-// larger handles keep the card's memory for those.
-constexpr int64_t TILE_MAX_NNZ = (int64_t)4 << 30;
 
 // Lanes per row (log2) such that a lane has 2 to 4 fours of the row's entries in
 // a tile.  Measured, us (lg: 3 / 4 / 5): 31 fours a row and tile 34.4 / 36.1 /
@@ -415,27 +467,13 @@ static int32_t tile_lg(double fours)
     return l;
 }
 
-static bool small_size(int64_t es, const InstPlan &p);
-
-// Whether tile.hip sweeps an operator of the instance: its gathers must lack
-// locality (most neighbouring entries of a row on different 128-byte lines of
-// the vector; over local columns the row-binned sweeps' gathers cost little, and
-// they took 11 us where tiles took 22-29 on a dispatch LP of 3.7M nonzeros), and
-// with several tiles the matrix must pay for each tile's way through LDS.
-// Measured, us (row bins / tiles), planted LPs in FP32: one tile, 0.9M nonzeros
-// 6.5 / 6.0, 1.2M 8.3 / 6.6, 5M 23 / 11; two tiles, 2.0M 12.4 / 15.1, 5.0M 26 /
-// 12.3; four, 12M 57 / 24; below 0.9M see tile_blocks().  Small LPs take it in
-// any case, since small.hip sums as it does.
 static void plan_tile(int64_t es, InstPlan &p)
 {
     for (int op = 0; op < 2; ++op) {
         TilePlan &t = p.tile[op];
         const auto &segs = op == 0 ? p.segT : p.segK;
-        const int64_t cols = op == 0 ? p.m : p.n, rows = op == 0 ? p.n : p.m;
-        // a tile's first element lies anywhere in a 16-byte line, its width is a multiple of four
-        const int64_t cap = TILE_BYTES / es - 4, nt = (cols + cap - 1) / cap;
-        if (p.nnz == 0 || nt > TILE_SPLIT || (nt > 1 && p.nnz < 600000 + 2000000 * (nt - 1))) continue;
-        if (!small_size(es, p) && (p.nnz < 4 * rows * nt || p.local[op] > 0)) continue;
+        const int64_t cols = op == 0 ? p.m : p.n, nt = tile_count(es, p, op);
+        if (!tiled(es, p, op)) continue;
         if (std::any_of(segs.begin(), segs.end(), [](const SegH &g) { return g.sliced != 0; })) continue;
         t.ntile = (int32_t)nt;
         t.width = (int32_t)(((cols + nt - 1) / nt + 3) / 4 * 4);
@@ -501,17 +539,6 @@ static void small_rows_layout(const std::vector<int32_t> &len, const std::vector
                 sp.src[o].push_back(q < g && at < len[r] ? (int32_t)first[r] + at : ~own);
             }
     });
-}
-
-// Whether small.hip iterates the instance: the vectors fit a CU's LDS, no column
-// slices apply, and an iteration on one CU, whose time grows with the entries, is
-// shorter than two launches (8.5-9 us).  Measured, us per iteration (launches /
-// one CU): FP32 12.5k nonzeros 9.5 / 4.0, 22k 8.8 / 6.2, 30k 8.6 / 7.6, 50k 8.9 / 10.8; FP64
-// 2k 7.7 / 1.4, 12.5k 9.8 / 5.8, 27k 9.1 / 10.3.
-constexpr int64_t SMALL_ENTRY_BYTES = 150000;
-static bool small_size(int64_t es, const InstPlan &p)
-{
-    return (es + 2) * p.nnz <= SMALL_ENTRY_BYTES && small_bytes(p.n, p.m, es, 0, 0, 0, 0) <= SMALL_LDS;
 }
 
 static void plan_small(const HostLP &h, int64_t es, InstPlan &p)
@@ -968,7 +995,7 @@ static void tile_blocks(const std::vector<InstPlan> &plans, const pdhg_opts *o, 
         yo[b + 1] = yo[b] + plans[b].m;
     }
     for (int op = 0; op < 2; ++op) {
-        auto cost = [&](const InstPlan &p) { return (double)((es + 2) * p.nnz + 24 * (int64_t)p.len[op].size()); };
+        auto cost = [&](const InstPlan &p) { return (double)((es + 2) * p.nnz + 24 * (op == 0 ? p.n : p.m)); };
         double all = 0;
         for (const InstPlan &p : plans) all += cost(p);
         for (int b = 0; b < B; ++b) {
@@ -982,7 +1009,7 @@ static void tile_blocks(const std::vector<InstPlan> &plans, const pdhg_opts *o, 
                 continue;
             }
             const auto &segs = op == 0 ? p.segT : p.segK;
-            const int64_t rows = (int64_t)p.len[op].size(), ncol = op == 0 ? p.m : p.n;
+            const int64_t rows = op == 0 ? p.n : p.m, ncol = op == 0 ? p.m : p.n;
             const double own = cost(p), share = TILE_BLOCKS * own / (part * all);
             const double want = std::max(share, own / (2.0 * es * ncol));
             const int64_t nb = std::max<int64_t>(1, std::min<int64_t>({(int64_t)std::ceil(want), TILE_BLOCKS, (rows + 3) / 4}));
@@ -1061,7 +1088,7 @@ static void spread_windows(const InstPlan &p, int64_t es, Sizes &sz, TileBlocks 
         const auto &segs = op == 0 ? p.segT : p.segK;
         const int64_t cols = op == 0 ? p.m : p.n, nt = (cols + width - 1) / width;
         if (sz.tile_blk[op] > 0 || p.local[op] > 0 || p.apart < 0 || nt > SPREAD_TILES || p.nnz >= INT32_MAX) continue;
-        if (cols * es < (es == 4 ? 1500000 : 5000000) || p.nnz < 5000000) continue;
+        if (cols * es < (es == 4 ? 1500000 : 5000000) || p.nnz < SPREAD_NNZ) continue;
         if (std::any_of(segs.begin(), segs.end(), [](const SegH &g) { return g.sliced != 0; })) continue;
         auto &win = tb.win[op];
         int64_t entries = 0;
@@ -1115,8 +1142,8 @@ static int plan_all(const pdhg_lp *lp, int32_t batch, const pdhg_opts *o, std::v
                 msgs[b] = g_err;  // the message is per thread
                 return;
             }
-            plan_instance(hosts[b], *o, plans[b]);
-            if (layouts) {
+            plan_instance(hosts[b], *o, layouts, plans[b]);
+            if (plans[b].second) {
                 plan_tile((int64_t)elem_size(o->precision), plans[b]);
                 plan_small(hosts[b], (int64_t)elem_size(o->precision), plans[b]);
             }

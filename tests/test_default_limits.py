@@ -19,13 +19,13 @@ def _bytes(lp, **kw):
     return pd.lib().pdhg_workspace_bytes(C.cast(arr, C.c_void_p), 1, C.byref(pd.default_opts(**kw)))
 
 
-def _lp(lens, n, seed=1):
-    """Rows of the given lengths over n columns in a random cyclic order, so that
-    the columns' lengths differ by one at most."""
+def _lp(lens, n, local=False, seed=1):
+    """Rows of the given lengths over n columns in a random cyclic order (local: in
+    their own), so that the columns' lengths differ by one at most."""
     lens = np.asarray(lens)
-    rng = np.random.default_rng(seed)
+    order = np.arange(n) if local else np.random.default_rng(seed).permutation(n)
     rowptr = np.concatenate([[0], np.cumsum(lens)]).astype(np.int64)
-    col = rng.permutation(n)[np.arange(rowptr[-1]) % n].astype(np.int32)
+    col = order[np.arange(rowptr[-1]) % n].astype(np.int32)
     return lpgen.LP(n, lens.size, rowptr, col, np.ones(col.size), np.zeros(lens.size, dtype=np.uint8),
                     np.zeros(lens.size), np.ones(n), np.zeros(n), np.ones(n))
 
@@ -38,6 +38,8 @@ CASES = {
     "200022": (np.full(200022 // 37, 37), 6667, {}, 8, 8),
     "999999": (np.full(999999 // 37, 37), 33333, dict(adaptive_step=1), 4, 4),
     "1000036": (np.full(1000036 // 37, 37), 33333, dict(adaptive_step=1), 8, 8),
+    "local": (np.full(16000, 37), 20000, dict(local=True), 4, 8),  # K over local columns: row bins
+    "local_more": (np.full(1000036 // 37, 37), 33333, dict(local=True), 8, 8),
     "half_long": (np.r_[np.full(100, 30), np.full(10, 300)], 660, {}, 4, 4),  # 3,000 and 3,000 entries
     "more_long": (np.r_[np.full(100, 30), np.full(11, 300)], 700, {}, 8, 4),
     "sliced": (np.full(1000036 // 37, 37), 33333, dict(col_slices=2), 4, 8),
@@ -48,7 +50,8 @@ CASES = {
 @pytest.mark.parametrize("name", sorted(CASES))
 def test_default_limits(name):
     lens, n, kw, dual, primal = CASES[name]
-    lp = _lp(lens, n)
+    kw = dict(kw)
+    lp = _lp(lens, n, kw.pop("local", False))
     for prec in ("f32", "f64"):
         got = {(a, b): _bytes(lp, precision=prec, bin_len_dual=LIM[a], bin_len_primal=LIM[b], **kw)
                for a in LIM for b in LIM}

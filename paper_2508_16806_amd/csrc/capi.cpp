@@ -2614,7 +2614,9 @@ static int fish_build_tables(pdhg_handle *h, hipStream_t s)
         int64_t entries = 0;
         for (auto t = shrt; t != tasks.end(); ++t) entries += t->z - t->y;
         const int64_t few = std::max<int64_t>(1, tasks.end() - shrt);
-        (op == 0 ? f.lenK : f.lenT) = (int32_t)((entries + few - 1) / few);
+        // a few long rows among short ones are the sweep's last to end: their length counts
+        const int32_t longest = shrt == tasks.end() ? 0 : shrt->z - shrt->y;
+        (op == 0 ? f.lenK : f.lenT) = longest > 32 ? longest : (int32_t)((entries + few - 1) / few);
         int32_t *rows = (int32_t *)(op == 0 ? f.rowK : f.rowT);
         int4 *tk = (int4 *)(op == 0 ? f.taskK : f.taskT);
         int4 *sp = (int4 *)(op == 0 ? f.splitK : f.splitT);

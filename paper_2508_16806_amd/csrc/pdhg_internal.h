@@ -202,7 +202,7 @@ struct FishDev {
     const int4 *splitK, *splitT;
     int64_t ntaskK, ntaskT, nsplitK, nsplitT;
     int64_t nlongK, nlongT;     // tasks (the first ones) longer than FISH_LONG entries
-    int32_t lenK, lenT;         // mean entries of the others, rounded up
+    int32_t lenK, lenT;         // entries of the others that set their lanes
     double *cpart;              // chunk partials, slots x PS
     double *part;               // per-workgroup gap partials, FISH_GRID x PS
     double *wmat;               // repopulation weights, (PS/2) x (PS/2)

@@ -510,14 +510,15 @@ static void small_rows_layout(const std::vector<int32_t> &len, const std::vector
         return std::max(sweep[r] - 2, std::min(l, sweep[r]));
     };
     auto tasks = [&](int cap, auto &&f) {
-        int cnt = 0;
-        for (int k = 0; k < nr; ++cnt) {
+        int cnt = 0;  // tasks with entries
+        for (int k = 0; k < nr;) {
             const int l = lanes_log2(ord[k], cap), most = 64 >> l;
             int g = 0;
             while (k + g < nr && g < most && lanes_log2(ord[k + g], cap) == l && sweep[ord[k + g]] == sweep[ord[k]] &&
                    (len[ord[k + g]] > 0) == (len[ord[k]] > 0))
                 ++g;
             f(k, g, l);
+            cnt += len[ord[k]] > 0;
             k += g;
         }
         return cnt;

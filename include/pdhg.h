@@ -122,10 +122,10 @@ typedef struct {
      * <= bin_len[k] (and above bin k-1's limit) and sweeps each with 2^k lanes
      * (k = 0..6) or a whole 256-lane workgroup (k = 7).  0 leaves the
      * limit to the library: 8, 16, 32, 64, 128, 256, 512, inf; for sweeps in
-     * column slices, and on LPs of fewer than 1e6 nonzeros (2e5 where the fixed
-     * steps without adaptive_step are not PDHG_SWEEP_ROWS) for operators with
-     * at least half of their entries in rows of 5 to 256, 4, 8, 16, 32, 64,
-     * 128, 512, inf. */
+     * column slices, and on LPs of fewer than 1e6 nonzeros (5e5 over local
+     * columns; 2e5 where the fixed steps without adaptive_step are not
+     * PDHG_SWEEP_ROWS) for operators with at least half of their entries in
+     * rows of 5 to 256, 4, 8, 16, 32, 64, 128, 512, inf. */
     int32_t bin_len_dual[8];   /* rows of K   (dual sweep)                        */
     int32_t bin_len_primal[8]; /* rows of K^T (primal sweep)                      */
     /* Rows handled by one lane group in bins 0..4 (1, 2 or 4; 0 means 1): the

@@ -343,14 +343,16 @@ static Bins make_bins(const int32_t *lim, const int32_t *rows, int f)
 // has lanes to spare: adaptive primal + dual sweep with 4 * 2^k and 8 * 2^k, random
 // LPs of 12k nonzeros 12.3 / 16.6, 50k 10.7 / 12.5, 250k 12.2 / 13.9, 0.5M 13.2 / 15.4,
 // 0.8M 12.8 / 13.7, 1.0M 15.2 / 15.6, 2.0M 26.6 / 24.8; fixed steps of a network LP
-// of 0.4M (256 and their checks, ms) 3.54 / 3.74.  Where fixed steps take tiles the
-// limits concern the checks, once in a check period, which gain earlier: random LPs
+// of 0.4M (256 and their checks, ms) 3.54 / 3.74.  Gathers from shared lines are
+// shorter links of the chain: dispatch LPs of 0.4M 10.2 / 10.1 us an iteration, 0.5M
+// (FP64) 10.6 / 10.7, 0.7M 12.4 / 11.0.  Where fixed steps take tiles the limits
+// concern the checks, once in a check period, which gain earlier: random LPs
 // of 12k nonzeros 8.0 / 8.8, 40k 8.5 / 9.8, 200k 13.4 / 11.0, 0.8M 22.5 / 18.6.  The
 // two differ in the lanes of rows of 5 to 256 entries only: where these hold less than
 // half of the entries, 8 * 2^k everywhere (20,000 rows of 2 entries 5.4 / 4.7 and
 // 5.6 / 5.6).  Sliced rows are gathered a piece at a time and take 4 * 2^k: 4 / 2
 // slices on 5.3M nonzeros 22.2 / 27.1 us primal, on 1.1M dual 21.8 / 22.8.
-constexpr int64_t SHORT_CHAIN_NNZ = 1000000, SHORT_CHAIN_NNZ_TILED = 200000;
+constexpr int64_t SHORT_CHAIN_NNZ = 1000000, SHORT_CHAIN_NNZ_LOCAL = 500000, SHORT_CHAIN_NNZ_TILED = 200000;
 template <typename F>
 static int default_limits(int64_t nnz, int S, int64_t long_chain, int64_t rows, F &&len)
 {
@@ -400,6 +402,7 @@ static void plan_instance(const HostLP &h, const pdhg_opts &o, bool second, Inst
     if (p.second && !small_size(es, p)) sample_locality(h, p);
     // nonzeros from which on the operator's default limits are 8 * 2^k
     auto long_chain = [&](int op) {
+        if (p.local[op] > 0) return SHORT_CHAIN_NNZ_LOCAL;
         return o.adaptive_step || !tiled(es, p, op) ? SHORT_CHAIN_NNZ : SHORT_CHAIN_NNZ_TILED;
     };
     const Bins bins = make_bins(o.bin_len_dual, o.bin_rows_dual,

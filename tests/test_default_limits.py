@@ -38,8 +38,9 @@ CASES = {
     "200022": (np.full(200022 // 37, 37), 6667, {}, 8, 8),
     "999999": (np.full(999999 // 37, 37), 33333, dict(adaptive_step=1), 4, 4),
     "1000036": (np.full(1000036 // 37, 37), 33333, dict(adaptive_step=1), 8, 8),
-    "local": (np.full(16000, 37), 20000, dict(local=True), 4, 8),  # K over local columns: row bins
-    "local_more": (np.full(1000036 // 37, 37), 33333, dict(local=True), 8, 8),
+    "local": (np.full(13513, 37), 16666, dict(local=True), 4, 8),  # K over local columns: row bins
+    "local_more": (np.full(13514, 37), 16667, dict(local=True), 8, 8),
+    "local_adaptive": (np.full(13514, 37), 16667, dict(local=True, adaptive_step=1), 8, 4),
     "half_long": (np.r_[np.full(100, 30), np.full(10, 300)], 660, {}, 4, 4),  # 3,000 and 3,000 entries
     "more_long": (np.r_[np.full(100, 30), np.full(11, 300)], 700, {}, 8, 4),
     "sliced": (np.full(1000036 // 37, 37), 33333, dict(col_slices=2), 4, 8),

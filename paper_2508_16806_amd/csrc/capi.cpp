@@ -278,7 +278,7 @@ static bool tiled(int64_t es, const InstPlan &p, int op)
 // Least nonzeros of an operator that spread.hip sweeps (spread_windows()).
 constexpr int64_t SPREAD_NNZ = 5000000;
 
-// The pattern's locality, where a second layout hangs on it.
+// The pattern's locality, where a second layout or the default limits hang on it.
 static void sample_locality(const HostLP &h, InstPlan &p)
 {
     // how many neighbouring entries of a row (of a column) share a line of the
@@ -397,9 +397,11 @@ static void plan_instance(const HostLP &h, const pdhg_opts &o, bool second, Inst
     p.m = h.m;
     p.m1 = h.m1;
     p.nnz = h.nnz;
-    p.second = second && (small_size(es, p) || tile_count(es, p, 0) > 0 || tile_count(es, p, 1) > 0 ||
-                          p.nnz >= SPREAD_NNZ);
-    if (p.second && !small_size(es, p)) sample_locality(h, p);
+    const bool sizes = small_size(es, p) || tile_count(es, p, 0) > 0 || tile_count(es, p, 1) > 0 || p.nnz >= SPREAD_NNZ;
+    p.second = second && sizes;
+    // the limits hang on it too, so that a plan without second layouts is the same
+    // where the LP has none anyway
+    if (sizes && !small_size(es, p)) sample_locality(h, p);
     // nonzeros from which on the operator's default limits are 8 * 2^k
     auto long_chain = [&](int op) {
         if (p.local[op] > 0) return SHORT_CHAIN_NNZ_LOCAL;

@@ -117,7 +117,7 @@ typedef struct {
     int32_t unroll_capacity;   /* max steps pdhg_iterate may record (0: none)       */
     int32_t unroll_checkpoint; /* checkpoint spacing C for the adjoint replay       */
     int32_t use_graph;         /* capture iteration chunks in a hipGraph            */
-    int32_t xcd_remap;         /* XCD-contiguous workgroup numbering                */
+    int32_t xcd_remap;         /* XCD-contiguous workgroup numbering (row bins)     */
     /* Row-length bins (autotuner output).  Bin k takes rows of length
      * <= bin_len[k] (and above bin k-1's limit) and sweeps each with 2^k lanes
      * (k = 0..6) or a whole 256-lane workgroup (k = 7).  0 leaves the
@@ -264,7 +264,7 @@ typedef struct {
     int32_t precision, batch;
     int64_t workspace_bytes;
     int32_t nseg_primal, nseg_dual; /* row-length bins in use                     */
-    int64_t nblk_primal, nblk_dual; /* workgroups per primal / dual sweep         */
+    int64_t nblk_primal, nblk_dual; /* blocks of rows per row-binned sweep         */
     /* phases of setup_seconds: validation and row binning, building the
      * device images of K~ and K~^T on the host, copying them to the device,
      * and the device work (Ruiz scaling, FP32 copies, power iteration) */
@@ -361,7 +361,9 @@ int pdhg_iterate(pdhg_handle *h, int64_t k, int32_t record, hipStream_t stream);
 /* Full restarted solve to opts.eps (Sections 2.3-2.4) from the handle's
  * current iterate.  Blocks until every instance has stopped; res points to
  * `batch` results.  Every instance of a batch follows exactly the iteration,
- * check and restart sequence it would follow alone. */
+ * check and restart sequence it would follow alone, bit for bit where both
+ * handles have the sweeps' second layouts or neither (a batch of more than
+ * 2^32 nonzeros and a workspace below pdhg_workspace_bytes have none). */
 int pdhg_solve(pdhg_handle *h, pdhg_result *res, hipStream_t stream);
 
 /* Writes instance `inst`'s point (which = PDHG_SOL_*) in the ORIGINAL
